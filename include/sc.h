@@ -82,7 +82,9 @@ typedef struct sc_params {
     double rho_ref;            /* storage shift; < 0 selects 0 for F32 and rho_liquid for 16-bit */
     void* stream;              /* hipStream_t to run on; NULL: the library creates one */
     const sc_allocator* allocator; /* NULL: hipMalloc / hipFree */
-    int32_t tile_x, tile_y, tile_z; /* step-kernel tile; 0 selects the tuned default */
+    int32_t tile_x, tile_y, tile_z; /* step-kernel tile; 0 selects the default (all four fields 0:
+                                       in D3Q19 a tile fitted to the box, of any width and height,
+                                       which sc_step_config reports but no field here accepts) */
     int32_t step_variant;      /* 0 default, 1 plain marching, 2 software-pipelined (D3Q19),
                                   3 plain with non-temporal population stores; with two
                                   components also 4 and 5 (D3Q19, one component per wave) */

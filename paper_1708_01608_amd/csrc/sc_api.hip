@@ -312,6 +312,91 @@ StepShape default_shape(const sc_params& p)
     return sh;
 }
 
+// Estimated time (us) of one D3Q19 step launch with this tile: rounds of resident blocks, each
+// marching its planes (and the prologue's) at the slowest of the plane latency, the memory
+// traffic and the arithmetic of a round's blocks.  The constants were fitted to the measured
+// times of 1,800 shapes on 25 boxes of 60 x 60 x 60 to 300 x 200 x 100 and 256^3, one and two
+// components, FP32 and 16-bit storage: the shape it picks is on average 1% (one component up to
+// 5%) slower than the fastest of those measured.
+double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
+{
+    const bool mix = p.components == 2, f64 = compute == SC_COMPUTE_F64;
+    const bool nt = s.variant == 3 || s.variant == 5;
+    const double es = (double)storage_bytes(p.storage), pops = mix ? 38 : 19;
+    const int tw = s.tile_x, th = s.tile_y;
+    const int waves = (tw * th + 63) / 64, ring_waves = (2 * (tw + 2) + 2 * th + 63) / 64;
+    const int bw = mix ? 2 * waves : waves;
+    int res = std::max(1, 16 / bw);  // blocks a CU holds: 16 waves of at most 128 registers
+    if (mix) {
+        const size_t lds = mix3d_split_lds(tw, th, f64 ? sizeof(double) : sizeof(float));
+        res = std::max(1, std::min(res, (int)((size_t)160 * 1024 / lds)));
+    }
+    const int64_t nb = (int64_t)((p.nx + tw - 1) / tw) * ((p.ny + th - 1) / th) *
+                       ((p.nz + s.tile_z - 1) / s.tile_z);
+    const int64_t slots = 256 * (int64_t)res;
+    // beyond what the last-level cache holds, stores that bypass L2 pay; rows that start and end
+    // inside a cache line cost the shared line again, for such stores most of all
+    const bool resident = (double)p.nx * p.ny * p.nz * 2 * pops * es < 230e6;
+    const bool aligned = std::fmod(p.nx * es, 128.0) == 0.0 && std::fmod(tw * es, 128.0) == 0.0;
+    const double edge_ld = aligned ? 0.0 : 0.65 * 128, edge_st = aligned ? 0.0 : (nt ? 1.8 : 1.0) * 128;
+    const double runs = tw == p.nx ? 1 : th, run = tw == p.nx ? tw * th * es : tw * es;
+    auto plane = [&](int64_t blocks) {
+        const double bytes = pops * (double)blocks *
+                             (runs * (2 * run + edge_ld + edge_st) +
+                              0.25 * 2 * (tw * es + edge_ld) + 2 * th * 128 * 0.32);
+        const double work = (double)((blocks + 255) / 256) * (bw + 0.6 * ring_waves * (mix ? 2 : 1)) *
+                            0.32 * (f64 ? 1.0 : 0.6);
+        return std::max({mix ? 4.3 : 3.6, bytes / 5.9e6, work});
+    };
+    double t = (double)(nb / slots) * plane(slots);
+    if (nb % slots) t += plane(nb % slots);
+    t *= s.tile_z + 1.3;
+    if (resident && nt) t *= 1.06;
+    if (!resident && aligned && !nt) t *= 1.05;
+    return t;
+}
+
+// Tile of an untuned D3Q19 box: the box's row cut into equal parts, as many rows as the block
+// then has threads for, cut evenly too, and equal chunks of planes; the cheapest by the estimate
+// above.  A power-of-two tile leaves lanes without a node (203 nodes in 256 lanes) and its last
+// round of blocks half empty: bf16 203 x 150 x 121 104 us with the fixed 32 x 8 x 16 tile, 95 us
+// with the best power-of-two one, 80 us with 203 x 5 x 16.
+StepShape fitted_shape(const sc_params& p, int compute)
+{
+    StepShape best = default_shape(p);
+    if (p.lattice != SC_D3Q19) return best;
+    const bool mix = p.components == 2;
+    const size_t es = compute == SC_COMPUTE_F64 ? sizeof(double) : sizeof(float);
+    double cost = 1e300;
+    for (int b : {128, 256, 384, 512, 768, 1024}) {
+        if (mix && b > 512) break;
+        int last_tw = 0;
+        for (int gx = 1; gx <= 64; ++gx) {
+            const int tw = (p.nx + gx - 1) / gx;
+            if (gx > 1 && tw < 16) break;
+            if (tw > b / 3 || tw == last_tw) continue;
+            last_tw = tw;
+            const int rows = b / tw, gy = (p.ny + rows - 1) / rows, th = (p.ny + gy - 1) / gy;
+            int last_tz = 0;
+            for (int gz = 1; gz <= p.nz; ++gz) {
+                const int tz = (p.nz + gz - 1) / gz;
+                if (tz == last_tz || tz > 512) continue;
+                last_tz = tz;
+                for (int v : {1, 3}) {
+                    const StepShape s{tw, th, tz, mix ? v + (v == 1 ? 3 : 2) : v};
+                    if (!(mix ? mix3d_tile_fits(s, es) : step3d_tile_fits(s))) continue;
+                    const double c = shape3d_cost(p, compute, s);
+                    if (c < cost) {
+                        cost = c;
+                        best = s;
+                    }
+                }
+            }
+        }
+    }
+    return best;
+}
+
 // Shapes chosen by sc_autotune, per (lattice, nx, ny, nz, storage, compute, components), for
 // this process.
 using TuneKey = std::tuple<int, int, int, int, int, int, int>;
@@ -339,7 +424,7 @@ std::vector<StepShape> tune_candidates(int q)
     return c;
 }
 
-std::vector<StepShape> tune_candidates_2c(int q)
+std::vector<StepShape> tune_candidates_2c(int q, int nz)
 {
     std::vector<StepShape> c;
     if (q == SC_D2Q9) {
@@ -349,8 +434,9 @@ std::vector<StepShape> tune_candidates_2c(int q)
     } else {
         const int tiles[][2] = {{32, 4}, {32, 8}, {64, 4}, {64, 8}, {128, 4}};
         for (auto& t : tiles)
-            for (int tz : {16, 32, 64})
-                for (int v : {1, 3, 4, 5}) c.push_back(StepShape{t[0], t[1], tz, v});
+            for (int tz : {16, 32, 64, 128})
+                for (int v : {1, 3, 4, 5})
+                    if (tz < 128 || nz >= 128) c.push_back(StepShape{t[0], t[1], tz, v});
     }
     return c;
 }
@@ -1225,6 +1311,7 @@ int sc_create(const sc_params* p, sc_sim** out)
                      : (p->storage == SC_STORE_F32 ? SC_COMPUTE_F64 : SC_COMPUTE_F32);
     s->shape = shape_from_params(*p);
     if (!(p->tile_x || p->tile_y || p->tile_z || p->step_variant)) {
+        s->shape = fitted_shape(*p, s->compute);
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(tune_key(*p, s->compute));
         if (it != g_tuned.end()) s->shape = it->second;
@@ -2127,7 +2214,7 @@ int sc_autotune(sc_sim* s, int32_t trials, sc_tune_entry* out, int32_t cap, int3
     if (trials < 1 || cap < 0 || (cap > 0 && !out)) return fail(SC_E_INVAL, "bad autotune arguments");
     StepArgs a = step_args(s);
     const Step2cArgs a2 = step2c_args(s);
-    const std::vector<StepShape> cand = s->two ? tune_candidates_2c(s->q) : tune_candidates(s->q);
+    const std::vector<StepShape> cand = s->two ? tune_candidates_2c(s->q, s->p.nz) : tune_candidates(s->q);
     // one step current -> spare buffers (the state itself is left as it is)
     auto launch = [&](const StepShape& sh) {
         if (s->two)

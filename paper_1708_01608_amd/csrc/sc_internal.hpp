@@ -41,6 +41,7 @@ size_t storage_bytes(int storage);
 
 // --- step kernels (sc_step.hip) ------------------------------------------------------------
 bool step_shape_supported(int q, const StepShape& s);
+bool step3d_tile_fits(const StepShape& s);
 bool step_combo_supported(int storage, int compute);
 hipError_t launch_step(int q, int storage, int compute, const void* src, void* dst,
                        const StepArgs& a, const StepShape& s, hipStream_t st);
@@ -57,6 +58,8 @@ struct Step2cArgs {
     double ref_l, ref_v;  // storage shifts of the two components (0 with FP32 storage)
 };
 bool step2c_shape_supported(int q, const StepShape& s);
+size_t mix3d_split_lds(int tx, int ty, size_t es);
+bool mix3d_tile_fits(const StepShape& s, size_t es);
 // FP32 storage runs FP64 arithmetic, FP16 / BF16 storage FP32 arithmetic.
 hipError_t launch_step2c(int q, int storage, const void* src_l, const void* src_v, void* dst_l,
                          void* dst_v, const Step2cArgs& a, const StepShape& s, hipStream_t st);

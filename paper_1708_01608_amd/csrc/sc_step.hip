@@ -128,30 +128,18 @@ __global__ void __launch_bounds__(TX) k_step2d(const S* __restrict__ src, S* __r
     }
 }
 
-// Ring cell (hlx, hly) of thread t in the psi tile of a wx x wy tile: the rows below and above
-// (wx + 2 cells each, corners included), then the left and right columns (wy cells each).
-__device__ __forceinline__ void ring_cell(int t, int wx, int wy, int& hlx, int& hly)
-{
-    if (t < wx + 2) {
-        hlx = t; hly = 0;
-    } else if (t < 2 * (wx + 2)) {
-        hlx = t - (wx + 2); hly = wy + 1;
-    } else if (t < 2 * (wx + 2) + wy) {
-        hlx = 0; hly = 1 + t - 2 * (wx + 2);
-    } else {
-        hlx = wx + 1; hly = 1 + t - 2 * (wx + 2) - wy;
-    }
-}
-
 // ------------------------------------------------------------------------------------------
-// D3Q19: a block owns a TX x TY tile of an x-y plane and marches `planes` planes in z.
+// D3Q19: a block owns a tw x th tile of an x-y plane (any tw th <= B) and marches `planes` planes
+// in z.  The tile is a launch argument: the host fits it to the box, so that no lane idles where a
+// power of two would overhang it.
 // ------------------------------------------------------------------------------------------
-template <typename S, typename A, int TX, int TY, bool NT = false, bool EXT = false>
-__global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S* __restrict__ dst,
-                                                   StepArgs a, StepGrid grid)
+template <typename S, typename A, int B, bool NT = false, bool EXT = false>
+__global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __restrict__ dst,
+                                              StepArgs a, StepGrid grid)
 {
     using L = lat<19>;
-    __shared__ A ps[4][TY + 2][TX + 2];
+    extern __shared__ double ring_lds[];
+    A* const ps = reinterpret_cast<A*>(ring_lds);  // psi of four planes: [4][th + 2][tw + 2]
     const Coef<A> c = coef_of(a, A());
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t N = a.N;
@@ -160,32 +148,27 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
     const int by = (lb / grid.gx) % grid.gy;
     const int bz = lb / (grid.gx * grid.gy);
     const int t = threadIdx.x;
-    const int tx = t % TX, ty = t / TX;
-    const int x0 = bx * TX, y0 = by * TY, z0 = bz * a.planes;
-    const int wx = min(TX, nx - x0), wy = min(TY, ny - y0);
+    const int tw = grid.tw, th = grid.th;
+    const int pw = tw + 2, psz = pw * (th + 2);  // row pitch and size of a plane slot
+    const int x0 = bx * tw, y0 = by * th, z0 = bz * a.planes;
+    const int wx = min(tw, nx - x0), wy = min(th, ny - y0);
     const int ze = min(z0 + a.planes, nz);
+    const int ty = t / tw, tx = t - ty * tw;
     const bool own = tx < wx && ty < wy;
     const int x = x0 + (own ? tx : 0), y = y0 + (own ? ty : 0);
     const int xm = wrap_once(x - 1, nx), xp = wrap_once(x + 1, nx);
     const int ym = wrap_once(y - 1, ny), yp = wrap_once(y + 1, ny);
 
-    // ring node of this thread (at most one: the host checks 2 (TX + 2) + 2 TY <= TX TY)
-    const int nring = 2 * (wx + 2) + 2 * wy;
-    const bool ring = t < nring;
+    // ring node of this thread (at most one: the host checks 2 (tw + 2) + 2 th <= threads)
+    const bool ring = t < 2 * (wx + 2) + 2 * wy;
     int hlx, hly;
-    if (t < wx + 2) {
-        hlx = t; hly = 0;
-    } else if (t < 2 * (wx + 2)) {
-        hlx = t - (wx + 2); hly = wy + 1;
-    } else if (t < 2 * (wx + 2) + wy) {
-        hlx = 0; hly = 1 + t - 2 * (wx + 2);
-    } else {
-        hlx = wx + 1; hly = 1 + t - 2 * (wx + 2) - wy;
-    }
-    const int hx = wrap_once(x0 - 1 + (ring ? hlx : 1), nx);
-    const int hy = wrap_once(y0 - 1 + (ring ? hly : 1), ny);
+    ring_cell(t, wx, wy, hlx, hly);
+    if (!ring) hlx = hly = 1;
+    const int hx = wrap_once(x0 - 1 + hlx, nx), hy = wrap_once(y0 - 1 + hly, ny);
     const int hxm = wrap_once(hx - 1, nx), hxp = wrap_once(hx + 1, nx);
     const int hym = wrap_once(hy - 1, ny), hyp = wrap_once(hy + 1, ny);
+    const int pc0 = pw * ((own ? ty : 0) + 1) + (own ? tx : 0) + 1;  // own and ring cell in a slot
+    const int ph0 = pw * hly + hlx;
 
     float cur[19], nxt[19];
     A dcur = (A)0, dnxt = (A)0;
@@ -196,12 +179,12 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
         if (own) {
             float g[19];
             pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
-            ps[0][ty + 1][tx + 1] = psi_f(c.rho_ref + sum_dev<19, A>(g));
+            ps[pc0] = psi_f(c.rho_ref + sum_dev<19, A>(g));
         }
         if (ring) {
             float h[19];
             pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
-            ps[0][hly][hlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
+            ps[ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
     }
     {
@@ -210,12 +193,12 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
         if (own) {
             pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, cur);
             dcur = sum_dev<19, A>(cur);
-            ps[1][ty + 1][tx + 1] = psi_f(c.rho_ref + dcur);
+            ps[psz + pc0] = psi_f(c.rho_ref + dcur);
         }
         if (ring) {
             float h[19];
             pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
-            ps[1][hly][hlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
+            ps[psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
     }
 
@@ -230,22 +213,22 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
             if (own) {
                 pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, zn, zm, zp, ld);
                 dld = sum_dev<19, A>(ld);
-                ps[sn][ty + 1][tx + 1] = psi_f(c.rho_ref + dld);
+                ps[sn * psz + pc0] = psi_f(c.rho_ref + dld);
             }
             if (ring) {
                 float h[19];
                 pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, zn, zm, zp, h);
-                ps[sn][hly][hlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
+                ps[sn * psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
             }
         }
         __syncthreads();
         if (own) {
-            const A pc = ps[s][ty + 1][tx + 1];
+            const A pc = ps[s * psz + pc0];
             A fx, fy, fz;
             interaction_sum<19, A>(
                 [&](int i) {
                     const int slot = L::ez[i] > 0 ? sn : (L::ez[i] < 0 ? sp : s);
-                    return ps[slot][ty + 1 + L::ey[i]][tx + 1 + L::ex[i]];
+                    return ps[slot * psz + pc0 + L::ey[i] * pw + L::ex[i]];
                 },
                 fx, fy, fz);
             const A gp = -c.G * pc;
@@ -259,51 +242,54 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
             if (z + 1 < ze) plane(z + 1, nxt, cur, dnxt, dcur);
         }
     } else {
-    for (int z = z0; z < ze; ++z) {
-        const int s = (z - z0 + 1) & 3;
-        const int sn = (s + 1) & 3, sp = (s + 3) & 3;
-        {
+        // the cell of this thread in the tile and its ring cell, two to a register
+        const int cell = own ? tx + (ty << 16) : 0, rcell = hlx + (hly << 16);
+        for (int z = z0; z < ze; ++z) {
+            const int s = (z - z0 + 1) & 3;
+            const int sn = (s + 1) & 3, sp = (s + 3) & 3;
             // FP64 arithmetic fills the 128 VGPRs of a 1024-thread block, so the loop is shaped
-            // for registers: every lane loads plane z+1 (a lane outside a ragged tile its clamped
-            // in-box node, harmlessly) and the ring's loads and sum form one block, so both sets
-            // of loads are in flight together and none is left pending past the sums (a pending
+            // for registers: every lane loads plane z+1 (a lane without a node the tile's first
+            // node, harmlessly) and the ring's loads and sum form one block, so both sets of
+            // loads are in flight together and none is left pending past the sums (a pending
             // load would make the copy into cur wait for every store of the plane); coordinates
-            // are derived from the thread index where they are used rather than held across
-            // the loop (held, they spill, and each reload waits for all loads in flight)
+            // are derived from the packed cells where they are used rather than held across the
+            // loop (held, they spill, and each reload waits for all loads in flight)
             {
                 const int zn = wrap_once(z + 1, nz);
                 const int zm = wrap_once(zn - 1, nz), zp = wrap_once(zn + 1, nz);
-                const int tt = opaque(t);
-                const int ltx = tt % TX, lty = tt / TX;
                 {
-                    const int ox = x0 + min(ltx, wx - 1), oy = y0 + min(lty, wy - 1);
+                    const int cc = opaque(cell);
+                    const int ox = x0 + (cc & 0xffff), oy = y0 + (cc >> 16);
                     pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, nxt);
                 }
                 if (ring) {
-                    int rlx, rly;
-                    ring_cell(tt, wx, wy, rlx, rly);
+                    const int cc = opaque(rcell);
+                    const int rlx = cc & 0xffff, rly = cc >> 16;
                     const int ox = wrap_once(x0 - 1 + rlx, nx), oy = wrap_once(y0 - 1 + rly, ny);
                     float h[19];
                     pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, h);
-                    ps[sn][rly][rlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
+                    ps[sn * psz + pw * rly + rlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
                 }
                 dnxt = sum_dev<19, A>(nxt);
-                if (own) ps[sn][lty + 1][ltx + 1] = psi_f(c.rho_ref + dnxt);
+                const int cc = opaque(cell);
+                const A pn = psi_f(c.rho_ref + dnxt);
+                if (own) ps[sn * psz + pw * ((cc >> 16) + 1) + (cc & 0xffff) + 1] = pn;
             }
             __syncthreads();
             if (own) {
-                const int tt = opaque(t);
-                const int ltx = tt % TX, lty = tt / TX;
-                const A pc = ps[s][lty + 1][ltx + 1];
+                const int cc = opaque(cell);
+                const int ltx = cc & 0xffff, lty = cc >> 16;
+                const int pc1 = pw * (lty + 1) + ltx + 1;
+                const A pc = ps[s * psz + pc1];
                 A fx, fy, fz;
                 interaction_sum<19, A>(
                     [&](int i) {
                         const int slot = L::ez[i] > 0 ? sn : (L::ez[i] < 0 ? sp : s);
-                        return ps[slot][lty + 1 + L::ey[i]][ltx + 1 + L::ex[i]];
+                        return ps[slot * psz + pc1 + L::ey[i] * pw + L::ex[i]];
                     },
                     fx, fy, fz);
                 const A gp = -c.G * pc;
@@ -311,13 +297,13 @@ __global__ void __launch_bounds__(TX* TY) k_step3d(const S* __restrict__ src, S*
                 collide_store<19, A, S, NT, EXT, true>(dst, N, (uint32_t)(ox + nx * (oy + ny * z)),
                                                       cur, dcur, gp * fx, gp * fy, gp * fz, c);
             }
-        }
 #pragma unroll
-        for (int i = 0; i < 19; ++i) cur[i] = nxt[i];
-        dcur = dnxt;
-    }
+            for (int i = 0; i < 19; ++i) cur[i] = nxt[i];
+            dcur = dnxt;
+        }
     }
 }
+
 // ------------------------------------------------------------------------------------------
 // D3Q19, software-pipelined: the loads of plane z+2 are issued before plane z is collided, so a
 // wave keeps a plane of loads in flight through its collision and stores.  Ring nodes go to the
@@ -556,6 +542,15 @@ bool step_shape_supported(int q, const StepShape& s)
     return false;
 }
 
+// What k_step3d needs of a tile: a thread for every node and for every ring node, cells that fit
+// 16 bits.
+bool step3d_tile_fits(const StepShape& s)
+{
+    const int tx = s.tile_x, ty = s.tile_y;
+    return (s.variant == 1 || s.variant == 3) && s.tile_z >= 1 && tx >= 1 && ty >= 1 &&
+           tx <= 1024 && ty <= 1024 && tx * ty <= 1024 && 2 * (tx + 2) + 2 * ty <= tx * ty;
+}
+
 template <typename S, typename A>
 static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, const StepShape& s,
                              hipStream_t st)
@@ -570,8 +565,9 @@ static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, con
         g.gy = (a.ny + s.tile_y - 1) / s.tile_y;
         g.gz = (a.nz + a.planes - 1) / a.planes;
     }
+    g.tw = s.tile_x;
+    g.th = s.tile_y;
     const int nb = g.gx * g.gy * g.gz;
-    g.remap = (nb % 8 == 0) ? 1 : 0;
     dim3 grid(nb);
     // the extended kernels (gravity) exist for the marching variants only
     const bool ext = a.grav != 0;
@@ -594,35 +590,40 @@ static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, con
             hipLaunchKernelGGL((k_step2d<S, A, TX>), grid, dim3(TX), 0, st, src, dst, a, g);     \
         return hipGetLastError();                                                                \
     }
-#define SC_L3(TX, TY)                                                                            \
+#define SC_L3P(TX, TY)                                                                           \
     if (s.tile_x == TX && s.tile_y == TY) {                                                      \
-        if (ext) {                                                                               \
-            if (s.variant == 3)                                                                  \
-                hipLaunchKernelGGL((k_step3d<S, A, TX, TY, true, true>), grid,                   \
-                                   dim3(TX * TY), 0, st, src, dst, a, g);                        \
-            else                                                                                 \
-                hipLaunchKernelGGL((k_step3d<S, A, TX, TY, false, true>), grid,                  \
-                                   dim3(TX * TY), 0, st, src, dst, a, g);                        \
-            return hipGetLastError();                                                            \
-        }                                                                                        \
-        if (s.variant == 2)                                                                      \
-            hipLaunchKernelGGL((k_step3d_pipe<S, A, TX, TY>), grid, dim3(TX * TY), 0, st, src,   \
-                               dst, a, g);                                                       \
+        hipLaunchKernelGGL((k_step3d_pipe<S, A, TX, TY>), grid, dim3(TX * TY), 0, st, src, dst,  \
+                           a, g);                                                                \
+        return hipGetLastError();                                                                \
+    }
+#define SC_L3(B)                                                                                 \
+    if (threads <= B) {                                                                          \
+        if (ext && s.variant == 3)                                                               \
+            hipLaunchKernelGGL((k_step3d<S, A, B, true, true>), grid, dim3(threads), lds, st,    \
+                               src, dst, a, g);                                                  \
+        else if (ext)                                                                            \
+            hipLaunchKernelGGL((k_step3d<S, A, B, false, true>), grid, dim3(threads), lds, st,   \
+                               src, dst, a, g);                                                  \
         else if (s.variant == 3)                                                                 \
-            hipLaunchKernelGGL((k_step3d<S, A, TX, TY, true>), grid, dim3(TX * TY), 0, st, src,  \
+            hipLaunchKernelGGL((k_step3d<S, A, B, true>), grid, dim3(threads), lds, st, src,     \
                                dst, a, g);                                                       \
         else                                                                                     \
-            hipLaunchKernelGGL((k_step3d<S, A, TX, TY>), grid, dim3(TX * TY), 0, st, src, dst,   \
-                               a, g);                                                            \
+            hipLaunchKernelGGL((k_step3d<S, A, B>), grid, dim3(threads), lds, st, src, dst, a,   \
+                               g);                                                               \
         return hipGetLastError();                                                                \
     }
     if (q == 9) {
         SC_L2(64) SC_L2(128) SC_L2(256) SC_L2(512)
+    } else if (s.variant == 2) {
+        SC_L3P(32, 4) SC_L3P(32, 8) SC_L3P(32, 16) SC_L3P(64, 4) SC_L3P(64, 8) SC_L3P(128, 4)
+        SC_L3P(16, 16) SC_L3P(128, 8) SC_L3P(256, 4)
     } else {
-        SC_L3(32, 4) SC_L3(32, 8) SC_L3(32, 16) SC_L3(64, 4) SC_L3(64, 8) SC_L3(128, 4)
-        SC_L3(16, 16) SC_L3(128, 8) SC_L3(256, 4)
+        const int threads = (s.tile_x * s.tile_y + 63) & ~63;
+        const size_t lds = 4 * sizeof(A) * (size_t)(s.tile_x + 2) * (size_t)(s.tile_y + 2);
+        SC_L3(256) SC_L3(512) SC_L3(1024)
     }
 #undef SC_L2
+#undef SC_L3P
 #undef SC_L3
     return hipErrorInvalidValue;
 }
@@ -637,7 +638,8 @@ bool step_combo_supported(int storage, int compute)
 hipError_t launch_step(int q, int storage, int compute, const void* src, void* dst,
                        const StepArgs& a, const StepShape& s, hipStream_t st)
 {
-    if (!step_shape_supported(q, s)) return hipErrorInvalidValue;
+    if (!step_shape_supported(q, s) && !(q == 19 && step3d_tile_fits(s)))
+        return hipErrorInvalidValue;
     if (compute == SC_COMPUTE_F64) {
         if (storage == SC_STORE_F32)
             return step_typed<float, double>(q, (const float*)src, (float*)dst, a, s, st);

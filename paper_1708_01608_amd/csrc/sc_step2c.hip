@@ -263,25 +263,26 @@ __global__ void __launch_bounds__(TX* TY) k_mix3d(const S* __restrict__ sl,
 }
 
 // ------------------------------------------------------------------------------------------
-// D3Q19, one component per wave: threads [0, T) carry the liquid of the T = TX x TY tile nodes,
-// threads [T, 2T) the gas, so each thread holds one component's populations (the register
+// D3Q19, one component per wave: threads [0, T) carry the liquid of the tw x th tile's nodes
+// (T: tw th rounded up to whole waves), threads [T, 2T) the gas, so each thread holds one component's populations (the register
 // budget of the one-component kernel) and every wave reads and writes a single component
 // through scalar bases.  Besides the density rings, the momenta of both components go to LDS at
 // load time (three plane slots: plane z is read between the barriers of iterations z and z+1,
 // plane z+3 is written only after the second of them); the collision reads its partner's
 // density and momentum there.
 // ------------------------------------------------------------------------------------------
-template <typename S, typename A, int TX, int TY, bool NT>
-__global__ void __launch_bounds__(2 * TX* TY) k_mix3d_split(const S* __restrict__ sl,
-                                                            const S* __restrict__ sv,
-                                                            S* __restrict__ dl,
-                                                            S* __restrict__ dv, Step2cArgs a,
-                                                            StepGrid grid)
+template <typename S, typename A, int B, bool NT>
+__global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
+                                                   const S* __restrict__ sv, S* __restrict__ dl,
+                                                   S* __restrict__ dv, Step2cArgs a, StepGrid grid)
 {
     using L = lat<19>;
-    constexpr int T = TX * TY;
-    __shared__ A rs[2][4][TY + 2][TX + 2];  // [component][plane slot][y][x] density deviations
-    __shared__ A js[2][3][3][T];            // [component][plane slot][axis][node] momenta
+    extern __shared__ double mix_lds[];
+    const int T = (int)blockDim.x >> 1;
+    const int tw = grid.tw, th = grid.th;
+    const int pw = tw + 2, psz = pw * (th + 2);    // row pitch and size of a plane slot
+    A* const rs = reinterpret_cast<A*>(mix_lds);   // [component][plane slot][y][x] density dev.
+    A* const js = rs + 8 * psz;                    // [component][plane slot][axis][node] momenta
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t N = a.N;
     const int lb = logical_block(grid);
@@ -296,34 +297,29 @@ __global__ void __launch_bounds__(2 * TX* TY) k_mix3d_split(const S* __restrict_
     S* __restrict__ dst = comp ? dv : dl;
     const A il = (A)(1.0 / a.tau_l), iv = (A)(1.0 / a.tau_v);
     const A ia = comp ? iv : il;
-    const A ka = (A)(-(comp ? a.tau_v : a.tau_l) * a.Gx);  // tau_a F_a / rho_a = ka sum(rho_b)
+    const A ka = -(A)(comp ? a.tau_v : a.tau_l) * (A)a.Gx;  // tau_a F_a / rho_a = ka sum(rho_b)
     const A ref_l = (A)a.ref_l, ref_v = (A)a.ref_v, ref_a = comp ? ref_v : ref_l;
-    const int tx = t % TX, ty = t / TX;
-    const int x0 = bx * TX, y0 = by * TY, z0 = bz * a.planes;
-    const int wx = min(TX, nx - x0), wy = min(TY, ny - y0);
+    const int ty = t / tw, tx = t - ty * tw;
+    const int x0 = bx * tw, y0 = by * th, z0 = bz * a.planes;
+    const int wx = min(tw, nx - x0), wy = min(th, ny - y0);
     const int ze = min(z0 + a.planes, nz);
     const bool own = tx < wx && ty < wy;
     const int x = x0 + (own ? tx : 0), y = y0 + (own ? ty : 0);
     const int xm = wrap_once(x - 1, nx), xp = wrap_once(x + 1, nx);
     const int ym = wrap_once(y - 1, ny), yp = wrap_once(y + 1, ny);
 
-    // ring node of this thread for its component (the host checks 2 (TX + 2) + 2 TY <= T)
-    const int nring = 2 * (wx + 2) + 2 * wy;
-    const bool ring = t < nring;
+    // ring node of this thread for its component (the host checks 2 (tw + 2) + 2 th <= T)
+    const bool ring = t < 2 * (wx + 2) + 2 * wy;
     int hlx, hly;
-    if (t < wx + 2) {
-        hlx = t; hly = 0;
-    } else if (t < 2 * (wx + 2)) {
-        hlx = t - (wx + 2); hly = wy + 1;
-    } else if (t < 2 * (wx + 2) + wy) {
-        hlx = 0; hly = 1 + t - 2 * (wx + 2);
-    } else {
-        hlx = wx + 1; hly = 1 + t - 2 * (wx + 2) - wy;
-    }
-    const int hx = wrap_once(x0 - 1 + (ring ? hlx : 1), nx);
-    const int hy = wrap_once(y0 - 1 + (ring ? hly : 1), ny);
+    ring_cell(t, wx, wy, hlx, hly);
+    if (!ring) hlx = hly = 1;
+    const int hx = wrap_once(x0 - 1 + hlx, nx), hy = wrap_once(y0 - 1 + hly, ny);
     const int hxm = wrap_once(hx - 1, nx), hxp = wrap_once(hx + 1, nx);
     const int hym = wrap_once(hy - 1, ny), hyp = wrap_once(hy + 1, ny);
+    const int pc0 = pw * ((own ? ty : 0) + 1) + (own ? tx : 0) + 1;  // own and ring cell in a slot
+    const int ph0 = pw * hly + hlx;
+    A* const ra = rs + comp * 4 * psz;        // this component's densities, and the other's
+    const A* const rb = rs + oc * 4 * psz;
 
     float cur[19], nxt[19];
 
@@ -332,19 +328,20 @@ __global__ void __launch_bounds__(2 * TX* TY) k_mix3d_split(const S* __restrict_
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
         if (own) {
             pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
-            rs[comp][k][ty + 1][tx + 1] = sum_dev<19, A>(g);
+            ra[k * psz + pc0] = sum_dev<19, A>(g);
             if (k3 >= 0) {
                 A jx, jy, jz;
                 momentum<19, A>(g, jx, jy, jz);
-                js[comp][k3][0][t] = jx;
-                js[comp][k3][1][t] = jy;
-                js[comp][k3][2][t] = jz;
+                A* const j3 = js + (comp * 9 + k3 * 3) * T + t;
+                j3[0] = jx;
+                j3[T] = jy;
+                j3[2 * T] = jz;
             }
         }
         if (ring) {
             float h[19];
             pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
-            rs[comp][k][hly][hlx] = sum_dev<19, A>(h);
+            ra[k * psz + ph0] = sum_dev<19, A>(h);
         }
     };
     load_plane(wrap_once(z0 - 1, nz), 0, -1, nxt);
@@ -360,13 +357,13 @@ __global__ void __launch_bounds__(2 * TX* TY) k_mix3d_split(const S* __restrict_
         if (own) {
             // both components in a fixed order (liquid first), so the two threads of a node
             // form the same common velocity
-            const A da = rs[comp][s][ty + 1][tx + 1], db = rs[oc][s][ty + 1][tx + 1];
+            const A da = ra[s * psz + pc0], db = rb[s * psz + pc0];
             const A rl = ref_l + (comp ? db : da), rv = ref_v + (comp ? da : db);
             A jl[3], jv[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                jl[c] = js[0][s3][c][t];
-                jv[c] = js[1][s3][c][t];
+                jl[c] = js[(s3 * 3 + c) * T + t];
+                jv[c] = js[(9 + s3 * 3 + c) * T + t];
             }
             const A iden = recip(fmad(rl, il, rv * iv));
             const A upx = fmad(jl[0], il, jv[0] * iv) * iden;
@@ -375,8 +372,8 @@ __global__ void __launch_bounds__(2 * TX* TY) k_mix3d_split(const S* __restrict_
             auto slot = [&](int i) { return L::ez[i] > 0 ? sn : (L::ez[i] < 0 ? sp : s); };
             A sx, sy, sz;
             interaction_sum<19, A>(
-                [&](int i) { return rs[oc][slot(i)][ty + 1 + L::ey[i]][tx + 1 + L::ex[i]]; }, sx,
-                sy, sz);
+                [&](int i) { return rb[slot(i) * psz + pc0 + L::ey[i] * pw + L::ex[i]]; }, sx, sy,
+                sz);
             relax_store<19, A, S, NT>(dst, N, (uint32_t)(x + nx * (y + ny * z)), cur, da,
                                       ref_a + da, fmad(ka, sx, upx), fmad(ka, sy, upy),
                                       fmad(ka, sz, upz), ia);
@@ -484,6 +481,24 @@ bool step2c_shape_supported(int q, const StepShape& s)
     return false;
 }
 
+// LDS of k_mix3d_split: four plane slots of both densities over tile and ring, three of both
+// components' momenta; `es` bytes a value.
+size_t mix3d_split_lds(int tx, int ty, size_t es)
+{
+    const size_t T = (size_t)((tx * ty + 63) & ~63);
+    return es * (8 * (size_t)(tx + 2) * (size_t)(ty + 2) + 18 * T);
+}
+
+// What k_mix3d_split needs of a tile: two threads for every node, one of each component for
+// every ring node, and its LDS.
+bool mix3d_tile_fits(const StepShape& s, size_t es)
+{
+    const int tx = s.tile_x, ty = s.tile_y;
+    return (s.variant == 4 || s.variant == 5) && s.tile_z >= 1 && tx >= 1 && ty >= 1 &&
+           tx <= 512 && ty <= 512 && tx * ty <= 512 && 2 * (tx + 2) + 2 * ty <= tx * ty &&
+           mix3d_split_lds(tx, ty, es) <= (size_t)160 * 1024;
+}
+
 namespace {
 
 template <typename S, typename A>
@@ -506,15 +521,6 @@ hipError_t step2c_typed(int q, const S* src_l, const S* src_v, S* dst_l, S* dst_
     }
 #define SC_M3(TX, TY)                                                                            \
     if (s.tile_x == TX && s.tile_y == TY) {                                                      \
-        if (split) {                                                                             \
-            if (nt)                                                                              \
-                hipLaunchKernelGGL((k_mix3d_split<S, A, TX, TY, true>), grid, dim3(2 * TX * TY), \
-                                   0, st, src_l, src_v, dst_l, dst_v, a, g);                     \
-            else                                                                                 \
-                hipLaunchKernelGGL((k_mix3d_split<S, A, TX, TY, false>), grid,                   \
-                                   dim3(2 * TX * TY), 0, st, src_l, src_v, dst_l, dst_v, a, g);  \
-            return hipGetLastError();                                                            \
-        }                                                                                        \
         if (nt)                                                                                  \
             hipLaunchKernelGGL((k_mix3d<S, A, TX, TY, true>), grid, dim3(TX * TY), 0, st, src_l, \
                                src_v, dst_l, dst_v, a, g);                                       \
@@ -523,13 +529,28 @@ hipError_t step2c_typed(int q, const S* src_l, const S* src_v, S* dst_l, S* dst_
                                src_l, src_v, dst_l, dst_v, a, g);                                \
         return hipGetLastError();                                                                \
     }
+#define SC_M3S(B)                                                                                \
+    if (threads <= B) {                                                                          \
+        if (nt)                                                                                  \
+            hipLaunchKernelGGL((k_mix3d_split<S, A, B, true>), grid, dim3(threads), lds, st,     \
+                               src_l, src_v, dst_l, dst_v, a, g);                                \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_mix3d_split<S, A, B, false>), grid, dim3(threads), lds, st,    \
+                               src_l, src_v, dst_l, dst_v, a, g);                                \
+        return hipGetLastError();                                                                \
+    }
     if (q == SC_D2Q9) {
         SC_M2(64) SC_M2(128) SC_M2(256) SC_M2(512)
+    } else if (s.variant >= 4) {
+        const int T = (s.tile_x * s.tile_y + 63) & ~63, threads = 2 * T;
+        const size_t lds = mix3d_split_lds(s.tile_x, s.tile_y, sizeof(A));
+        SC_M3S(256) SC_M3S(512) SC_M3S(1024)
     } else {
         SC_M3(32, 4) SC_M3(32, 8) SC_M3(64, 4) SC_M3(64, 8) SC_M3(128, 4)
     }
 #undef SC_M2
 #undef SC_M3
+#undef SC_M3S
     return hipErrorInvalidValue;
 }
 
@@ -557,10 +578,14 @@ hipError_t fields2c_typed(int q, const S* f_l, const S* f_v, double* dens, float
 hipError_t launch_step2c(int q, int storage, const void* src_l, const void* src_v, void* dst_l,
                          void* dst_v, const Step2cArgs& a0, const StepShape& s, hipStream_t st)
 {
-    if (!step2c_shape_supported(q, s)) return hipErrorInvalidValue;
+    const size_t es = storage == SC_STORE_F32 ? sizeof(double) : sizeof(float);
+    if (!step2c_shape_supported(q, s) && !(q == SC_D3Q19 && mix3d_tile_fits(s, es)))
+        return hipErrorInvalidValue;
     Step2cArgs a = a0;
     a.planes = s.tile_z;
     StepGrid g;
+    g.tw = s.tile_x;
+    g.th = s.tile_y;
     g.gx = (a.nx + s.tile_x - 1) / s.tile_x;
     if (q == SC_D2Q9) {
         g.gy = (a.ny + a.planes - 1) / a.planes;
@@ -569,7 +594,6 @@ hipError_t launch_step2c(int q, int storage, const void* src_l, const void* src_
         g.gy = (a.ny + s.tile_y - 1) / s.tile_y;
         g.gz = (a.nz + a.planes - 1) / a.planes;
     }
-    g.remap = ((g.gx * g.gy * g.gz) % 8 == 0) ? 1 : 0;
     switch (storage) {
         case SC_STORE_F32:
             return step2c_typed<float, double>(q, (const float*)src_l, (const float*)src_v,

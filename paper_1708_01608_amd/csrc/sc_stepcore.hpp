@@ -26,18 +26,32 @@ __device__ __forceinline__ float opaque(float v)
 
 struct StepGrid {
     int gx, gy, gz;  // tiles along x, y and plane chunks
-    int remap;       // 1: contiguous tile ranges per XCD (8 XCDs, round-robin dispatch)
+    int tw, th;      // tile width and height in nodes
 };
 
 // Logical tile of this block.  Blocks are dispatched round-robin over the 8 XCDs, so block b
-// runs on XCD b % 8; with remap, XCD k processes the contiguous logical range
-// [k * n/8, (k+1) * n/8) and neighbouring tiles share that XCD's L2.
+// runs on XCD b % 8; XCD k processes a contiguous logical range (the first n % 8 XCDs one tile
+// more than the others), so neighbouring tiles share that XCD's L2.
 __device__ __forceinline__ int logical_block(const StepGrid& g)
 {
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, k = b & 7;
     const int n = g.gx * g.gy * g.gz;
-    if (!g.remap) return b;
-    return (b & 7) * (n >> 3) + (b >> 3);
+    return k * (n >> 3) + min(k, n & 7) + (b >> 3);
+}
+
+// Ring cell (hlx, hly) of thread t in the psi tile of a wx x wy tile: the rows below and above
+// (wx + 2 cells each, corners included), then the left and right columns (wy cells each).
+__device__ __forceinline__ void ring_cell(int t, int wx, int wy, int& hlx, int& hly)
+{
+    if (t < wx + 2) {
+        hlx = t; hly = 0;
+    } else if (t < 2 * (wx + 2)) {
+        hlx = t - (wx + 2); hly = wy + 1;
+    } else if (t < 2 * (wx + 2) + wy) {
+        hlx = 0; hly = 1 + t - 2 * (wx + 2);
+    } else {
+        hlx = wx + 1; hly = 1 + t - 2 * (wx + 2) - wy;
+    }
 }
 
 // Pulled populations g_i = stored_i(x - e_i) of one node: unsigned 32-bit byte offsets from a
