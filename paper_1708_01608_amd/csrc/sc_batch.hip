@@ -9,7 +9,8 @@
 // queue hands out boxes largest first.  Every workgroup leaves the loop once the queue is empty.
 //
 // A box is at most 256 nodes wide: one thread per column, marching over the rows with the psi
-// of four rows in LDS (the full row is in the block, so the x neighbours wrap inside LDS).
+// of four rows in LDS (the full row is in the block, so the x neighbours wrap inside LDS), two
+// time steps in one sweep over the rows.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -40,6 +41,7 @@ struct BatchOut {
     int32_t film_len, status;
     double lap_p, rho_film;
     double totals[3];
+    int32_t buf, pad;  // population buffer (0, 1) that holds the final state
 };
 
 struct BatchArgs {
@@ -183,6 +185,126 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
         }
     }
     __syncthreads();  // this step's stores are the next step's loads
+}
+
+// ---- two time steps of a whole box in one sweep ------------------------------------------------
+// The rows stream through two stages: stage A takes the populations of step t from global memory
+// and leaves those of step t + 1 (rounded to the storage's FP32, as a store would) in LDS, stage B
+// pulls from there and stores step t + 2.  A box is as wide as the block, so neither stage needs a
+// halo in x, and in y only the blocks before the first and after the last row are done twice.
+// Blocks of rb = 256 / nx rows as in batch_step, one node a lane.  Between two barriers
+//   A collides block i          (psi of i - 1 .. i + 1)  -> populations of block i in LDS
+//   A loads block i + 2         -> its psi at the end, behind the rest of the interval's work
+//   B collides block i - 4      (psi of i - 5 .. i - 3)  -> global memory
+//   B pulls block i - 2         (populations of i - 3 .. i - 1) -> its psi
+// so everything read was written before the barrier and four ring slots of each kind suffice.
+// One step at a time is bound by HBM and by its one load latency per barrier; this sweep moves
+// half the bytes and is bound by the FP64 arithmetic (figures at k_batch).
+template <typename A>
+__device__ void batch_step2(const float* __restrict__ src, float* __restrict__ dst, int nx, int ny,
+                            const Coef<A>& c, A* __restrict__ psa, A* __restrict__ psb,
+                            float* __restrict__ mid)
+{
+    using L = lat<9>;
+    constexpr int W = kBatchThreads;
+    const int N = nx * ny;
+    const int rb = max(1, W / nx);
+    const int nblk = (ny + rb - 1) / rb;
+    const int t = threadIdx.x;
+    const int row = t / nx, col = t - row * nx;
+    const bool act = row < rb;
+    const int xm = wrap_once(col - 1, nx), xp = wrap_once(col + 1, nx);
+    const int rb_ny = rb % ny;
+    // entry of the neighbour (column x, row + dy) of a lane of block b in a ring of slots
+    const bool up_in = row + 1 < rb, dn_in = row > 0;
+    const int r0 = t - col;
+    auto at = [&](int b, int dy, int x) {
+        if (dy == 0) return (b & 3) * W + r0 + x;
+        if (dy > 0) return up_in ? (b & 3) * W + r0 + nx + x : ((b + 1) & 3) * W + x;
+        return dn_in ? (b & 3) * W + r0 - nx + x : ((b + 3) & 3) * W + (rb - 1) * nx + x;
+    };
+    auto xof = [&](int ex) { return ex > 0 ? xp : (ex < 0 ? xm : col); };
+    auto force = [&](const A* ps, int b, A& fx, A& fy) {
+        const int rc = at(b, 0, 0), ru = at(b, 1, 0), rd = at(b, -1, 0);
+        const A pc = ps[rc + col];
+        A fz;  // the single-box kernel's grouped sum
+        interaction_sum<9, A>(
+            [&](int i) {
+                return ps[(L::ey[i] > 0 ? ru : (L::ey[i] < 0 ? rd : rc)) + xof(L::ex[i])];
+            },
+            fx, fy, fz);
+        const A gp = -c.G * pc;
+        fx *= gp;
+        fy *= gp;
+    };
+    // row of block b of this lane: block 1 holds rows 0 .. rb - 1, blocks outside wrap around
+    int yl = (-3 * rb + row) % ny;  // the next block to load: -2
+    if (yl < 0) yl += ny;
+    auto pull = [&](float* g) {
+        pull_node<9>(src, N, nx, ny, col, xm, xp, yl, wrap_once(yl - 1, ny), wrap_once(yl + 1, ny),
+                     0, 0, 0, g);
+        yl = wrap_once(yl + rb_ny, ny);
+    };
+    float ca[9], na[9], cb[9], nb[9];
+    A dca = (A)0, dna = (A)0, dcb = (A)0, dnb = (A)0;
+    if (act) {
+        float g[9];
+        pull(g);
+        pull(ca);
+        pull(na);
+        psa[(-2 & 3) * W + t] = psi_f(c.rho_ref + sum_dev<9, A>(g));
+        dca = sum_dev<9, A>(ca);
+        psa[(-1 & 3) * W + t] = psi_f(c.rho_ref + dca);
+        dna = sum_dev<9, A>(na);
+        psa[t] = psi_f(c.rho_ref + dna);
+    }
+    __syncthreads();
+    for (int i = -1; i <= nblk + 4; ++i) {
+        if (act) {
+            const bool more = i + 2 <= nblk + 3;
+            float la[9];
+            if (more) pull(la);
+            if (i <= nblk + 2) {
+                A fx, fy;
+                force(psa, i, fx, fy);
+                collide_store<9, A, float>(mid + (i & 3) * 9 * W, W, (uint32_t)t, ca, dca, fx, fy,
+                                           (A)0, c);
+            }
+            const int yb = (i - 5) * rb + row;
+            if (i >= 5 && yb < ny) {
+                A fx, fy;
+                force(psb, i - 4, fx, fy);
+                collide_store<9, A, float>(dst, N, (uint32_t)(col + nx * yb), cb, dcb, fx, fy,
+                                           (A)0, c);
+            }
+#pragma unroll
+            for (int k = 0; k < 9; ++k) cb[k] = nb[k];
+            dcb = dnb;
+            if (i >= 2 && i - 2 <= nblk + 1) {
+                const int b = i - 2;
+                // slot and entry of the rows pulled from: y, y - 1 (e_y > 0) and y + 1
+                const int sc = (b & 3) * 9 * W + r0;
+                const int su = up_in ? sc + nx : ((b + 1) & 3) * 9 * W;
+                const int sd = dn_in ? sc - nx : ((b + 3) & 3) * 9 * W + (rb - 1) * nx;
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+                    nb[k] = mid[(L::ey[k] > 0 ? sd : (L::ey[k] < 0 ? su : sc)) + k * W +
+                                xof(-L::ex[k])];
+                dnb = sum_dev<9, A>(nb);
+                psb[(b & 3) * W + t] = psi_f(c.rho_ref + dnb);
+            }
+#pragma unroll
+            for (int k = 0; k < 9; ++k) ca[k] = na[k];
+            dca = dna;
+            if (more) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) na[k] = la[k];
+                dna = sum_dev<9, A>(na);
+                psa[((i + 2) & 3) * W + t] = psi_f(c.rho_ref + dna);
+            }
+        }
+        __syncthreads();  // (the last one: this sweep's stores are the next step's loads)
+    }
 }
 
 // ---- test pass of one box --------------------------------------------------------------------
@@ -521,13 +643,20 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
     return stop;
 }
 
-// Waves per SIMD the compiler must fit (the second launch bound): one box per workgroup leaves
-// latency to hide, so with one node slot per lane the registers are capped for three waves (a
-// few spills, measured 16% faster than two); more slots need two.
+// With one node slot per lane a box takes two steps a sweep: 2048 boxes of 64 .. 256 a side, 400
+// steps, 286 -> 215 ms with a test pass every 10 steps (54 -> 72 G node-steps/s), 338 -> 234 ms
+// without (62 -> 89); two and four slots take one step a sweep and hold 256 registers (736 ms and
+// about 400 ms).  Waves per SIMD the compiler must fit (the second launch bound): one box per
+// workgroup leaves latency to hide, so with one slot the registers are capped for three waves (a
+// few spills; the rings' 53 KB of LDS allow three workgroups a CU too); more slots need two.
 template <typename A, int RB>
 __global__ void __launch_bounds__(kBatchThreads, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
 {
     __shared__ A ps[4 * RB * kBatchThreads];
+    // one slot a lane: the second stage's psi and the populations between the stages
+    constexpr int kMid = RB == 1 ? 4 * kBatchThreads : 1;
+    __shared__ A psb[kMid];
+    __shared__ float mid[9 * kMid];
     __shared__ Scratch sh;
     __shared__ BatchOut s_out;
     __shared__ int s_idx;
@@ -560,14 +689,23 @@ __global__ void __launch_bounds__(kBatchThreads, RB == 1 ? 3 : 2) k_batch(BatchA
         int cur = 0;
         int64_t step = 0;
         while (!stop && step < b.max_steps) {
-            batch_step<A, RB>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps);
+            // two steps a sweep up to the next test pass, a last odd one by itself
+            bool two = false;
+            if constexpr (RB == 1)
+                two = step + 2 <= b.max_steps && (b.K <= 0 || step % b.K + 2 <= b.K);
+            if (two)
+                batch_step2<A>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps, psb, mid);
+            else
+                batch_step<A, RB>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps);
             cur ^= 1;
-            ++step;
+            step += two ? 2 : 1;
             if (b.K > 0 && step % b.K == 0)
                 stop = batch_test(cur ? f1 : f0, par, in, b.K, b.film_max, step, true, o, sh);
         }
         if (threadIdx.x == 0) {
             o.steps_run = step;
+            o.buf = cur;
+            o.pad = 0;
             b.out[k] = o;
         }
         __syncthreads();
@@ -594,7 +732,7 @@ using namespace sc;
 struct sc_batch {
     int n = 0;
     int K = 10, film_max = 8, max_steps = 5000, compute = SC_COMPUTE_F64;
-    int rb = 2;  // rows per thread per iteration of the box step
+    int rb = 1;  // rows per thread per iteration of the box step
     hipStream_t stream = nullptr;
     bool own_stream = false;
     sc_allocator alloc{};
@@ -885,7 +1023,7 @@ int sc_batch_fields(sc_batch* b, int32_t k, float* rho)
     if (!b->ran) return set_error(SC_E_STATE, "sc_batch_run has not run");
     const BatchInst& in = b->inst[k];
     const int N = in.nx * in.ny;
-    const float* f = (const float*)b->d_pool + in.off + (b->last[k].steps_run % 2 ? (int64_t)9 * N : 0);
+    const float* f = (const float*)b->d_pool + in.off + (b->last[k].buf ? (int64_t)9 * N : 0);
     if (!b->d_rho) {
         b->d_rho = balloc(b, sizeof(float) * (size_t)kBatchThreads * 65536);
         if (!b->d_rho) return set_error(SC_E_NOMEM, "density buffer");
