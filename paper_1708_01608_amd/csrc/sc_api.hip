@@ -78,7 +78,7 @@ struct sc_sim {
     double rho0 = 0.0;
 
     // two-component mode: the gas component's populations (same layout and cur as f) and the
-    // FP64 densities of both components that the reported fields are formed from
+    // FP64 densities of both components that the 2D reported fields are formed from
     bool two = false;
     void* fv[2] = {nullptr, nullptr};
     DevBuf dens2;
@@ -1355,7 +1355,8 @@ int sc_create(const sc_params* p, sc_sim** out)
         s->rho_ref_v = s->rho_ref != 0.0 ? p->rho_dissolved : 0.0;
         s->fv[0] = dev_alloc(s, bytes);
         s->fv[1] = dev_alloc(s, bytes);
-        if (!s->fv[0] || !s->fv[1] || ensure(s, s->dens2, sizeof(double) * 2 * (size_t)s->N) != SC_OK) {
+        if (!s->fv[0] || !s->fv[1] ||
+            (s->q == 9 && ensure(s, s->dens2, sizeof(double) * 2 * (size_t)s->N) != SC_OK)) {
             release(s);
             delete s;
             return fail(SC_E_NOMEM, "gas component buffers");
@@ -1656,14 +1657,24 @@ int sc_step(sc_sim* s, int32_t nsteps)
 static int fields_to_device(sc_sim* s, float* rho_d, float* u_d)
 {
     if (!rho_d && !u_d) return SC_OK;
-    if (s->two) {
-        HIPX(launch_fields2c(s->q, s->p.storage, s->f[s->cur], s->fv[s->cur],
-                             (double*)s->dens2.p, rho_d, nullptr, u_d, step2c_args(s), s->stream));
+    const FieldArgs fa = field_args(s);
+    if (s->q == 19 && s->two) {
+        HIPX(launch_mix_fields3d(s->p.storage, s->f[s->cur], rho_d, nullptr, u_d, fa, s->stream));
         return SC_OK;
     }
-    const FieldArgs fa = field_args(s);
-    TRY(ensure(s, s->psi, sizeof(double) * (size_t)s->N));
-    HIPX(launch_psi(s->q, s->p.storage, s->f[s->cur], (double*)s->psi.p, fa, s->stream));
+    if (s->two) {
+        HIPX(launch_fields2c(s->p.storage, s->f[s->cur], s->fv[s->cur], (double*)s->dens2.p, rho_d,
+                             nullptr, u_d, step2c_args(s), s->stream));
+        return SC_OK;
+    }
+    if (s->q == 19 && u_d) {
+        HIPX(launch_fields3d(s->p.storage, s->f[s->cur], rho_d, u_d, fa, s->stream));
+        return SC_OK;
+    }
+    if (u_d) {
+        TRY(ensure(s, s->psi, sizeof(double) * (size_t)s->N));
+        HIPX(launch_psi(s->p.storage, s->f[s->cur], (double*)s->psi.p, fa, s->stream));
+    }
     HIPX(launch_fields(s->q, s->p.storage, s->f[s->cur], (const double*)s->psi.p, rho_d, u_d, fa,
                        s->stream));
     return SC_OK;
@@ -1740,17 +1751,29 @@ int sc_fields_device(sc_sim* s, float* rho_dev, float* u_dev)
     return SC_OK;
 }
 
+// p and its Laplacian into device buffers, queued on the sim's stream: in 3D in one sweep (either
+// may be NULL), in 2D the Laplacian from p (not NULL).
+static int laplacian_to_device(sc_sim* s, double* p_d, double* lap_d, const FieldArgs& fa)
+{
+    if (s->q == 19 && lap_d) {
+        HIPX(launch_laplacian3d(s->p.storage, s->f[s->cur], p_d, lap_d, fa, s->stream));
+        return SC_OK;
+    }
+    HIPX(launch_pressure(s->q, s->p.storage, s->f[s->cur], p_d, fa, s->stream));
+    if (lap_d) HIPX(launch_laplacian(p_d, lap_d, fa, s->stream));
+    return SC_OK;
+}
+
 int sc_laplacian_p(sc_sim* s, double* p, double* lap)
 {
     TRY(check_usable(s));
     if (!p && !lap) return SC_OK;
     const FieldArgs fa = field_args(s);
-    TRY(ensure(s, s->p_out, sizeof(double) * (size_t)s->N));
-    HIPX(launch_pressure(s->q, s->p.storage, s->f[s->cur], (double*)s->p_out.p, fa, s->stream));
+    if (p || s->q == 9) TRY(ensure(s, s->p_out, sizeof(double) * (size_t)s->N));
+    if (lap) TRY(ensure(s, s->lap_out, sizeof(double) * (size_t)s->N));
+    TRY(laplacian_to_device(s, p || s->q == 9 ? (double*)s->p_out.p : nullptr,
+                            lap ? (double*)s->lap_out.p : nullptr, fa));
     if (lap) {
-        TRY(ensure(s, s->lap_out, sizeof(double) * (size_t)s->N));
-        HIPX(launch_laplacian(s->q, (const double*)s->p_out.p, (double*)s->lap_out.p, fa,
-                              s->stream));
         HIPX(hipMemcpyAsync(lap, s->lap_out.p, sizeof(double) * (size_t)s->N,
                             hipMemcpyDeviceToHost, s->stream));
     }
@@ -1771,12 +1794,11 @@ int sc_laplacian_p_device(sc_sim* s, double* p_dev, double* lap_dev)
                        sizeof(double) * (size_t)s->N, "p and lap"));
     const FieldArgs fa = field_args(s);
     double* p_d = p_dev;
-    if (!p_d) {  // the Laplacian alone still needs p
+    if (!p_d && s->q == 9) {  // in 2D the Laplacian alone still needs p
         TRY(ensure(s, s->p_out, sizeof(double) * (size_t)s->N));
         p_d = (double*)s->p_out.p;
     }
-    HIPX(launch_pressure(s->q, s->p.storage, s->f[s->cur], p_d, fa, s->stream));
-    if (lap_dev) HIPX(launch_laplacian(s->q, p_d, lap_dev, fa, s->stream));
+    TRY(laplacian_to_device(s, p_d, lap_dev, fa));
     HIPX(hipStreamSynchronize(s->stream));
     return SC_OK;
 }
@@ -1984,9 +2006,12 @@ int sc_gas_density(sc_sim* s, float* rho_v)
         return SC_OK;
     }
     TRY(ensure(s, s->rho_out, sizeof(float) * (size_t)s->N));
-    HIPX(launch_fields2c(s->q, s->p.storage, s->f[s->cur], s->fv[s->cur],
-                         (double*)s->dens2.p, nullptr, (float*)s->rho_out.p, nullptr,
-                         step2c_args(s), s->stream));
+    if (s->q == 19)
+        HIPX(launch_mix_fields3d(s->p.storage, s->f[s->cur], nullptr, (float*)s->rho_out.p,
+                                 nullptr, field_args(s), s->stream));
+    else
+        HIPX(launch_fields2c(s->p.storage, s->f[s->cur], s->fv[s->cur], (double*)s->dens2.p,
+                             nullptr, (float*)s->rho_out.p, nullptr, step2c_args(s), s->stream));
     HIPX(hipMemcpyAsync(rho_v, s->rho_out.p, sizeof(float) * (size_t)s->N, hipMemcpyDeviceToHost,
                         s->stream));
     HIPX(hipStreamSynchronize(s->stream));

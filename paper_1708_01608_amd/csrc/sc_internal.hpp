@@ -63,9 +63,9 @@ bool mix3d_tile_fits(const StepShape& s, size_t es);
 // FP32 storage runs FP64 arithmetic, FP16 / BF16 storage FP32 arithmetic.
 hipError_t launch_step2c(int q, int storage, const void* src_l, const void* src_v, void* dst_l,
                          void* dst_v, const Step2cArgs& a, const StepShape& s, hipStream_t st);
-// Reported fields of the mixture: rho_l, rho_v (FP32) and the barycentric velocity; dens holds
+// Reported fields of the 2D mixture: rho_l, rho_v (FP32) and the barycentric velocity; dens holds
 // [2][N] FP64 densities afterwards.
-hipError_t launch_fields2c(int q, int storage, const void* f_l, const void* f_v, double* dens,
+hipError_t launch_fields2c(int storage, const void* f_l, const void* f_v, double* dens,
                            float* rho_l, float* rho_v, float* u, const Step2cArgs& a,
                            hipStream_t st);
 
@@ -108,13 +108,21 @@ struct FieldArgs {
     double Gx;
     double rho_ref2;  // storage shift of the gas component
 };
-hipError_t launch_psi(int q, int storage, const void* f, double* psi, const FieldArgs& a,
-                      hipStream_t st);
+// 2D: psi, then rho and u from it (without u neither psi nor the 3D sweep is needed: any lattice).
+hipError_t launch_psi(int storage, const void* f, double* psi, const FieldArgs& a, hipStream_t st);
 hipError_t launch_fields(int q, int storage, const void* f, const double* psi, float* rho,
                          float* u, const FieldArgs& a, hipStream_t st);
 hipError_t launch_pressure(int q, int storage, const void* f, double* p, const FieldArgs& a,
                            hipStream_t st);
-hipError_t launch_laplacian(int q, const double* p, double* lap, const FieldArgs& a,
+// 3D, one sweep each (sc_fields.hip): rho and u; the mixture's fields; p and its Laplacian (any
+// output but u and lap may be NULL).
+hipError_t launch_fields3d(int storage, const void* f, float* rho, float* u, const FieldArgs& a,
+                           hipStream_t st);
+hipError_t launch_mix_fields3d(int storage, const void* f, float* rho_l, float* rho_v, float* u,
+                               const FieldArgs& a, hipStream_t st);
+hipError_t launch_laplacian3d(int storage, const void* f, double* p, double* lap,
+                              const FieldArgs& a, hipStream_t st);
+hipError_t launch_laplacian(const double* p, double* lap, const FieldArgs& a,
                             hipStream_t st);
 // FP64 totals (M, Jx, Jy, Jz) into out_d[4] (device); partials holds >= totals_blocks() * 4.
 int totals_blocks(int64_t N);

@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
 }
 
 // ------------------------------------------------------------------------------------------
-// Reported fields: both densities (FP64, shift added back, one pass), then rho_l, rho_v and the
+// Reported fields in 2D: both densities (FP64, shift added back, one pass), then rho_l, rho_v and the
 // barycentric
 // velocity u = (j_l + j_v + (F_l + F_v) / 2) / (rho_l + rho_v).  Grid-stride, test cadence only.
 // ------------------------------------------------------------------------------------------
@@ -555,21 +555,13 @@ hipError_t step2c_typed(int q, const S* src_l, const S* src_v, S* dst_l, S* dst_
 }
 
 template <typename S>
-hipError_t fields2c_typed(int q, const S* f_l, const S* f_v, double* dens, float* rho_l,
+hipError_t fields2c_typed(const S* f_l, const S* f_v, double* dens, float* rho_l,
                           float* rho_v, float* u, const Step2cArgs& a, hipStream_t st)
 {
     const dim3 grid = grid_nodes(a.N);
-    if (q == SC_D2Q9) {
-        hipLaunchKernelGGL((k_dens2c<9, S>), grid, dim3(256), 0, st, f_l, f_v, dens, a);
-        hipLaunchKernelGGL((k_fields2c<9, S>), grid, dim3(256), 0, st, f_l, f_v, dens, rho_l,
-                           rho_v, u, a);
-    } else if (q == SC_D3Q19) {
-        hipLaunchKernelGGL((k_dens2c<19, S>), grid, dim3(256), 0, st, f_l, f_v, dens, a);
-        hipLaunchKernelGGL((k_fields2c<19, S>), grid, dim3(256), 0, st, f_l, f_v, dens, rho_l,
-                           rho_v, u, a);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((k_dens2c<9, S>), grid, dim3(256), 0, st, f_l, f_v, dens, a);
+    hipLaunchKernelGGL((k_fields2c<9, S>), grid, dim3(256), 0, st, f_l, f_v, dens, rho_l, rho_v, u,
+                       a);
     return hipGetLastError();
 }
 
@@ -609,19 +601,19 @@ hipError_t launch_step2c(int q, int storage, const void* src_l, const void* src_
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_fields2c(int q, int storage, const void* f_l, const void* f_v, double* dens,
+hipError_t launch_fields2c(int storage, const void* f_l, const void* f_v, double* dens,
                            float* rho_l, float* rho_v, float* u, const Step2cArgs& a,
                            hipStream_t st)
 {
     switch (storage) {
         case SC_STORE_F32:
-            return fields2c_typed<float>(q, (const float*)f_l, (const float*)f_v, dens, rho_l,
+            return fields2c_typed<float>((const float*)f_l, (const float*)f_v, dens, rho_l,
                                          rho_v, u, a, st);
         case SC_STORE_F16:
-            return fields2c_typed<_Float16>(q, (const _Float16*)f_l, (const _Float16*)f_v, dens,
+            return fields2c_typed<_Float16>((const _Float16*)f_l, (const _Float16*)f_v, dens,
                                             rho_l, rho_v, u, a, st);
         case SC_STORE_BF16:
-            return fields2c_typed<__bf16>(q, (const __bf16*)f_l, (const __bf16*)f_v, dens, rho_l,
+            return fields2c_typed<__bf16>((const __bf16*)f_l, (const __bf16*)f_v, dens, rho_l,
                                           rho_v, u, a, st);
     }
     return hipErrorInvalidValue;

@@ -1132,12 +1132,23 @@ __global__ void k_fill_u64(unsigned long long* p, unsigned long long v, int64_t 
         else return hipErrorInvalidValue;                                                         \
     } while (0)
 
-hipError_t launch_psi(int q, int storage, const void* f, double* psi, const FieldArgs& a,
-                      hipStream_t st)
+hipError_t launch_psi(int storage, const void* f, double* psi, const FieldArgs& a, hipStream_t st)
 {
-    SC_DISPATCH(q, storage,
-                hipLaunchKernelGGL((k_psi<QQ, SS>), grid_for(a.N), dim3(256), 0, st,
-                                   (const SS*)f, psi, a));
+    switch (storage) {
+        case SC_STORE_F32:
+            hipLaunchKernelGGL((k_psi<9, float>), grid_for(a.N), dim3(256), 0, st, (const float*)f,
+                               psi, a);
+            break;
+        case SC_STORE_F16:
+            hipLaunchKernelGGL((k_psi<9, _Float16>), grid_for(a.N), dim3(256), 0, st,
+                               (const _Float16*)f, psi, a);
+            break;
+        case SC_STORE_BF16:
+            hipLaunchKernelGGL((k_psi<9, __bf16>), grid_for(a.N), dim3(256), 0, st,
+                               (const __bf16*)f, psi, a);
+            break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -1159,15 +1170,9 @@ hipError_t launch_pressure(int q, int storage, const void* f, double* p, const F
     return hipGetLastError();
 }
 
-hipError_t launch_laplacian(int q, const double* p, double* lap, const FieldArgs& a,
-                            hipStream_t st)
+hipError_t launch_laplacian(const double* p, double* lap, const FieldArgs& a, hipStream_t st)
 {
-    if (q == 9)
-        hipLaunchKernelGGL((k_laplacian<9>), grid_for(a.N), dim3(256), 0, st, p, lap, a);
-    else if (q == 19)
-        hipLaunchKernelGGL((k_laplacian<19>), grid_for(a.N), dim3(256), 0, st, p, lap, a);
-    else
-        return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_laplacian<9>), grid_for(a.N), dim3(256), 0, st, p, lap, a);
     return hipGetLastError();
 }
 
