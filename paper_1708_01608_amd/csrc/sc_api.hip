@@ -615,15 +615,14 @@ int label_current(sc_sim* s, uint32_t* labels_d, uint32_t* ncomp_host, const uin
         TRY(ensure(s, s->mask8, (size_t)s->N));
         HIPX(hipMemcpyAsync(s->mask8.p, mask_host, (size_t)s->N, hipMemcpyHostToDevice,
                             s->stream));
-        HIPX(launch_mask_from_bytes((const uint8_t*)s->mask8.p, (uint32_t*)s->parent.p, s->N,
+        HIPX(launch_mask_from_bytes((const uint8_t*)s->mask8.p, (uint32_t*)s->parent.p, fa,
                                     s->stream));
     } else {
         HIPX(launch_mask_from_rho(s->q, s->p.storage, s->f[s->cur], (uint32_t*)s->parent.p, fa,
                                   s->stream));
     }
     uint32_t* ncomp_d = (uint32_t*)((char*)s->small.p + 64);
-    HIPX(launch_union(s->q, (uint32_t*)s->parent.p, ncomp_d, fa, s->stream));
-    HIPX(launch_flatten((uint32_t*)s->parent.p, labels_d, ncomp_d, s->N, s->stream));
+    HIPX(launch_labels(s->q, labels_d, (uint32_t*)s->parent.p, ncomp_d, fa, s->stream));
     if (ncomp_host)
         HIPX(hipMemcpyAsync(ncomp_host, ncomp_d, sizeof(uint32_t), hipMemcpyDeviceToHost,
                             s->stream));
@@ -1872,14 +1871,13 @@ int sc_label_bubbles_noalloc(sc_sim* s, const uint8_t* mask_dev, uint32_t* label
     uint32_t* parent = base;
     uint32_t* ncomp_d = base + kScratchMaxNodes;  // 256-byte aligned: kScratchMaxNodes * 4
     const FieldArgs fa = field_args(s);
-    // every parent entry below N is written by the mask kernel; the counter is cleared by the
-    // union kernel (the array keeps the previous call's contents)
+    // every scratch entry that is read is written first; the counter is cleared by the union
+    // kernel (the array keeps the previous call's contents)
     if (mask_dev)
-        HIPX(launch_mask_from_bytes(mask_dev, parent, s->N, s->stream));
+        HIPX(launch_mask_from_bytes(mask_dev, parent, fa, s->stream));
     else
         HIPX(launch_mask_from_rho(s->q, s->p.storage, s->f[s->cur], parent, fa, s->stream));
-    HIPX(launch_union(s->q, parent, ncomp_d, fa, s->stream));
-    HIPX(launch_flatten(parent, labels_dev, ncomp_d, s->N, s->stream));
+    HIPX(launch_labels(s->q, labels_dev, parent, ncomp_d, fa, s->stream));
     uint32_t nc = 0;
     HIPX(hipMemcpyAsync(&nc, ncomp_d, sizeof(nc), hipMemcpyDeviceToHost, s->stream));
     HIPX(hipStreamSynchronize(s->stream));

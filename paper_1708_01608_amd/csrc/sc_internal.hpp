@@ -129,21 +129,22 @@ int totals_blocks(int64_t N);
 hipError_t launch_totals(int q, int storage, const void* f, double* partials, double* out_d,
                          const FieldArgs& a, hipStream_t st);
 
-// Labelling: parent[N] (uint32, 0xffffffff = liquid), labels[N] (1 + root, 0 = liquid).
-// Gas mask (as launch_mask_from_rho) and the FP64 totals (as launch_totals, into out_d[4]) from
-// one sweep of the populations.
-hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* parent,
-                              double* partials, double* out_d, const FieldArgs& a, hipStream_t st);
-hipError_t launch_mask_from_rho(int q, int storage, const void* f, uint32_t* parent,
+// Sums the block partials of nb <= 1024 blocks in block order into out_d[4].
+hipError_t launch_totals_final(const double* partials, int nb, double* out_d, double base_mass,
+                               hipStream_t st);
+
+// Labelling (sc_label.hip), in two calls: the gas mask, as words in scratch[N] (8-byte aligned;
+// from rho < theta, the same with the FP64 totals, as launch_totals, into out_d[4] from one sweep
+// of the populations, or from bytes); then the labels (1 + root, 0 = liquid) and the component
+// count.
+hipError_t launch_mask_from_rho(int q, int storage, const void* f, uint32_t* scratch,
                                 const FieldArgs& a, hipStream_t st);
-hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* parent, int64_t N,
+hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* scratch,
+                              double* partials, double* out_d, const FieldArgs& a, hipStream_t st);
+hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* scratch, const FieldArgs& a,
                                   hipStream_t st);
-// Union-find of the mask in parent (tile-local in LDS, then the links between tiles); with
-// zero_counter, the counter of the flatten that follows is set to zero.
-hipError_t launch_union(int q, uint32_t* parent, uint32_t* zero_counter, const FieldArgs& a,
-                        hipStream_t st);
-hipError_t launch_flatten(uint32_t* parent, uint32_t* labels, uint32_t* ncomp_d, int64_t N,
-                          hipStream_t st);
+hipError_t launch_labels(int q, uint32_t* labels, uint32_t* scratch, uint32_t* ncomp_d,
+                         const FieldArgs& a, hipStream_t st);
 
 // Bubble statistics and the merge test.
 hipError_t launch_gather_labels(const uint32_t* labels, const int64_t* nodes_d, uint32_t* out_d,

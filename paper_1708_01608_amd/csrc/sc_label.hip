@@ -1,0 +1,646 @@
+// sc_label.hip -- gas mask, FP64 totals and canonical bubble labels of libsc (gfx950).
+//
+// Labels are 1 + the smallest linear index of a component (Fig. 1 step 7).  The mask is kept as
+// one 64-bit word for each 64-node segment of a row along x, and the union-find works on the runs
+// of a word instead of on nodes: a bubble of R = 12 has 7,200 nodes in about 450 runs, and all
+// links between two rows are found with a few bit operations.  Only run starts have parents.  Two
+// starts of a row are never neighbours unless a segment ends between them, so the parent of the
+// start at column x of row r lies at entry r ceil(nx / 2) + x / 2, and the parents and the words
+// together fit the N entries of the caller's scratch.
+//   1. mask words (from a byte mask, from rho < threshold, or with the FP64 totals of the same
+//      sweep);
+//   2. k_label_local: a block unites the runs of its tile (256 words: 16 x 16 rows of 64 nodes, in
+//      2D 256 rows) in LDS and writes every run's parent;
+//   3. k_label_cross: the links between tiles, between segments and around the box, in global
+//      memory;
+//   4. k_label_flatten: every gas node takes its run's root.
+// Roots link to the smaller index, so the labels are canonical whatever the order of the unions.
+// 256^3 mask with 8.6% gas in 200 balls, microseconds with a union a node (local in 16^3 tiles) and
+// now: mask 25 -> 6, local 118 -> 22, cross 268 -> 31, flatten 36 -> 34; the call 477 -> 115.
+#include <algorithm>
+
+#include "sc_device.hpp"
+#include "sc_internal.hpp"
+#include "sc_stepcore.hpp"
+
+namespace sc {
+
+namespace {
+
+constexpr int kSeg = 64;
+
+__host__ __device__ __forceinline__ int segs_of(int nx) { return (nx + kSeg - 1) / kSeg; }
+
+template <int Q>
+struct LabelTile;
+template <>
+struct LabelTile<9> {
+    static constexpr int RY = 256, RZ = 1;
+};
+template <>
+struct LabelTile<19> {
+    static constexpr int RY = 16, RZ = 16;
+};
+constexpr int kTileWords = 256;
+
+// ---- bits of a word --------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t below(int p) { return p ? ~0ull >> (64 - p) : 0ull; }
+
+// First bit of the run of `w` that contains bit p.
+__device__ __forceinline__ int run_start(uint64_t w, int p)
+{
+    const uint64_t gap = ~w & below(p);
+    return gap ? 64 - __clzll((long long)gap) : 0;
+}
+
+// The run of `w` that starts at bit s, as a mask.
+__device__ __forceinline__ uint64_t run_at(uint64_t w, int s)
+{
+    const uint64_t t = ~(w >> s);
+    const int len = t ? __ffsll((long long)t) - 1 : 64;
+    return below(min(len, 64 - s)) << s;
+}
+
+// The scratch of a labelling: the words (one a segment, rows one after the other), then the parents.
+// A parent is kept as its entry times two plus the parity of its column, which names the node.
+struct Scratch {
+    uint64_t* words;
+    uint32_t* parent;
+    uint32_t half;  // parents a row
+};
+__host__ __device__ __forceinline__ Scratch scratch_of(uint32_t* p, const FieldArgs& a)
+{
+    const size_t words = (size_t)segs_of(a.nx) * a.ny * a.nz;
+    return Scratch{reinterpret_cast<uint64_t*>(p), p + 2 * words, (uint32_t)(a.nx + 1) / 2};
+}
+// Code of the run start at column x of row r, and the node of a code.
+__device__ __forceinline__ uint32_t code_of(uint32_t r, int x, uint32_t half)
+{
+    return 2 * (r * half + ((uint32_t)x >> 1)) + ((uint32_t)x & 1);
+}
+__device__ __forceinline__ uint32_t node_of_code(uint32_t c, uint32_t half, int nx)
+{
+    const uint32_t e = c >> 1, r = e / half;
+    return r * (uint32_t)nx + 2 * (e - r * half) + (c & 1);
+}
+
+// Segment `w` of the box: first node, width, row.
+struct Seg {
+    int64_t n;
+    uint32_t r;
+    int width, x0, y, z;
+};
+__device__ __forceinline__ Seg seg_of(int64_t w, const FieldArgs& a)
+{
+    const uint32_t segs = (uint32_t)segs_of(a.nx), r = (uint32_t)w / segs, s = (uint32_t)w - r * segs;
+    Seg g;
+    g.x0 = (int)s * kSeg;
+    g.width = min(kSeg, a.nx - g.x0);
+    g.r = r;
+    g.n = (int64_t)r * a.nx + g.x0;
+    g.z = (int)(r / (uint32_t)a.ny);
+    g.y = (int)(r - (uint32_t)g.z * (uint32_t)a.ny);
+    return g;
+}
+
+// ---- mask words ----------------------------------------------------------------------------------
+// A wave takes kMaskWords segments a turn, loads first.
+constexpr int kMaskWords = 8;
+
+__global__ void __launch_bounds__(256) k_mask_bytes(const uint8_t* __restrict__ mask,
+                                                    uint64_t* __restrict__ out, int64_t words,
+                                                    FieldArgs a)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 4 * (int64_t)blockIdx.x;
+    for (int64_t w0 = wave * kMaskWords; w0 < words; w0 += 4 * (int64_t)gridDim.x * kMaskWords) {
+        bool gas[kMaskWords];
+#pragma unroll
+        for (int u = 0; u < kMaskWords; ++u) {
+            gas[u] = false;
+            if (w0 + u >= words) continue;
+            const Seg g = seg_of(w0 + u, a);
+            if (lane < g.width) gas[u] = mask[g.n + lane] != 0;
+        }
+        uint64_t mine = 0ull;
+#pragma unroll
+        for (int u = 0; u < kMaskWords; ++u) {
+            const uint64_t m = __ballot(gas[u]);
+            if (lane == u) mine = m;
+        }
+        if (lane < kMaskWords && w0 + lane < words) out[w0 + lane] = mine;
+    }
+}
+
+// The same where every segment is full (nx a multiple of 64) and the mask 16-byte aligned: a lane
+// takes 16 bytes, four lanes a word, a wave 16 words a turn.  16.8 MB: 25 us with a byte a lane,
+// which a wave's 64-byte loads bound, 6 us so.
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v)
+{
+    return (v & 0xffu ? 1u : 0u) | (v & 0xff00u ? 2u : 0u) | (v & 0xff0000u ? 4u : 0u) |
+           (v & 0xff000000u ? 8u : 0u);
+}
+
+__global__ void __launch_bounds__(256) k_mask_bytes16(const uint4* __restrict__ mask,
+                                                      uint64_t* __restrict__ out, int64_t words)
+{
+    const int64_t quads = words * 4, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < quads; q += stride) {
+        const uint4 v = mask[q];
+        uint64_t m = (uint64_t)(nonzero_bytes(v.x) | nonzero_bytes(v.y) << 4 |
+                                nonzero_bytes(v.z) << 8 | nonzero_bytes(v.w) << 12)
+                     << 16 * (threadIdx.x & 3);
+        // the four lanes of a word are all in range or all out of it
+        m |= __shfl_xor((unsigned long long)m, 1, 64);
+        m |= __shfl_xor((unsigned long long)m, 2, 64);
+        if ((threadIdx.x & 3) == 0) out[q >> 2] = m;
+    }
+}
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_down(v, off, 64);
+    return v;
+}
+
+// The gas mask rho < theta (FP64 density, the step kernel's order of the sum) and, with TOTALS, per
+// block the sums of the pulled values and their momenta: the pulled values are a permutation of the
+// stored ones, so these are the totals of the populations.  Two segments a turn, loads of both
+// first (one wave carries many, and would otherwise wait out a full memory latency each).
+template <int Q, typename S, bool TOTALS>
+__global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
+                                                  uint64_t* __restrict__ out,
+                                                  double* __restrict__ partials, int64_t words,
+                                                  FieldArgs a)
+{
+    using L = lat<Q>;
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 4 * (int64_t)blockIdx.x;
+    double m = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
+    for (int64_t w0 = wave * 2; w0 < words; w0 += 8 * (int64_t)gridDim.x) {
+        float g[2][Q];
+        Seg sg[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (w0 + u >= words) continue;
+            sg[u] = seg_of(w0 + u, a);
+            const int x = sg[u].x0 + lane, y = sg[u].y, z = sg[u].z;
+            if (lane < sg[u].width)
+                pull_node<Q>(f, a.N, a.nx, a.ny, x, wrap_once(x - 1, a.nx), wrap_once(x + 1, a.nx),
+                             y, wrap_once(y - 1, a.ny), wrap_once(y + 1, a.ny), z,
+                             Q == 19 ? wrap_once(z - 1, a.nz) : 0,
+                             Q == 19 ? wrap_once(z + 1, a.nz) : 0, g[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (w0 + u >= words) continue;
+            bool gas = false;
+            if (lane < sg[u].width) {
+                double s = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const double v = (double)g[u][i];
+                    s += v;
+                    if (!TOTALS) continue;
+                    if (L::ex[i] > 0) sx += v; else if (L::ex[i] < 0) sx -= v;
+                    if (L::ey[i] > 0) sy += v; else if (L::ey[i] < 0) sy -= v;
+                    if (L::ez[i] > 0) sz += v; else if (L::ez[i] < 0) sz -= v;
+                }
+                gas = a.rho_ref_d + s < a.theta;
+                m += s;
+                jx += sx;
+                jy += sy;
+                jz += sz;
+            }
+            const uint64_t mask = __ballot(gas);
+            if (lane == 0) out[w0 + u] = mask;
+        }
+    }
+    if constexpr (TOTALS) {
+        __shared__ double red[4][4];
+        m = wave_sum(m); jx = wave_sum(jx); jy = wave_sum(jy); jz = wave_sum(jz);
+        const int w = threadIdx.x >> 6;
+        if (lane == 0) { red[w][0] = m; red[w][1] = jx; red[w][2] = jy; red[w][3] = jz; }
+        __syncthreads();
+        if (threadIdx.x < 4) {
+            double t = 0.0;
+            for (int k = 0; k < 4; ++k) t += red[k][threadIdx.x];
+            partials[(int64_t)blockIdx.x * 4 + threadIdx.x] = t;
+        }
+    }
+}
+
+// ---- union-find over runs -------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t lds_load(const uint32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Roots of a and b, followed together so that their loads overlap.  In LDS the walk halves its path:
+// a visited entry is relinked to its grandparent, an ancestor with a smaller index, so concurrent
+// unions stay correct.
+__device__ __forceinline__ uint32_t lds_root(uint32_t* lp, uint32_t x)
+{
+    while (true) {
+        const uint32_t p = lds_load(lp + x);
+        if (p == x) return x;
+        const uint32_t g = lds_load(lp + p);
+        if (g == p) return p;
+        __hip_atomic_store(lp + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        x = g;
+    }
+}
+
+__device__ void lds_unite(uint32_t* lp, uint32_t a, uint32_t b)
+{
+    while (true) {
+        a = lds_root(lp, a);
+        b = lds_root(lp, b);
+        if (a == b) return;
+        if (a > b) { const uint32_t t = a; a = b; b = t; }
+        const uint32_t old = atomicMin(lp + b, a);
+        if (old == b) return;
+        b = old;
+    }
+}
+
+// parent of a code (an agent-scope load: other blocks relink)
+__device__ __forceinline__ uint32_t load_parent(const uint32_t* parent, uint32_t c)
+{
+    return __hip_atomic_load(parent + (c >> 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// parents only decrease and always point inside the same set, so a stale read is still an ancestor;
+// atomicMin links root b under a and reports a concurrent re-link through its result.
+__device__ void unite(uint32_t* parent, uint32_t a, uint32_t b)
+{
+    while (true) {
+        while (true) {
+            if (a == b) return;
+            const uint32_t pa = load_parent(parent, a), pb = load_parent(parent, b);
+            if (pa == a && pb == b) break;
+            a = pa;
+            b = pb;
+        }
+        if (a > b) { const uint32_t t = a; a = b; b = t; }
+        const uint32_t old = atomicMin(parent + (b >> 1), a);
+        if (old == b) return;
+        b = old;
+    }
+}
+
+// Calls link(sa, sb) once for every pair of touching runs of two adjacent rows: sa, sb the first
+// bits of the runs of words A and B; `wide` rows touch diagonally too.
+template <typename F>
+__device__ __forceinline__ void touching_runs(uint64_t A, uint64_t B, bool wide, F link)
+{
+    const uint64_t reach = wide ? (A | A << 1 | A >> 1) : A;
+    if (!(reach & B)) return;
+    for (uint64_t left = A; left;) {
+        const int sa = __ffsll((long long)left) - 1;
+        const uint64_t run = run_at(A, sa);
+        left &= ~run;
+        uint64_t hit = B & (wide ? (run | run << 1 | run >> 1) : run);
+        while (hit) {
+            const int sb = run_start(B, __ffsll((long long)hit) - 1);
+            hit &= ~run_at(B, sb);
+            link(sa, sb);
+        }
+    }
+}
+
+// The rows after a row that its nodes link to (half of the lattice's directions, the other half
+// seen from there), and whether along x by one node as well as straight.
+template <int Q>
+struct RowLinks;
+template <>
+struct RowLinks<9> {
+    static constexpr int n = 1;
+    static constexpr int dy[1] = {1}, dz[1] = {0};
+    static constexpr bool wide[1] = {true};
+};
+template <>
+struct RowLinks<19> {
+    static constexpr int n = 4;
+    static constexpr int dy[4] = {1, 0, 1, 1}, dz[4] = {0, 1, 1, -1};
+    static constexpr bool wide[4] = {true, true, false, false};
+};
+
+// One word a thread; the index of a run in LDS is its word's index times 32 plus half its first
+// bit, which follows the global order, so a local root is the smallest node of its local set.
+// Bound by the latency of the LDS chains.
+template <int Q>
+__global__ void __launch_bounds__(kTileWords) k_label_local(uint32_t* scratch,
+                                                            uint32_t* zero_counter, FieldArgs a)
+{
+    using T = LabelTile<Q>;
+    using R = RowLinks<Q>;
+    static_assert(T::RY * T::RZ == kTileWords, "one word a thread");
+    __shared__ uint64_t bits[kTileWords];
+    __shared__ uint32_t lp[kTileWords * (kSeg / 2)];
+    // the component counter of the flatten that follows starts at zero
+    if (zero_counter && blockIdx.x == 0 && threadIdx.x == 0) *zero_counter = 0u;
+    const Scratch sc = scratch_of(scratch, a);
+    const int segs = segs_of(a.nx), gy = (a.ny + T::RY - 1) / T::RY;
+    const int b = blockIdx.x, t = threadIdx.x;
+    const int seg = b % segs, y0 = ((b / segs) % gy) * T::RY, z0 = (b / (segs * gy)) * T::RZ;
+    const int iy = t % T::RY, iz = t / T::RY;
+    const bool in = y0 + iy < a.ny && z0 + iz < a.nz;
+    const uint32_t r = (uint32_t)(y0 + iy) + (uint32_t)a.ny * (uint32_t)(z0 + iz);
+    const uint64_t A = in ? sc.words[(size_t)r * segs + seg] : 0ull;
+    bits[t] = A;
+    for (uint64_t left = A; left;) {
+        const int s = __ffsll((long long)left) - 1;
+        left &= ~run_at(A, s);
+        lp[t * 32 + (s >> 1)] = (uint32_t)(t * 32 + (s >> 1));
+    }
+    if (!__syncthreads_or(A != 0ull)) return;
+#pragma unroll
+    for (int d = 0; d < R::n; ++d) {
+        const int jy = iy + R::dy[d], jz = iz + R::dz[d];
+        // a row outside the box has no bits, so only the tile's own edges need a test
+        if (!A || jy >= T::RY || jz < 0 || jz >= T::RZ) continue;
+        const int u = jz * T::RY + jy;
+        touching_runs(A, bits[u], R::wide[d], [&](int sa, int sb) {
+            lds_unite(lp, (uint32_t)(t * 32 + (sa >> 1)), (uint32_t)(u * 32 + (sb >> 1)));
+        });
+    }
+    __syncthreads();
+    for (uint64_t left = A; left;) {
+        const int s = __ffsll((long long)left) - 1;
+        left &= ~run_at(A, s);
+        const uint32_t e = lds_root(lp, (uint32_t)(t * 32 + (s >> 1)));
+        const int w = (int)(e >> 5), h = 2 * (int)(e & 31);
+        // the start of the root's run is at bit h or h + 1 of its word: the one that is gas and
+        // has no gas before it
+        const uint64_t W = bits[w], starts = W & ~(W << 1);
+        const int x = seg * kSeg + h + (int)(~(starts >> h) & 1ull);
+        const uint32_t rr = (uint32_t)(y0 + w % T::RY) + (uint32_t)a.ny * (uint32_t)(z0 + w / T::RY);
+        sc.parent[(size_t)r * sc.half + ((seg * kSeg + s) >> 1)] = code_of(rr, x, sc.half);
+    }
+}
+
+// The links the tiles could not see, one word a thread: to the next segment, to rows of other
+// tiles, and around the box.  Bound by the latency of the parents' loads, which go past the L2s
+// of the eight XCDs: both ends are followed together, and a pair of parents just united by this
+// thread is not looked up again.
+template <int Q>
+__global__ void __launch_bounds__(256) k_label_cross(uint32_t* scratch, int64_t words, FieldArgs a)
+{
+    using T = LabelTile<Q>;
+    using R = RowLinks<Q>;
+    const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (w >= words) return;
+    const Scratch sc = scratch_of(scratch, a);
+    const uint64_t A = sc.words[w];
+    if (!A) return;
+    const Seg g = seg_of(w, a);
+    const uint32_t segs = (uint32_t)segs_of(a.nx), seg = (uint32_t)g.x0 / kSeg;
+    const int last = g.width - 1;
+    const bool first_gas = A & 1ull, last_gas = A >> last & 1ull;
+    const uint32_t sn = seg + 1 < segs ? seg + 1 : 0, sb = seg > 0 ? seg - 1 : segs - 1;
+    const int wb = min(kSeg, a.nx - (int)sb * kSeg);  // width of the segment before
+    uint32_t la = 0u, lb = 0u;
+    bool have = false;
+    auto link = [&](uint32_t ra, int xa, uint32_t rb, int xb) {
+        const uint32_t pa = load_parent(sc.parent, code_of(ra, xa, sc.half));
+        const uint32_t pb = load_parent(sc.parent, code_of(rb, xb, sc.half));
+        if (pa == pb || (have && pa == la && pb == lb)) return;
+        la = pa;
+        lb = pb;
+        have = true;
+        unite(sc.parent, pa, pb);
+    };
+    auto word = [&](uint32_t r, uint32_t s) { return sc.words[(size_t)r * segs + s]; };
+    if (last_gas && (word(g.r, sn) & 1ull))
+        link(g.r, g.x0 + run_start(A, last), g.r, (int)sn * kSeg);
+#pragma unroll
+    for (int d = 0; d < R::n; ++d) {
+        const int y = g.y + R::dy[d], z = g.z + R::dz[d];
+        const bool here = y < a.ny && z >= 0 && z < a.nz && y / T::RY == g.y / T::RY &&
+                          z / T::RZ == g.z / T::RZ;
+        if (here && !(R::wide[d] && (first_gas || last_gas))) continue;
+        const uint32_t r2 = (uint32_t)wrap_once(y, a.ny) + (uint32_t)a.ny * (uint32_t)wrap_once(z, a.nz);
+        if (!here)
+            touching_runs(A, word(r2, seg), R::wide[d],
+                          [&](int sa, int sb2) { link(g.r, g.x0 + sa, r2, g.x0 + sb2); });
+        if (!R::wide[d]) continue;
+        if (last_gas && (word(r2, sn) & 1ull))
+            link(g.r, g.x0 + run_start(A, last), r2, (int)sn * kSeg);
+        if (first_gas) {
+            const uint64_t B = word(r2, sb);
+            if (B >> (wb - 1) & 1ull) link(g.r, g.x0, r2, (int)sb * kSeg + run_start(B, wb - 1));
+        }
+    }
+}
+
+// Labels from the words and the parents.  Bound by the write of the labels; most segments hold no
+// gas and are filled with zeros at once, the others' walks to their roots go side by side.
+template <int FW>
+__global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ lab,
+                                                       uint32_t* scratch, uint32_t* ncomp,
+                                                       int64_t words, FieldArgs a)
+{
+    const Scratch sc = scratch_of(scratch, a);
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) + 4 * (int)blockIdx.x);
+    const uint32_t segs = (uint32_t)segs_of(a.nx);
+    unsigned roots = 0;
+    for (int64_t w0 = (int64_t)wave * FW; w0 < words; w0 += 4 * (int64_t)gridDim.x * FW) {
+        uint64_t A[FW];
+#pragma unroll
+        for (int u = 0; u < FW; ++u) A[u] = w0 + u < words ? sc.words[w0 + u] : 0ull;
+#pragma unroll
+        for (int u = 0; u < FW; ++u)  // the same in every lane: scalar, so that its tests are branches
+            A[u] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)A[u]) |
+                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(A[u] >> 32)) << 32;
+        // row and first column of the segments, and where their labels start
+        uint32_t row[FW];
+        int x0[FW];
+        uint32_t rr = __builtin_amdgcn_readfirstlane((uint32_t)w0 / segs);
+        uint32_t ss = (uint32_t)w0 - rr * segs;
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < FW; ++u) {
+            row[u] = rr;
+            x0[u] = (int)ss * kSeg;
+            if (++ss == segs) {
+                ss = 0;
+                ++rr;
+            }
+            any |= A[u] != 0ull;
+        }
+        uint32_t v[FW];
+#pragma unroll
+        for (int u = 0; u < FW; ++u) v[u] = 0u;
+        if (any) {
+            uint32_t r[FW];
+            int s[FW];
+#pragma unroll
+            for (int u = 0; u < FW; ++u) {
+                r[u] = 0u;
+                s[u] = 0;
+                if (!A[u]) continue;
+                s[u] = run_start(A[u], lane);
+                r[u] = code_of(row[u], x0[u] + s[u], sc.half);
+            }
+            bool more = true;
+            while (more) {
+                more = false;
+                uint32_t p[FW];
+#pragma unroll
+                for (int u = 0; u < FW; ++u) {
+                    p[u] = r[u];
+                    if (A[u] && (A[u] >> lane & 1ull)) p[u] = sc.parent[r[u] >> 1];
+                }
+#pragma unroll
+                for (int u = 0; u < FW; ++u) {
+                    more |= p[u] != r[u];
+                    r[u] = p[u];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < FW; ++u) {
+                if (!A[u] || !(A[u] >> lane & 1ull)) continue;
+                v[u] = node_of_code(r[u], sc.half, a.nx) + 1;
+                if (s[u] == lane && r[u] == code_of(row[u], x0[u] + lane, sc.half)) ++roots;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < FW; ++u)
+            if (w0 + u < words && x0[u] + lane < a.nx)
+                lab[(int64_t)row[u] * a.nx + x0[u] + lane] = v[u];
+    }
+    if (!__ballot(roots != 0)) return;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) roots += __shfl_xor(roots, off, 64);
+    if (lane == 0) atomicAdd(ncomp, roots);
+}
+
+// Block partials to the totals: the partials of a component are summed in block order by one
+// thread; the block stages them in LDS first, so the ordered chain waits on LDS and not on one
+// memory latency after the other (25 -> 11 us for 1,024 blocks).
+constexpr int kTotBlocks = 1024;
+
+__global__ void __launch_bounds__(256) k_totals_final(const double* __restrict__ partials, int nb,
+                                                      double* __restrict__ out, double base_mass)
+{
+    __shared__ double v[4 * kTotBlocks];
+    for (int k = threadIdx.x; k < 4 * nb; k += 256) v[k] = partials[k];
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c >= 4) return;
+    double s = 0.0;
+#pragma unroll 16
+    for (int b = 0; b < nb; ++b) s += v[4 * b + c];
+    out[c] = (c == 0) ? base_mass + s : s;
+}
+
+int64_t words_of(const FieldArgs& a) { return (int64_t)segs_of(a.nx) * a.ny * a.nz; }
+
+dim3 word_grid(int64_t words, int per_block)
+{
+    const int64_t b = (words + per_block - 1) / per_block;
+    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(b, 65536)));
+}
+
+template <int Q, typename S, bool TOTALS>
+void mask_rho(const void* f, uint32_t* scratch, double* partials, int nb, const FieldArgs& a,
+              hipStream_t st)
+{
+    hipLaunchKernelGGL((k_mask_rho<Q, S, TOTALS>), dim3(nb), dim3(256), 0, st, (const S*)f,
+                       scratch_of(scratch, a).words, partials, words_of(a), a);
+}
+
+template <bool TOTALS>
+hipError_t mask_rho_any(int q, int storage, const void* f, uint32_t* scratch, double* partials,
+                        const FieldArgs& a, hipStream_t st)
+{
+    const int nb = totals_blocks(a.N);
+    if (q == 9 && storage == SC_STORE_F32) mask_rho<9, float, TOTALS>(f, scratch, partials, nb, a, st);
+    else if (q == 9 && storage == SC_STORE_F16) mask_rho<9, _Float16, TOTALS>(f, scratch, partials, nb, a, st);
+    else if (q == 9 && storage == SC_STORE_BF16) mask_rho<9, __bf16, TOTALS>(f, scratch, partials, nb, a, st);
+    else if (q == 19 && storage == SC_STORE_F32) mask_rho<19, float, TOTALS>(f, scratch, partials, nb, a, st);
+    else if (q == 19 && storage == SC_STORE_F16) mask_rho<19, _Float16, TOTALS>(f, scratch, partials, nb, a, st);
+    else if (q == 19 && storage == SC_STORE_BF16) mask_rho<19, __bf16, TOTALS>(f, scratch, partials, nb, a, st);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+template <int Q>
+hipError_t label_words(uint32_t* lab, uint32_t* scratch, uint32_t* ncomp, const FieldArgs& a,
+                       hipStream_t st)
+{
+    using T = LabelTile<Q>;
+    const int64_t words = words_of(a);
+    const int64_t tiles = (int64_t)segs_of(a.nx) * ((a.ny + T::RY - 1) / T::RY) *
+                          ((a.nz + T::RZ - 1) / T::RZ);
+    const int64_t cross = (words + 255) / 256;
+    if (tiles > 0x7fffffff || cross > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_label_local<Q>), dim3((unsigned)tiles), dim3(kTileWords), 0, st, scratch,
+                       ncomp, a);
+    hipLaunchKernelGGL((k_label_cross<Q>), dim3((unsigned)cross), dim3(256), 0, st, scratch, words,
+                       a);
+    // one word a wave while the waves do not fill the chip (its latencies are then the bound)
+    if (words < 16384)
+        hipLaunchKernelGGL(k_label_flatten<1>, word_grid(words, 4), dim3(256), 0, st, lab,
+                           scratch, ncomp, words, a);
+    else
+        hipLaunchKernelGGL(k_label_flatten<4>, word_grid(words, 16), dim3(256), 0, st, lab,
+                           scratch, ncomp, words, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int totals_blocks(int64_t N)
+{
+    const int64_t b = (N + 255) / 256;
+    return (int)(b < kTotBlocks ? (b < 1 ? 1 : b) : kTotBlocks);
+}
+
+hipError_t launch_totals_final(const double* partials, int nb, double* out_d, double base_mass,
+                               hipStream_t st)
+{
+    if (nb < 1 || nb > kTotBlocks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_totals_final, dim3(1), dim3(256), 0, st, partials, nb, out_d, base_mass);
+    return hipGetLastError();
+}
+
+hipError_t launch_mask_from_rho(int q, int storage, const void* f, uint32_t* scratch,
+                                const FieldArgs& a, hipStream_t st)
+{
+    return mask_rho_any<false>(q, storage, f, scratch, nullptr, a, st);
+}
+
+hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* scratch,
+                              double* partials, double* out_d, const FieldArgs& a, hipStream_t st)
+{
+    const hipError_t e = mask_rho_any<true>(q, storage, f, scratch, partials, a, st);
+    if (e != hipSuccess) return e;
+    return launch_totals_final(partials, totals_blocks(a.N), out_d, (double)a.N * a.rho_ref_d, st);
+}
+
+hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* scratch, const FieldArgs& a,
+                                  hipStream_t st)
+{
+    const int64_t words = words_of(a);
+    if (a.nx % kSeg == 0 && (uintptr_t)mask_d % 16 == 0)
+        hipLaunchKernelGGL(k_mask_bytes16, word_grid(words, 64), dim3(256), 0, st,
+                           (const uint4*)mask_d, scratch_of(scratch, a).words, words);
+    else
+        hipLaunchKernelGGL(k_mask_bytes, word_grid(words, 4 * kMaskWords), dim3(256), 0, st,
+                           mask_d, scratch_of(scratch, a).words, words, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_labels(int q, uint32_t* labels, uint32_t* scratch, uint32_t* ncomp_d,
+                         const FieldArgs& a, hipStream_t st)
+{
+    if (q == 9) return label_words<9>(labels, scratch, ncomp_d, a, st);
+    if (q == 19) return label_words<19>(labels, scratch, ncomp_d, a, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace sc

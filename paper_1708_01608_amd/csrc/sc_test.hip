@@ -1,5 +1,6 @@
-// sc_test.hip -- output fields, FP64 EOS / Laplacian / totals, gas labelling, bubble statistics,
-// merge criterion and blowing-agent source of libsc (gfx950).
+// sc_test.hip -- 2D output fields, FP64 EOS / Laplacian / totals, bubble statistics, merge
+// criterion and blowing-agent source of libsc (gfx950); the gas mask and labels are in
+// sc_label.hip, the 3D fields in sc_fields.hip.
 //
 // Every kernel reads the pull-layout populations: f_i(x, t) = stored_i(x - e_i) + w_i rho_ref.
 #include <algorithm>
@@ -212,14 +213,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-constexpr int kTotBlocks = 1024;
-
-int totals_blocks(int64_t N)
-{
-    int64_t b = (N + 255) / 256;
-    return (int)(b < kTotBlocks ? (b < 1 ? 1 : b) : kTotBlocks);
-}
-
 // Sums the stored values directly (a permutation of the pulled ones): M = N rho_ref + sum g,
 // J = sum_i e_i sum_y g_i(y).
 template <int Q, typename S>
@@ -247,314 +240,6 @@ __global__ void __launch_bounds__(256) k_totals(const S* f, double* partials, Fi
         double s = 0.0;
         for (int k = 0; k < 4; ++k) s += red[k][threadIdx.x];
         partials[(int64_t)blockIdx.x * 4 + threadIdx.x] = s;
-    }
-}
-
-__global__ void k_totals_final(const double* partials, int nb, double* out, double base_mass)
-{
-    // one thread per component, blocks summed in index order; the loads of 16 partials are
-    // issued together before their ordered adds, so the sum waits out one latency per 16
-    const int c = threadIdx.x;
-    if (c >= 4) return;
-    double s = 0.0;
-    int b = 0;
-    for (; b + 16 <= nb; b += 16) {
-        double v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = partials[(int64_t)(b + k) * 4 + c];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s += v[k];
-    }
-    for (; b < nb; ++b) s += partials[(int64_t)b * 4 + c];
-    out[c] = (c == 0) ? base_mass + s : s;
-}
-
-// ---- gas labelling: lock-free union-find, roots linked towards the smaller index ------------
-constexpr uint32_t kLiquid = 0xffffffffu;
-
-template <int Q, typename S>
-__global__ void k_mask_rho(const S* f, uint32_t* parent, FieldArgs a)
-{
-    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < a.N;
-         n += (int64_t)gridDim.x * blockDim.x)
-        parent[n] = (rho_d<Q, S>(f, n, a) < a.theta) ? (uint32_t)n : kLiquid;
-}
-
-// The test pass's mask and FP64 totals from one sweep of pulled populations: parent[n] exactly as
-// k_mask_rho (same density, same order of the sum), and per block the partial sums of the pulled
-// values and their momenta, as k_totals forms them from the stored values (the pulled values are a
-// permutation of the stored ones, so the totals are the same sums in another order).
-template <int Q, typename S>
-__global__ void __launch_bounds__(256) k_mask_totals(const S* f, uint32_t* parent,
-                                                     double* partials, FieldArgs a)
-{
-    using L = lat<Q>;
-    double m = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-    // two nodes per pass, loads of both first (one block carries many nodes, so each pass would
-    // otherwise wait out a full memory latency); the sums keep the node order
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t n0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n0 < a.N; n0 += 2 * stride) {
-        float g[2][Q];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int64_t n = n0 + u * stride;
-            if (n < a.N) {
-                int x, y, z;
-                coords3(n, a.nx, a.ny, x, y, z);
-#pragma unroll
-                for (int i = 0; i < Q; ++i)
-                    g[u][i] = load_f(f[(int64_t)i * a.N + shifted<Q>(x, y, z, i, -1, a)]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int64_t n = n0 + u * stride;
-            if (n >= a.N) continue;
-            double s = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                const double v = (double)g[u][i];
-                s += v;
-                sx += v * L::ex[i];
-                sy += v * L::ey[i];
-                sz += v * L::ez[i];
-            }
-            parent[n] = (a.rho_ref_d + s < a.theta) ? (uint32_t)n : kLiquid;
-            m += s;
-            jx += sx;
-            jy += sy;
-            jz += sz;
-        }
-    }
-    __shared__ double red[4][4];
-    m = wave_sum(m); jx = wave_sum(jx); jy = wave_sum(jy); jz = wave_sum(jz);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { red[w][0] = m; red[w][1] = jx; red[w][2] = jy; red[w][3] = jz; }
-    __syncthreads();
-    if (threadIdx.x < 4) {
-        double t = 0.0;
-        for (int k = 0; k < 4; ++k) t += red[k][threadIdx.x];
-        partials[(int64_t)blockIdx.x * 4 + threadIdx.x] = t;
-    }
-}
-
-__global__ void k_mask_bytes(const uint8_t* mask, uint32_t* parent, int64_t N)
-{
-    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < N;
-         n += (int64_t)gridDim.x * blockDim.x)
-        parent[n] = mask[n] ? (uint32_t)n : kLiquid;
-}
-
-__device__ __forceinline__ uint32_t load_parent(const uint32_t* parent, uint32_t x)
-{
-    return __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint32_t find_root(const uint32_t* parent, uint32_t x)
-{
-    uint32_t p = load_parent(parent, x);
-    while (p != x) {
-        x = p;
-        p = load_parent(parent, x);
-    }
-    return x;
-}
-
-// parent values only decrease and always point inside the same set, so a stale read is still an
-// ancestor; atomicMin links root b under a and reports a concurrent re-link through its result.
-__device__ void unite(uint32_t* parent, uint32_t a, uint32_t b)
-{
-    while (true) {
-        a = find_root(parent, a);
-        b = find_root(parent, b);
-        if (a == b) return;
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(parent + b, a);
-        if (old == b) return;
-        b = old;
-    }
-}
-
-__global__ void k_flatten(const uint32_t* parent, uint32_t* labels, uint32_t* ncomp, int64_t N)
-{
-    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < N;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t p = parent[n];
-        if (p == kLiquid) {
-            labels[n] = 0;
-            continue;
-        }
-        uint32_t r = (uint32_t)n, q = p;
-        while (q != r) {
-            r = q;
-            q = parent[r];
-        }
-        labels[n] = r + 1;
-        if (r == (uint32_t)n) atomicAdd(ncomp, 1u);
-    }
-}
-
-// Tiled labelling.  A plain union over every lattice link sends all of them through global
-// atomics and pointer chases; on a gas-rich box that is most of the test pass.  Instead each block
-// first unites the links inside its tile in LDS (local indices follow the global index order
-// within a tile, so a local root is the smallest global index of its local set) and writes the
-// local roots to parent; a second kernel unites only the links that leave a tile (or wrap around
-// the box) through the global structure.  Roots still link to smaller indices, so the labels
-// stay the canonical 1 + smallest index of each component.
-template <int Q>
-struct UnionTile;
-template <>
-struct UnionTile<9> {
-    static constexpr int TX = 32, TY = 32, TZ = 1, THREADS = 1024;  // one node per thread
-};
-template <>
-struct UnionTile<19> {
-    static constexpr int TX = 16, TY = 16, TZ = 16, THREADS = 256;  // sixteen nodes per thread
-};
-
-__device__ __forceinline__ uint32_t lds_load(const uint32_t* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ uint32_t lds_root(const uint32_t* lp, uint32_t x)
-{
-    uint32_t p = lds_load(lp + x);
-    while (p != x) {
-        x = p;
-        p = lds_load(lp + x);
-    }
-    return x;
-}
-
-__device__ void lds_unite(uint32_t* lp, uint32_t a, uint32_t b)
-{
-    while (true) {
-        a = lds_root(lp, a);
-        b = lds_root(lp, b);
-        if (a == b) return;
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(lp + b, a);
-        if (old == b) return;
-        b = old;
-    }
-}
-
-// Neighbour (x + e_i) of a tile node stays inside the tile and the box: a local link.
-template <int Q>
-__device__ __forceinline__ bool local_link(int lx, int ly, int lz, int x, int y, int z, int i,
-                                           const FieldArgs& a)
-{
-    using L = lat<Q>;
-    using T = UnionTile<Q>;
-    const int mx = lx + L::ex[i], my = ly + L::ey[i], mz = lz + L::ez[i];
-    return mx >= 0 && mx < T::TX && my >= 0 && my < T::TY && mz >= 0 && mz < T::TZ &&
-           x + L::ex[i] >= 0 && x + L::ex[i] < a.nx && y + L::ey[i] >= 0 &&
-           y + L::ey[i] < a.ny && z + L::ez[i] >= 0 && z + L::ez[i] < a.nz;
-}
-
-template <int Q>
-__global__ void __launch_bounds__(UnionTile<Q>::THREADS) k_union_local(uint32_t* parent,
-                                                                       uint32_t* zero_counter,
-                                                                       FieldArgs a)
-{
-    // the component counter of the flatten that follows starts at zero
-    if (zero_counter && blockIdx.x == 0 && threadIdx.x == 0) *zero_counter = 0u;
-    using L = lat<Q>;
-    using T = UnionTile<Q>;
-    constexpr int NT = T::TX * T::TY * T::TZ;
-    __shared__ uint32_t lp[NT];
-    const int gx = (a.nx + T::TX - 1) / T::TX, gy = (a.ny + T::TY - 1) / T::TY;
-    const int b = blockIdx.x;
-    const int x0 = (b % gx) * T::TX, y0 = ((b / gx) % gy) * T::TY, z0 = (b / (gx * gy)) * T::TZ;
-    auto node = [&](int li, int& lx, int& ly, int& lz, int& x, int& y, int& z) {
-        lx = li % T::TX;
-        ly = (li / T::TX) % T::TY;
-        lz = li / (T::TX * T::TY);
-        x = x0 + lx; y = y0 + ly; z = z0 + lz;
-        return x < a.nx && y < a.ny && z < a.nz;
-    };
-    static_assert(64 % T::TX == 0, "a wave holds whole tile rows");
-    // runs along x: a wave holds 64 consecutive tile nodes, whole rows, so one ballot of the gas
-    // mask gives every gas node the first node of its run, which becomes its parent (x-links
-    // need no union at all)
-    constexpr uint64_t kRowStarts = T::TX == 32 ? 0x0000000100000001ull
-                                                : 0x0001000100010001ull;  // lanes with lx == 0
-    static_assert(T::TX == 32 || T::TX == 16, "row-start mask for 16- or 32-node rows");
-    for (int li = threadIdx.x; li < NT; li += blockDim.x) {
-        int lx, ly, lz, x, y, z;
-        const bool in = node(li, lx, ly, lz, x, y, z);
-        const bool gas = in && parent[idx3(x, y, z, a.nx, a.ny)] != kLiquid;
-        const uint64_t mask = __ballot(gas);
-        const uint64_t starts = mask & ~((mask << 1) & ~kRowStarts);
-        const int lane = li & 63;
-        const uint64_t upto = ~0ull >> (63 - lane);
-        lp[li] = gas ? (uint32_t)((li & ~63) + 63 - __clzll(starts & upto)) : kLiquid;
-    }
-    __syncthreads();
-    // links to other rows: two adjacent runs always have a link at which one end starts its run
-    // (the later-starting run's first node lies within the other's neighbourhood window, or the
-    // other's first node touches it), so only such links are united -- per run, not per node
-    auto starts_run = [&](int li, int lx) {
-        return lx == 0 || lds_load(lp + li - 1) == kLiquid;
-    };
-    for (int li = threadIdx.x; li < NT; li += blockDim.x) {
-        if (lds_load(lp + li) == kLiquid) continue;
-        int lx, ly, lz, x, y, z;
-        node(li, lx, ly, lz, x, y, z);
-        const bool s0 = starts_run(li, lx);
-#pragma unroll
-        for (int h = 0; h < L::nhalf; ++h) {
-            const int i = L::half[h];
-            if (L::ey[i] == 0 && L::ez[i] == 0) continue;  // along the row: the run
-            if (!local_link<Q>(lx, ly, lz, x, y, z, i, a)) continue;
-            const int lj = li + L::ex[i] + T::TX * (L::ey[i] + T::TY * L::ez[i]);
-            if (lds_load(lp + lj) == kLiquid) continue;
-            if (!s0 && !starts_run(lj, lx + L::ex[i])) continue;
-            lds_unite(lp, (uint32_t)li, (uint32_t)lj);
-        }
-    }
-    __syncthreads();
-    for (int li = threadIdx.x; li < NT; li += blockDim.x) {
-        if (lp[li] == kLiquid) continue;
-        int lx, ly, lz, x, y, z;
-        node(li, lx, ly, lz, x, y, z);
-        const uint32_t r = lds_root(lp, (uint32_t)li);
-        const int rx = x0 + (int)(r % T::TX), ry = y0 + (int)((r / T::TX) % T::TY);
-        const int rz = z0 + (int)(r / (T::TX * T::TY));
-        parent[idx3(x, y, z, a.nx, a.ny)] = (uint32_t)idx3(rx, ry, rz, a.nx, a.ny);
-    }
-}
-
-// The links the tiles could not see: those that leave a tile or wrap around the box.  As inside
-// the tiles, only links at which one end starts its run along x (the first gas node of a tile
-// row, or one whose left neighbour is liquid) are united: an x-link across a tile face always
-// ends at such a node, and two adjacent runs of different rows always share such a link.
-template <int Q>
-__global__ void k_union_cross(uint32_t* parent, FieldArgs a)
-{
-    using L = lat<Q>;
-    using T = UnionTile<Q>;
-    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < a.N;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        if (load_parent(parent, (uint32_t)n) == kLiquid) continue;
-        int x, y, z;
-        coords3(n, a.nx, a.ny, x, y, z);
-        const int lx = x % T::TX, ly = y % T::TY, lz = z % T::TZ;
-        const bool s0 = lx == 0 || load_parent(parent, (uint32_t)(n - 1)) == kLiquid;
-#pragma unroll
-        for (int h = 0; h < L::nhalf; ++h) {
-            const int i = L::half[h];
-            if (local_link<Q>(lx, ly, lz, x, y, z, i, a)) continue;
-            const int64_t m = shifted<Q>(x, y, z, i, +1, a);
-            if (m == n) continue;
-            if (load_parent(parent, (uint32_t)m) == kLiquid) continue;
-            if (!s0) {
-                const int mx = wrap_once(x + L::ex[i], a.nx);
-                if (mx % T::TX != 0 && load_parent(parent, (uint32_t)(m - 1)) != kLiquid) continue;
-            }
-            unite(parent, (uint32_t)n, (uint32_t)m);
-        }
     }
 }
 
@@ -1185,68 +870,7 @@ hipError_t launch_totals(int q, int storage, const void* f, double* partials, do
                                    partials, a));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_totals_final, dim3(1), dim3(64), 0, st, partials, nb, out_d,
-                       (double)a.N * a.rho_ref_d);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_from_rho(int q, int storage, const void* f, uint32_t* parent,
-                                const FieldArgs& a, hipStream_t st)
-{
-    SC_DISPATCH(q, storage,
-                hipLaunchKernelGGL((k_mask_rho<QQ, SS>), grid_for(a.N), dim3(256), 0, st,
-                                   (const SS*)f, parent, a));
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* parent,
-                              double* partials, double* out_d, const FieldArgs& a, hipStream_t st)
-{
-    const int nb = totals_blocks(a.N);
-    SC_DISPATCH(q, storage,
-                hipLaunchKernelGGL((k_mask_totals<QQ, SS>), dim3(nb), dim3(256), 0, st,
-                                   (const SS*)f, parent, partials, a));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_totals_final, dim3(1), dim3(64), 0, st, partials, nb, out_d,
-                       (double)a.N * a.rho_ref_d);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* parent, int64_t N,
-                                  hipStream_t st)
-{
-    hipLaunchKernelGGL(k_mask_bytes, grid_for(N), dim3(256), 0, st, mask_d, parent, N);
-    return hipGetLastError();
-}
-
-template <int Q>
-static hipError_t launch_union_tiled(uint32_t* parent, uint32_t* zero_counter, const FieldArgs& a,
-                                     hipStream_t st)
-{
-    using T = UnionTile<Q>;
-    const int64_t tiles = (int64_t)((a.nx + T::TX - 1) / T::TX) * ((a.ny + T::TY - 1) / T::TY) *
-                          ((a.nz + T::TZ - 1) / T::TZ);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_union_local<Q>), dim3((unsigned)tiles), dim3(T::THREADS), 0, st,
-                       parent, zero_counter, a);
-    hipLaunchKernelGGL((k_union_cross<Q>), grid_for(a.N), dim3(256), 0, st, parent, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_union(int q, uint32_t* parent, uint32_t* zero_counter, const FieldArgs& a,
-                        hipStream_t st)
-{
-    if (q == 9) return launch_union_tiled<9>(parent, zero_counter, a, st);
-    if (q == 19) return launch_union_tiled<19>(parent, zero_counter, a, st);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_flatten(uint32_t* parent, uint32_t* labels, uint32_t* ncomp_d, int64_t N,
-                          hipStream_t st)
-{
-    hipLaunchKernelGGL(k_flatten, grid_for(N), dim3(256), 0, st, parent, labels, ncomp_d, N);
-    return hipGetLastError();
+    return launch_totals_final(partials, nb, out_d, (double)a.N * a.rho_ref_d, st);
 }
 
 hipError_t launch_gather_labels(const uint32_t* labels, const int64_t* nodes_d, uint32_t* out_d,
