@@ -59,6 +59,7 @@ struct sc_sim {
     void* f[2] = {nullptr, nullptr};
     int cur = 0;
     StepShape shape{};
+    MultiShape multi{1, 0, 0, 0};
     int64_t t = 0;
     int latched = 0;
 
@@ -315,7 +316,7 @@ StepShape default_shape(const sc_params& p)
 // Estimated time (us) of one D3Q19 step launch with this tile: rounds of resident blocks, each
 // marching its planes (and the prologue's) at the slowest of the plane latency, the memory
 // traffic and the arithmetic of a round's blocks.  The constants were fitted to the measured
-// times of 1,800 shapes on 25 boxes of 60 x 60 x 60 to 300 x 200 x 100 and 256^3, one and two
+// times of some 8,000 shapes on 25 boxes of 48^3 to 300 x 200 x 100 and 256^3, one and two
 // components, FP32 and 16-bit storage: the shape it picks is on average 1% (one component up to
 // 5%) slower than the fastest of those measured.
 double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
@@ -337,7 +338,8 @@ double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
     // beyond what the last-level cache holds, stores that bypass L2 pay; rows that start and end
     // inside a cache line cost the shared line again, for such stores most of all
     const bool resident = (double)p.nx * p.ny * p.nz * 2 * pops * es < 230e6;
-    const bool aligned = std::fmod(p.nx * es, 128.0) == 0.0 && std::fmod(tw * es, 128.0) == 0.0;
+    const int bytes_el = (int)storage_bytes(p.storage);
+    const bool aligned = (int64_t)p.nx * bytes_el % 128 == 0 && tw * bytes_el % 128 == 0;
     const double edge_ld = aligned ? 0.0 : 0.65 * 128, edge_st = aligned ? 0.0 : (nt ? 1.8 : 1.0) * 128;
     const double runs = tw == p.nx ? 1 : th, run = tw == p.nx ? tw * th * es : tw * es;
     auto plane = [&](int64_t blocks) {
@@ -356,7 +358,7 @@ double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
     return t;
 }
 
-// Tile of an untuned D3Q19 box: the box's row cut into equal parts, as many rows as the block
+// Tile of an untuned box.  D3Q19: the box's row cut into equal parts, as many rows as the block
 // then has threads for, cut evenly too, and equal chunks of planes; the cheapest by the estimate
 // above.  A power-of-two tile leaves lanes without a node (203 nodes in 256 lanes) and its last
 // round of blocks half empty: bf16 203 x 150 x 121 104 us with the fixed 32 x 8 x 16 tile, 95 us
@@ -364,6 +366,14 @@ double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
 StepShape fitted_shape(const sc_params& p, int compute)
 {
     StepShape best = default_shape(p);
+    if (p.lattice == SC_D2Q9 && p.components == 1) {
+        // single steps in 2D (the others go several to a launch): a small box is a few latencies,
+        // one row a block; 128^2 7.2 -> 4.4 us, 308 x 927 9.6 -> 8.4, 1024^2 18.1 as before
+        const int64_t N = (int64_t)p.nx * p.ny;
+        if (N <= 1 << 17) return StepShape{p.nx <= 64 ? 64 : 128, 1, 1, 3};
+        if (N < 900000) return StepShape{256, 1, 2, 3};
+        return best;
+    }
     if (p.lattice != SC_D3Q19) return best;
     const bool mix = p.components == 2;
     const size_t es = compute == SC_COMPUTE_F64 ? sizeof(double) : sizeof(float);
@@ -377,11 +387,10 @@ StepShape fitted_shape(const sc_params& p, int compute)
             if (tw > b / 3 || tw == last_tw) continue;
             last_tw = tw;
             const int rows = b / tw, gy = (p.ny + rows - 1) / rows, th = (p.ny + gy - 1) / gy;
-            int last_tz = 0;
-            for (int gz = 1; gz <= p.nz; ++gz) {
-                const int tz = (p.nz + gz - 1) / gz;
-                if (tz == last_tz || tz > 512) continue;
-                last_tz = tz;
+            // every distinct number of planes ceil(nz / gz), gz = 1, 2, ..
+            for (int tz = p.nz, gz = 1; tz > 0; gz = tz > 1 ? (p.nz + tz - 2) / (tz - 1) : p.nz + 1,
+                     tz = gz <= p.nz ? (p.nz + gz - 1) / gz : 0) {
+                if (tz > 512) continue;
                 for (int v : {1, 3}) {
                     const StepShape s{tw, th, tz, mix ? v + (v == 1 ? 3 : 2) : v};
                     if (!(mix ? mix3d_tile_fits(s, es) : step3d_tile_fits(s))) continue;
@@ -394,6 +403,59 @@ StepShape fitted_shape(const sc_params& p, int compute)
             }
         }
     }
+    return best;
+}
+
+// Estimated time (us) of one k_step2d_multi launch, for a step: the launch, then the longer of the
+// arithmetic on the busiest CU and the latencies of its rounds of blocks, and part of the shorter.
+// Cycles a wave: 91 to load and place a node, 150 to pull it again and form its psi, 226 to
+// collide it (FP32 arithmetic 0.62 of that).  Fitted to the times of some thousand shapes on nine
+// boxes of 64 x 86 to 2048^2; the shape it picks is a few percent from the fastest measured.
+double multi_cost(const sc_params& p, int compute, const MultiShape& m)
+{
+    const bool f64 = compute == SC_COMPUTE_F64;
+    const int W = m.tile_x + 4 * m.T - 2, H = m.tile_y + 4 * m.T - 2, waves = m.threads / 64;
+    const int npt = (W * H + m.threads - 1) / m.threads;
+    double work = npt * waves * 91.0;
+    for (int s = 1; s <= m.T; ++s) {
+        const int far = 2 * (m.T - s);
+        if (s > 1) work += (m.tile_y + 2 * (far + 1)) * (double)W / 64 * 150.0;
+        work += (m.tile_y + 2 * far) * (double)W / 64 * 226.0;
+    }
+    const size_t lds = (size_t)W * H * (9 * storage_bytes(p.storage) + (f64 ? 8 : 4));
+    const int res = std::max(1, std::min(16 / waves, (int)((size_t)160 * 1024 / lds)));
+    const int64_t nb = (int64_t)((p.nx + m.tile_x - 1) / m.tile_x) *
+                       ((p.ny + m.tile_y - 1) / m.tile_y);
+    const double per_cu = nb > 256 * (int64_t)res ? nb / 256.0 : (double)((nb + 255) / 256);
+    double valu = per_cu * work / 2400.0 * (f64 ? 1.0 : 0.62);
+    if (npt == 3) valu *= 1.15;  // spills
+    const double lat = (double)((nb + 256 * res - 1) / (256 * res)) * (0.3 + 0.74 * m.T);
+    return (3.4 + std::max(lat, valu) + 0.42 * std::min(lat, valu)) / m.T;
+}
+
+// Steps a launch and tile of an untuned one-component D2Q9 box, used where steps follow one another
+// with no source, barrier fix-up or test pass between them; the cheapest by the estimate above.
+// Microseconds a step, FP64 arithmetic, one step a launch and several: 128^2 4.4 -> 2.1 (T = 4),
+// 200 x 160 4.3 -> 2.2, 308 x 927 8.3 -> 5.6 (T = 2), 1024^2 18.1 -> 15.4, 2048^2 67.1 -> 55.7.
+MultiShape multi_shape(const sc_params& p, int compute)
+{
+    MultiShape best{1, 0, 0, 0};
+    if (p.lattice != SC_D2Q9 || p.components != 1) return best;
+    double cost = 1e300;
+    for (int T = 2; T <= 5; ++T)
+        for (int x = 4; x <= 64; x += 4)
+            for (int y = 4; y <= 64; y += 4)
+                for (int npt = 1; npt <= 3; ++npt) {
+                    const int nodes = (x + 4 * T - 2) * (y + 4 * T - 2);
+                    const int threads = ((nodes + npt - 1) / npt + 63) & ~63;
+                    const MultiShape m{T, x, y, threads};
+                    if (!step2d_multi_fits(m, p.storage, compute)) continue;
+                    const double c = multi_cost(p, compute, m);
+                    if (c < cost) {
+                        cost = c;
+                        best = m;
+                    }
+                }
     return best;
 }
 
@@ -1311,6 +1373,7 @@ int sc_create(const sc_params* p, sc_sim** out)
     s->shape = shape_from_params(*p);
     if (!(p->tile_x || p->tile_y || p->tile_z || p->step_variant)) {
         s->shape = fitted_shape(*p, s->compute);
+        s->multi = multi_shape(*p, s->compute);
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(tune_key(*p, s->compute));
         if (it != g_tuned.end()) s->shape = it->second;
@@ -1466,6 +1529,37 @@ static int launch_one_step(sc_sim* s, const StepArgs& a, int c)
     return SC_OK;
 }
 
+// Steps from now on that only launch the step, at most `left`: up to the next test pass or step of
+// the source, none with a barrier frontier.
+static int quiet_steps(const sc_sim* s, int left)
+{
+    if (s->p.barrier && s->frontier_count > 0) return 0;
+    const int K = s->p.test_every;
+    int m = K > 0 ? std::min<int64_t>(left, K - s->t % K) : left;
+    m = std::min(m, s->chunk_len - s->chunk_pos);
+    if (s->list_count > 0)
+        for (int k = 0; k < m; ++k)
+            if (s->step_active[(size_t)(s->chunk_pos + k)]) return k;
+    return m;
+}
+
+// Launches m quiet steps from buffer c on, several to a launch where the box has a shape for it,
+// and returns the buffer that holds the result.
+static int launch_quiet(sc_sim* s, const StepArgs& a, int m, int c, int* c_out)
+{
+    const int n = (m + s->multi.T - 1) / s->multi.T;  // launches, of even numbers of steps
+    for (int k = 0; k < n; ++k, c ^= 1) {
+        const int T = (int)((int64_t)m * (k + 1) / n - (int64_t)m * k / n);
+        if (T == 1)
+            TRY(launch_one_step(s, a, c));
+        else
+            HIPX(launch_step2d_multi(s->p.storage, s->compute, s->f[c], s->f[c ^ 1], a, s->multi,
+                                     T, s->stream));
+    }
+    *c_out = c;
+    return SC_OK;
+}
+
 // A K-step block runs as one graph when its launches are the same every block: a box small
 // enough that launching dominates (N <= 2^22 nodes), no barrier fix-up, and no source launch in
 // the block.  The block starts right after a test pass (t % K == 0, schedule position 0).
@@ -1487,7 +1581,7 @@ static int run_block_graph(sc_sim* s, const StepArgs& a, int K)
 {
     const int c0 = s->cur;
     std::vector<char> key(sizeof(StepArgs) + sizeof(Step2cArgs) + sizeof(StepShape) +
-                          6 * sizeof(void*) + sizeof(int));
+                          sizeof(MultiShape) + 6 * sizeof(void*) + sizeof(int));
     {
         char* k = key.data();
         const Step2cArgs a2 = step2c_args(s);
@@ -1496,6 +1590,7 @@ static int run_block_graph(sc_sim* s, const StepArgs& a, int K)
         std::memcpy(k, &a, sizeof(a)); k += sizeof(a);
         std::memcpy(k, &a2, sizeof(a2)); k += sizeof(a2);
         std::memcpy(k, &s->shape, sizeof(s->shape)); k += sizeof(s->shape);
+        std::memcpy(k, &s->multi, sizeof(s->multi)); k += sizeof(s->multi);
         std::memcpy(k, ptrs, sizeof(ptrs)); k += sizeof(ptrs);
         std::memcpy(k, &K, sizeof(K));
     }
@@ -1505,9 +1600,8 @@ static int run_block_graph(sc_sim* s, const StepArgs& a, int K)
             s->graph_exec[c0] = nullptr;
         }
         HIPX(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-        int rc = SC_OK;
         int c = c0;
-        for (int k = 0; k < K && rc == SC_OK; ++k, c ^= 1) rc = launch_one_step(s, a, c);
+        const int rc = launch_quiet(s, a, K, c0, &c);
         hipGraph_t g = nullptr;
         const hipError_t e = hipStreamEndCapture(s->stream, &g);
         if (rc != SC_OK) {
@@ -1528,6 +1622,7 @@ static int run_block_graph(sc_sim* s, const StepArgs& a, int K)
     if (s->prof) s->recs.back().launches = K;
     HIPX(hipGraphLaunch(s->graph_exec[c0], s->stream));
     TRY(prof_end(s, pe));
+    s->cur = c0 ^ (((K + s->multi.T - 1) / s->multi.T) & 1);
     return SC_OK;
 }
 
@@ -1580,6 +1675,18 @@ int sc_step_graphs(sc_sim* s, int32_t enable)
     return SC_OK;
 }
 
+// Bookkeeping of m steps inside the current chunk: budgets, schedule position, time.
+static void count_steps(sc_sim* s, int m)
+{
+    s->chunk_pos += m;
+    s->t += m;
+    if (!s->rem.empty() && s->chunk_len > 0) {
+        const size_t n = s->rem.size();
+        std::copy(s->rem_host.begin() + (s->chunk_pos - 1) * n,
+                  s->rem_host.begin() + s->chunk_pos * n, s->rem.begin());
+    }
+}
+
 int sc_step(sc_sim* s, int32_t nsteps)
 {
     TRY(check_usable(s));
@@ -1592,16 +1699,7 @@ int sc_step(sc_sim* s, int32_t nsteps)
             // a whole K-step block without source launches: one graph, then the bookkeeping
             // the per-step loop below does, and the test pass
             TRY(run_block_graph(s, a, K));
-            if (K & 1) s->cur ^= 1;
-            for (int k = 0; k < K; ++k) {
-                if (!s->rem.empty() && s->chunk_len > 0) {
-                    const size_t n = s->rem.size();
-                    std::copy(s->rem_host.begin() + s->chunk_pos * n,
-                              s->rem_host.begin() + (s->chunk_pos + 1) * n, s->rem.begin());
-                }
-                s->chunk_pos++;
-                s->t += 1;
-            }
+            count_steps(s, K);
             it += K - 1;
             // the pass's device part as a graph too, unless a ledger is to be read back
             hipEvent_t pe;
@@ -1617,6 +1715,17 @@ int sc_step(sc_sim* s, int32_t nsteps)
             continue;
         }
         hipEvent_t pe;
+        const int m = s->multi.T > 1 ? quiet_steps(s, nsteps - it) : 1;
+        if (m > 1) {
+            TRY(prof_begin(s, SC_KERNEL_STEP, &pe));
+            if (s->prof) s->recs.back().launches = m;
+            TRY(launch_quiet(s, a, m, s->cur, &s->cur));
+            TRY(prof_end(s, pe));
+            count_steps(s, m);
+            it += m - 1;
+            if (K > 0 && s->t % K == 0) TRY(test_pass(s, true));
+            continue;
+        }
         TRY(prof_begin(s, SC_KERNEL_STEP, &pe));
         TRY(launch_one_step(s, a, s->cur));
         TRY(prof_end(s, pe));
@@ -1637,13 +1746,7 @@ int sc_step(sc_sim* s, int32_t nsteps)
                                ledger_view(s, s->chunk_pos), s->t, fa, s->stream));
             TRY(prof_end(s, pe));
         }
-        if (!s->rem.empty() && s->chunk_len > 0) {
-            const size_t n = s->rem.size();
-            std::copy(s->rem_host.begin() + s->chunk_pos * n,
-                      s->rem_host.begin() + (s->chunk_pos + 1) * n, s->rem.begin());
-        }
-        s->chunk_pos++;
-        s->t += 1;
+        count_steps(s, 1);
         if (K > 0 && s->t % K == 0) TRY(test_pass(s, true));
     }
     HIPX(hipStreamSynchronize(s->stream));

@@ -36,6 +36,12 @@ struct StepShape {
     int variant;                 // 1: plain marching kernel, 2: software-pipelined (3D only)
 };
 
+// Several D2Q9 steps in one launch: up to T steps on tile_x x tile_y tiles of `threads` threads
+// (T = 1: the marching kernel of the shape above).
+struct MultiShape {
+    int T, tile_x, tile_y, threads;
+};
+
 // storage codes as in sc.h: 0 F32, 1 F16, 2 BF16
 size_t storage_bytes(int storage);
 
@@ -45,6 +51,9 @@ bool step3d_tile_fits(const StepShape& s);
 bool step_combo_supported(int storage, int compute);
 hipError_t launch_step(int q, int storage, int compute, const void* src, void* dst,
                        const StepArgs& a, const StepShape& s, hipStream_t st);
+bool step2d_multi_fits(const MultiShape& m, int storage, int compute);
+hipError_t launch_step2d_multi(int storage, int compute, const void* src, void* dst,
+                               const StepArgs& a, const MultiShape& m, int T, hipStream_t st);
 // --- two-component kernels (sc_step2c.hip) ---------------------------------------------------
 // Two-component step (FP32 unshifted storage, FP64 arithmetic): one fused marching kernel per
 // step (both densities over the tile and its ring in LDS, the cross forces, the common velocity,

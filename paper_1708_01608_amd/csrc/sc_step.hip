@@ -129,6 +129,95 @@ __global__ void __launch_bounds__(TX) k_step2d(const S* __restrict__ src, S* __r
 }
 
 // ------------------------------------------------------------------------------------------
+// D2Q9, several time steps in one launch: a block owns a tw x th tile and carries it T steps, the
+// populations between the steps in LDS (rounded to the storage type, as a store would).  Step s
+// collides the nodes within 2 (T - s) of the tile, which needs the psi, and so the pulled
+// populations, of one node more, so the block loads the tile and a rim of 2 T - 1 nodes; what
+// lies beyond the box is the periodic image.  Slot k of thread t is node t + k blockDim of that
+// region at every step.
+// A 2D box rarely fills HBM's queue: a step of 128^2 is a launch and two memory latencies, one of
+// 1024^2 streams 75 MB through the last-level cache at the pace of its three dependent row loads.
+// T steps a launch pay the launch and the latency once and move the populations once, for the
+// rim's arithmetic (figures at multi_shape, which picks T and the tile).
+// ------------------------------------------------------------------------------------------
+template <typename S, typename A, bool EXT, int NPT>
+__global__ void __launch_bounds__(512, 4) k_step2d_multi(const S* __restrict__ src,
+                                                         S* __restrict__ dst, StepArgs a,
+                                                         StepGrid grid, int T)
+{
+    using L = lat<9>;
+    extern __shared__ double ring_lds[];
+    const Coef<A> c = coef_of(a, A());
+    const int nx = a.nx, ny = a.ny;
+    const int64_t N = a.N;
+    const int lb = logical_block(grid);
+    const int rim = 2 * T - 1;
+    const int x0 = (lb % grid.gx) * grid.tw - rim, y0 = (lb / grid.gx) * grid.th - rim;
+    const int W = grid.tw + 2 * rim, n0 = W * (grid.th + 2 * rim);
+    A* const psi = reinterpret_cast<A*>(ring_lds);     // [n0]
+    S* const pop = reinterpret_cast<S*>(psi + n0);     // [9][n0]
+
+    float g[NPT][9];
+    A d[NPT];
+    int dist[NPT];  // distance from the tile (beyond the region: never active)
+    uint32_t at[NPT];
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+        const int j = (int)threadIdx.x + k * (int)blockDim.x;
+        const int jy = j / W, jx = j - jy * W;
+        dist[k] = j < n0 ? max(max(rim - jx, jx - rim - grid.tw + 1),
+                               max(max(rim - jy, jy - rim - grid.th + 1), 0))
+                         : 1 << 20;
+        if (j >= n0) continue;
+        int x = (x0 + jx) % nx, y = (y0 + jy) % ny;
+        if (x < 0) x += nx;
+        if (y < 0) y += ny;
+        at[k] = (uint32_t)x + (uint32_t)nx * (uint32_t)y;
+        // a node of the tile beyond the box is another tile's: computed, not stored
+        if (dist[k] == 0 && (x0 + jx >= nx || y0 + jy >= ny)) at[k] = ~0u;
+        pull_node<9>(src, N, nx, ny, x, wrap_once(x - 1, nx), wrap_once(x + 1, nx), y,
+                     wrap_once(y - 1, ny), wrap_once(y + 1, ny), 0, 0, 0, g[k]);
+    }
+    for (int s = 1; s <= T; ++s) {
+        const int far = 2 * (T - s);  // nodes within `far` of the tile collide
+        // (addresses are formed from the thread index where they are used: hoisted, they spill)
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int j = opaque((int)threadIdx.x) + k * (int)blockDim.x;
+            __builtin_amdgcn_sched_barrier(0);
+            if (dist[k] > far + 1) continue;
+            if (s > 1) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) g[k][i] = load_f(pop[i * n0 + j - L::ex[i] - W * L::ey[i]]);
+            }
+            d[k] = sum_dev<9, A>(g[k]);
+            psi[j] = psi_f(c.rho_ref + d[k]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int j = opaque((int)threadIdx.x) + k * (int)blockDim.x;
+            // one node's collision at a time: interleaved, they spill
+            __builtin_amdgcn_sched_barrier(0);
+            if (dist[k] > far) continue;
+            A fx, fy, fz;
+            interaction_sum<9, A>([&](int i) { return psi[j + L::ex[i] + W * L::ey[i]]; }, fx, fy, fz);
+            const A gp = -c.G * psi[j];
+            S out[9];
+            collide_store<9, A, S, false, EXT>(out, 1, 0u, g[k], d[k], gp * fx, gp * fy, (A)0, c);
+            if (s < T) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) pop[i * n0 + j] = out[i];
+            } else if (at[k] != ~0u) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) dst[(int64_t)i * N + at[k]] = out[i];
+            }
+        }
+        if (s < T) __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // D3Q19: a block owns a tw x th tile of an x-y plane (any tw th <= B) and marches `planes` planes
 // in z.  The tile is a launch argument: the host fits it to the box, so that no lane idles where a
 // power of two would overhang it.
@@ -625,6 +714,69 @@ static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, con
 #undef SC_L2
 #undef SC_L3P
 #undef SC_L3
+    return hipErrorInvalidValue;
+}
+
+// Region of a tile carried T steps, and what k_step2d_multi needs of it: at most three nodes a
+// thread of a block of up to 512, its LDS.
+static int multi_nodes(int tw, int th, int T) { return (tw + 4 * T - 2) * (th + 4 * T - 2); }
+static size_t multi_lds(int tw, int th, int T, int storage, int compute)
+{
+    return (size_t)multi_nodes(tw, th, T) *
+           (9 * storage_bytes(storage) + (compute == SC_COMPUTE_F64 ? 8 : 4));
+}
+bool step2d_multi_fits(const MultiShape& m, int storage, int compute)
+{
+    return m.T >= 1 && m.tile_x >= 1 && m.tile_y >= 1 && m.threads >= 64 && m.threads <= 512 &&
+           m.threads % 64 == 0 && multi_nodes(m.tile_x, m.tile_y, m.T) <= 3 * m.threads &&
+           multi_lds(m.tile_x, m.tile_y, m.T, storage, compute) <= (size_t)160 * 1024;
+}
+
+template <typename S, typename A>
+static hipError_t multi_typed(const S* src, S* dst, const StepArgs& a, const MultiShape& m, int T,
+                              size_t lds, hipStream_t st)
+{
+    StepGrid g;
+    g.gx = (a.nx + m.tile_x - 1) / m.tile_x;
+    g.gy = (a.ny + m.tile_y - 1) / m.tile_y;
+    g.gz = 1;
+    g.tw = m.tile_x;
+    g.th = m.tile_y;
+    const int per = (multi_nodes(m.tile_x, m.tile_y, T) + m.threads - 1) / m.threads;
+    const dim3 grid(g.gx * g.gy), block(m.threads);
+#define SC_MU(NPT)                                                                               \
+    if (per <= NPT) {                                                                            \
+        if (a.grav)                                                                              \
+            hipLaunchKernelGGL((k_step2d_multi<S, A, true, NPT>), grid, block, lds, st, src,     \
+                               dst, a, g, T);                                                    \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_step2d_multi<S, A, false, NPT>), grid, block, lds, st, src,    \
+                               dst, a, g, T);                                                    \
+        return hipGetLastError();                                                                \
+    }
+    SC_MU(1) SC_MU(2) SC_MU(3)
+#undef SC_MU
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_step2d_multi(int storage, int compute, const void* src, void* dst,
+                               const StepArgs& a, const MultiShape& m, int T, hipStream_t st)
+{
+    if (T < 1 || T > m.T || !step2d_multi_fits(m, storage, compute)) return hipErrorInvalidValue;
+    const size_t lds = multi_lds(m.tile_x, m.tile_y, T, storage, compute);
+    if (compute == SC_COMPUTE_F64)
+        return storage == SC_STORE_F32
+                   ? multi_typed<float, double>((const float*)src, (float*)dst, a, m, T, lds, st)
+                   : hipErrorInvalidValue;
+    switch (storage) {
+        case SC_STORE_F32:
+            return multi_typed<float, float>((const float*)src, (float*)dst, a, m, T, lds, st);
+        case SC_STORE_F16:
+            return multi_typed<_Float16, float>((const _Float16*)src, (_Float16*)dst, a, m, T, lds,
+                                                st);
+        case SC_STORE_BF16:
+            return multi_typed<__bf16, float>((const __bf16*)src, (__bf16*)dst, a, m, T, lds, st);
+    }
     return hipErrorInvalidValue;
 }
 
