@@ -125,6 +125,7 @@ struct sc_sim {
     char* stage = nullptr;      // host address
     char* stage_dev = nullptr;  // the same memory as the device addresses it
     int stage_n = -1;
+    hipEvent_t pass_done = nullptr;  // behind a pass that steps are already queued after
 
     // K-step blocks of a launch-bound box as HIP graphs: one executable per starting buffer
     // parity, valid while the captured arguments (graph_key) stay the same
@@ -937,8 +938,14 @@ int pass_enqueue(sc_sim* s, bool with_criterion)
     o.dst_sums = sd.sums; o.dst_owed = sd.owed; o.dst_pairs = sd.pairs; o.dst_ab = sd.ab;
     o.dst_res = sd.res;
 
+    // a small box: the mask words and everything behind them, two launches
+    const bool small = n > 0 && small_pass_fits(fa);
     // 1. gas mask, labels and FP64 totals
-    TRY(label_current(s, (uint32_t*)s->labels.p, nullptr, nullptr, st.tot, true, false));
+    if (small)
+        HIPX(launch_mask_words(s->q, s->p.storage, s->f[s->cur], (uint32_t*)s->parent.p,
+                               (double*)s->partials.p, fa, s->stream));
+    else
+        TRY(label_current(s, (uint32_t*)s->labels.p, nullptr, nullptr, st.tot, true, false));
     o.tot = (const double*)s->small.p;
     if (s->two) {
         TRY(gas_totals_queue(s));
@@ -953,10 +960,13 @@ int pass_enqueue(sc_sim* s, bool with_criterion)
     if (n > 0) {
         t = bubble_tab_view(s->btab.p, n);
         const BubbleTab prev = bubble_tab_view(s->btab.p, s->btab_n);
-        HIPX(launch_bubble_table((const uint32_t*)s->labels.p, (const int64_t*)s->nodes.p, n,
-                                 prev, t, (int32_t*)s->slots.p, fa, s->stream));
-        HIPX(launch_stats((const uint32_t*)s->labels.p, (const int32_t*)s->slots.p, t.anchors,
-                          t.count, t.sums, fa, s->stream));
+        if (!small) {
+            HIPX(launch_bubble_table((const uint32_t*)s->labels.p, (const int64_t*)s->nodes.p, n,
+                                     prev, t, (int32_t*)s->slots.p, fa, s->stream));
+            HIPX(launch_stats((const uint32_t*)s->labels.p, (uint32_t*)s->parent.p,
+                              (const int32_t*)s->slots.p, t.anchors, t.count, t.sums, fa,
+                              s->stream));
+        }
         if (with_criterion && n >= 2) {
             do_pairs = true;
             pair_cap = std::max(kStagePairs, s->pair_cap);
@@ -975,6 +985,26 @@ int pass_enqueue(sc_sim* s, bool with_criterion)
     o.owed = (const double*)s->ledger.p;
     o.ledger_nb = s->ledger_nb;
     // the merge groups are read where the host staged them (pinned memory)
+    if (small) {
+        SmallPass sp;
+        sp.nuc_node = (const int64_t*)s->nodes.p;
+        sp.n = n;
+        sp.prev = bubble_tab_view(s->btab.p, s->btab_n);
+        sp.tab = t;
+        sp.slot_of_root = (int32_t*)s->slots.p;
+        sp.group = sd.group;
+        sp.film_max = s->p.film_max;
+        sp.cap = pair_cap;
+        sp.do_pairs = do_pairs ? 1 : 0;
+        sp.pairs = (MergePair*)s->pair_buf.p;
+        sp.ab = (int32_t*)s->pair_ab.p;
+        sp.res = (MergeResult*)s->res_buf.p;
+        sp.out = o;
+        HIPX(launch_pass_small(s->q, s->p.storage, s->f[s->cur], (uint32_t*)s->parent.p,
+                               (uint32_t*)s->labels.p, (const double*)s->partials.p,
+                               (double*)s->small.p, sp, fa, s->stream));
+        return SC_OK;
+    }
     HIPX(launch_pass_tail(s->q, s->p.storage, t, sd.group, s->p.film_max,
                           (MergePair*)s->pair_buf.p, (int32_t*)s->pair_ab.p,
                           (MergeResult*)s->res_buf.p, pair_cap, do_pairs ? 1 : 0, o,
@@ -982,7 +1012,8 @@ int pass_enqueue(sc_sim* s, bool with_criterion)
     return SC_OK;
 }
 
-int pass_finish(sc_sim* s, bool with_criterion)
+// `done`: an event recorded behind the pass, when work of later steps is already queued behind it.
+int pass_finish(sc_sim* s, bool with_criterion, hipEvent_t done = nullptr)
 {
 #pragma clang fp contract(off)
     const FieldArgs fa = field_args(s);
@@ -992,7 +1023,10 @@ int pass_finish(sc_sim* s, bool with_criterion)
     int pair_cap = (with_criterion && n >= 2) ? std::max(kStagePairs, s->pair_cap) : 0;
     const BubbleTab t = n > 0 ? bubble_tab_view(s->btab.p, n) : BubbleTab{};
     s->have_labels = true;
-    HIPX(hipStreamSynchronize(s->stream));
+    if (done)
+        HIPX(hipEventSynchronize(done));
+    else
+        HIPX(hipStreamSynchronize(s->stream));
 
     for (int b = 0; b < ledger_nb; ++b)
         if (st.owed[b] != 0.0) s->owed_nuc[(size_t)s->ledger_lead[b]] += st.owed[b];
@@ -1308,6 +1342,7 @@ void release(sc_sim* s)
         (void)hipEventDestroy(r.b);
     }
     for (auto e : s->pool) (void)hipEventDestroy(e);
+    if (s->pass_done) (void)hipEventDestroy(s->pass_done);
     for (auto& g : s->graph_exec)
         if (g) (void)hipGraphExecDestroy(g);
     for (auto& g : s->pass_exec)
@@ -1687,6 +1722,18 @@ static void count_steps(sc_sim* s, int m)
     }
 }
 
+// Whether the steps after a test pass are the same whatever it finds: no agent to feed, no barrier,
+// and so few nuclei that every pair is tested in the pass itself (more pairs than the buffers hold
+// are walked again on the populations of the pass).  The host's part of the pass, some 20 us of
+// waking, registry and launching, then runs beside them: 128^2 with a pass every 10 steps
+// 644 -> 484 us for 100 steps.
+static bool pass_leaves_steps(const sc_sim* s)
+{
+    const int64_t n = (int64_t)s->rad.size();
+    return s->rate == 0.0 && s->ledger_nb == 0 && !s->p.barrier && !s->prof &&
+           n * (n - 1) / 2 <= kStagePairs;
+}
+
 int sc_step(sc_sim* s, int32_t nsteps)
 {
     TRY(check_usable(s));
@@ -1694,11 +1741,13 @@ int sc_step(sc_sim* s, int32_t nsteps)
     const StepArgs a = step_args(s);
     const FieldArgs fa = field_args(s);
     const int K = s->p.test_every;
+    bool queued = false;  // the coming block's steps are already in the stream
     for (int it = 0; it < nsteps; ++it) {
-        if (block_graph_ok(s, K, nsteps - it)) {
+        if (queued || block_graph_ok(s, K, nsteps - it)) {
             // a whole K-step block without source launches: one graph, then the bookkeeping
             // the per-step loop below does, and the test pass
-            TRY(run_block_graph(s, a, K));
+            if (!queued) TRY(run_block_graph(s, a, K));
+            queued = false;
             count_steps(s, K);
             it += K - 1;
             // the pass's device part as a graph too, unless a ledger is to be read back
@@ -1709,8 +1758,18 @@ int sc_step(sc_sim* s, int32_t nsteps)
                 TRY(run_pass_graph(s));
             else
                 TRY(pass_enqueue(s, true));
-            const int rc = pass_finish(s, true);
+            // the next block's steps go behind the pass before the host waits for it, if nothing
+            // the pass finds can change them
+            if (nsteps - it - 1 >= K && pass_leaves_steps(s)) {
+                if (!s->pass_done)
+                    HIPX(hipEventCreateWithFlags(&s->pass_done, hipEventDisableTiming));
+                HIPX(hipEventRecord(s->pass_done, s->stream));
+                TRY(run_block_graph(s, a, K));
+                queued = true;
+            }
+            const int rc = pass_finish(s, true, queued ? s->pass_done : nullptr);
             TRY(prof_end(s, pe));
+            if (rc != SC_OK && queued) (void)hipStreamSynchronize(s->stream);
             TRY(rc);
             continue;
         }

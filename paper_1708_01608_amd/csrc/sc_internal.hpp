@@ -150,6 +150,9 @@ hipError_t launch_mask_from_rho(int q, int storage, const void* f, uint32_t* scr
                                 const FieldArgs& a, hipStream_t st);
 hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* scratch,
                               double* partials, double* out_d, const FieldArgs& a, hipStream_t st);
+// launch_mask_totals without the totals' final sum.
+hipError_t launch_mask_words(int q, int storage, const void* f, uint32_t* scratch,
+                             double* partials, const FieldArgs& a, hipStream_t st);
 hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* scratch, const FieldArgs& a,
                                   hipStream_t st);
 hipError_t launch_labels(int q, uint32_t* labels, uint32_t* scratch, uint32_t* ncomp_d,
@@ -160,10 +163,10 @@ hipError_t launch_gather_labels(const uint32_t* labels, const int64_t* nodes_d, 
                                 int n, int64_t N, hipStream_t st);
 hipError_t launch_set_slots(int32_t* slot_of_root, const uint32_t* labels_of_bubbles_d, int nb,
                             int clear, hipStream_t st);
-hipError_t launch_stats(const uint32_t* labels, const int32_t* slot_of_root,
-                        const int32_t* anchors_d /*[nb][3]*/, unsigned long long* count_d,
-                        unsigned long long* sums_d /*[nb][3]*/, const FieldArgs& a,
-                        hipStream_t st);
+// scratch: of the labelling that wrote these labels (its mask words).
+hipError_t launch_stats(const uint32_t* labels, uint32_t* scratch, const int32_t* slot_of_root,
+                        const int32_t* anchors_d, unsigned long long* count_d,
+                        unsigned long long* sums_d, const FieldArgs& a, hipStream_t st);
 // Fed gas nodes in node order; block_counts holds gas_list_scratch_words() words of scratch.
 int gas_list_scratch_words();
 hipError_t launch_gas_list(const uint32_t* labels, const int32_t* slot_of_root,
@@ -250,6 +253,25 @@ hipError_t launch_stage_out(const StageOut& o, hipStream_t st);
 
 // The tail of a test pass in one block: with do_pairs, the candidate pairs (as launch_pairs)
 // and their merge test; then the read-back (as launch_stage_out).
+// The pass of a small one-component box in one launch, behind launch_mask_words (its mask words and
+// the totals' partial sums): labels, totals, table, statistics, pairs, read-back.
+constexpr int kSmallParts = 128;  // blocks of the partial sums of 2^15 nodes
+struct SmallPass {
+    const int64_t* nuc_node;
+    int n;
+    BubbleTab prev, tab;
+    int32_t* slot_of_root;
+    const int32_t* group;
+    int film_max, cap, do_pairs;
+    MergePair* pairs;
+    int32_t* ab;
+    MergeResult* res;
+    StageOut out;
+};
+bool small_pass_fits(const FieldArgs& a);
+hipError_t launch_pass_small(int q, int storage, const void* f, uint32_t* scratch,
+                             uint32_t* labels, const double* partials, double* tot,
+                             const SmallPass& p, const FieldArgs& a, hipStream_t st);
 hipError_t launch_pass_tail(int q, int storage, const BubbleTab& t, const int32_t* group,
                             int film_max, MergePair* pairs, int32_t* ab, MergeResult* res,
                             int cap, int do_pairs, const StageOut& o, const void* f,

@@ -21,15 +21,12 @@
 
 #include "sc_device.hpp"
 #include "sc_internal.hpp"
+#include "sc_runs.hpp"
 #include "sc_stepcore.hpp"
 
 namespace sc {
 
 namespace {
-
-constexpr int kSeg = 64;
-
-__host__ __device__ __forceinline__ int segs_of(int nx) { return (nx + kSeg - 1) / kSeg; }
 
 template <int Q>
 struct LabelTile;
@@ -42,66 +39,6 @@ struct LabelTile<19> {
     static constexpr int RY = 16, RZ = 16;
 };
 constexpr int kTileWords = 256;
-
-// ---- bits of a word --------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t below(int p) { return p ? ~0ull >> (64 - p) : 0ull; }
-
-// First bit of the run of `w` that contains bit p.
-__device__ __forceinline__ int run_start(uint64_t w, int p)
-{
-    const uint64_t gap = ~w & below(p);
-    return gap ? 64 - __clzll((long long)gap) : 0;
-}
-
-// The run of `w` that starts at bit s, as a mask.
-__device__ __forceinline__ uint64_t run_at(uint64_t w, int s)
-{
-    const uint64_t t = ~(w >> s);
-    const int len = t ? __ffsll((long long)t) - 1 : 64;
-    return below(min(len, 64 - s)) << s;
-}
-
-// The scratch of a labelling: the words (one a segment, rows one after the other), then the parents.
-// A parent is kept as its entry times two plus the parity of its column, which names the node.
-struct Scratch {
-    uint64_t* words;
-    uint32_t* parent;
-    uint32_t half;  // parents a row
-};
-__host__ __device__ __forceinline__ Scratch scratch_of(uint32_t* p, const FieldArgs& a)
-{
-    const size_t words = (size_t)segs_of(a.nx) * a.ny * a.nz;
-    return Scratch{reinterpret_cast<uint64_t*>(p), p + 2 * words, (uint32_t)(a.nx + 1) / 2};
-}
-// Code of the run start at column x of row r, and the node of a code.
-__device__ __forceinline__ uint32_t code_of(uint32_t r, int x, uint32_t half)
-{
-    return 2 * (r * half + ((uint32_t)x >> 1)) + ((uint32_t)x & 1);
-}
-__device__ __forceinline__ uint32_t node_of_code(uint32_t c, uint32_t half, int nx)
-{
-    const uint32_t e = c >> 1, r = e / half;
-    return r * (uint32_t)nx + 2 * (e - r * half) + (c & 1);
-}
-
-// Segment `w` of the box: first node, width, row.
-struct Seg {
-    int64_t n;
-    uint32_t r;
-    int width, x0, y, z;
-};
-__device__ __forceinline__ Seg seg_of(int64_t w, const FieldArgs& a)
-{
-    const uint32_t segs = (uint32_t)segs_of(a.nx), r = (uint32_t)w / segs, s = (uint32_t)w - r * segs;
-    Seg g;
-    g.x0 = (int)s * kSeg;
-    g.width = min(kSeg, a.nx - g.x0);
-    g.r = r;
-    g.n = (int64_t)r * a.nx + g.x0;
-    g.z = (int)(r / (uint32_t)a.ny);
-    g.y = (int)(r - (uint32_t)g.z * (uint32_t)a.ny);
-    return g;
-}
 
 // ---- mask words ----------------------------------------------------------------------------------
 // A wave takes kMaskWords segments a turn, loads first.
@@ -231,40 +168,7 @@ __global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
     }
 }
 
-// ---- union-find over runs -------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t lds_load(const uint32_t* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Roots of a and b, followed together so that their loads overlap.  In LDS the walk halves its path:
-// a visited entry is relinked to its grandparent, an ancestor with a smaller index, so concurrent
-// unions stay correct.
-__device__ __forceinline__ uint32_t lds_root(uint32_t* lp, uint32_t x)
-{
-    while (true) {
-        const uint32_t p = lds_load(lp + x);
-        if (p == x) return x;
-        const uint32_t g = lds_load(lp + p);
-        if (g == p) return p;
-        __hip_atomic_store(lp + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        x = g;
-    }
-}
-
-__device__ void lds_unite(uint32_t* lp, uint32_t a, uint32_t b)
-{
-    while (true) {
-        a = lds_root(lp, a);
-        b = lds_root(lp, b);
-        if (a == b) return;
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(lp + b, a);
-        if (old == b) return;
-        b = old;
-    }
-}
-
+// ---- union-find over runs, in global memory ---------------------------------------------------
 // parent of a code (an agent-scope load: other blocks relink)
 __device__ __forceinline__ uint32_t load_parent(const uint32_t* parent, uint32_t c)
 {
@@ -290,43 +194,6 @@ __device__ void unite(uint32_t* parent, uint32_t a, uint32_t b)
     }
 }
 
-// Calls link(sa, sb) once for every pair of touching runs of two adjacent rows: sa, sb the first
-// bits of the runs of words A and B; `wide` rows touch diagonally too.
-template <typename F>
-__device__ __forceinline__ void touching_runs(uint64_t A, uint64_t B, bool wide, F link)
-{
-    const uint64_t reach = wide ? (A | A << 1 | A >> 1) : A;
-    if (!(reach & B)) return;
-    for (uint64_t left = A; left;) {
-        const int sa = __ffsll((long long)left) - 1;
-        const uint64_t run = run_at(A, sa);
-        left &= ~run;
-        uint64_t hit = B & (wide ? (run | run << 1 | run >> 1) : run);
-        while (hit) {
-            const int sb = run_start(B, __ffsll((long long)hit) - 1);
-            hit &= ~run_at(B, sb);
-            link(sa, sb);
-        }
-    }
-}
-
-// The rows after a row that its nodes link to (half of the lattice's directions, the other half
-// seen from there), and whether along x by one node as well as straight.
-template <int Q>
-struct RowLinks;
-template <>
-struct RowLinks<9> {
-    static constexpr int n = 1;
-    static constexpr int dy[1] = {1}, dz[1] = {0};
-    static constexpr bool wide[1] = {true};
-};
-template <>
-struct RowLinks<19> {
-    static constexpr int n = 4;
-    static constexpr int dy[4] = {1, 0, 1, 1}, dz[4] = {0, 1, 1, -1};
-    static constexpr bool wide[4] = {true, true, false, false};
-};
-
 // One word a thread; the index of a run in LDS is its word's index times 32 plus half its first
 // bit, which follows the global order, so a local root is the smallest node of its local set.
 // Bound by the latency of the LDS chains.
@@ -341,7 +208,7 @@ __global__ void __launch_bounds__(kTileWords) k_label_local(uint32_t* scratch,
     __shared__ uint32_t lp[kTileWords * (kSeg / 2)];
     // the component counter of the flatten that follows starts at zero
     if (zero_counter && blockIdx.x == 0 && threadIdx.x == 0) *zero_counter = 0u;
-    const Scratch sc = scratch_of(scratch, a);
+    const LabelScratch sc = scratch_of(scratch, a);
     const int segs = segs_of(a.nx), gy = (a.ny + T::RY - 1) / T::RY;
     const int b = blockIdx.x, t = threadIdx.x;
     const int seg = b % segs, y0 = ((b / segs) % gy) * T::RY, z0 = (b / (segs * gy)) * T::RZ;
@@ -392,7 +259,7 @@ __global__ void __launch_bounds__(256) k_label_cross(uint32_t* scratch, int64_t 
     using R = RowLinks<Q>;
     const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (w >= words) return;
-    const Scratch sc = scratch_of(scratch, a);
+    const LabelScratch sc = scratch_of(scratch, a);
     const uint64_t A = sc.words[w];
     if (!A) return;
     const Seg g = seg_of(w, a);
@@ -442,7 +309,7 @@ __global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ la
                                                        uint32_t* scratch, uint32_t* ncomp,
                                                        int64_t words, FieldArgs a)
 {
-    const Scratch sc = scratch_of(scratch, a);
+    const LabelScratch sc = scratch_of(scratch, a);
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) + 4 * (int)blockIdx.x);
     const uint32_t segs = (uint32_t)segs_of(a.nx);
@@ -620,6 +487,12 @@ hipError_t launch_mask_totals(int q, int storage, const void* f, uint32_t* scrat
     const hipError_t e = mask_rho_any<true>(q, storage, f, scratch, partials, a, st);
     if (e != hipSuccess) return e;
     return launch_totals_final(partials, totals_blocks(a.N), out_d, (double)a.N * a.rho_ref_d, st);
+}
+
+hipError_t launch_mask_words(int q, int storage, const void* f, uint32_t* scratch,
+                             double* partials, const FieldArgs& a, hipStream_t st)
+{
+    return mask_rho_any<true>(q, storage, f, scratch, partials, a, st);
 }
 
 hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* scratch, const FieldArgs& a,

@@ -7,6 +7,7 @@
 
 #include "sc_device.hpp"
 #include "sc_internal.hpp"
+#include "sc_runs.hpp"
 
 namespace sc {
 
@@ -174,37 +175,6 @@ __global__ void k_laplacian(const double* p, double* lap, FieldArgs a)
     }
 }
 
-// ---- wave-level aggregation of per-node atomics ------------------------------------------------
-// Per-node contributions to per-bubble counters arrive from many nodes of the same bubble at
-// once; one atomic per node onto a few hundred addresses serialises.  The lanes of a wave that
-// carry the same key (a bubble slot, >= 0) sum their values with a butterfly and one lane adds the
-// sum: one atomic per distinct key per wave.  Integer sums, so the result does not depend on the
-// grouping.  Every lane of the wave must call these (the loops below are wave-uniform).
-__device__ __forceinline__ long long wave_sum_i64(long long v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-template <int M, typename Flush>
-__device__ __forceinline__ void wave_add_by_key(int key, const long long (&v)[M], Flush flush)
-{
-    const int lane = (int)(threadIdx.x & 63);
-    unsigned long long pending = __ballot(key >= 0);
-    while (pending) {
-        const int leader = __ffsll(pending) - 1;
-        const int k = __shfl(key, leader, 64);
-        const bool mine = key == k;
-        const unsigned long long grp = __ballot(mine);
-        long long sum[M];
-#pragma unroll
-        for (int j = 0; j < M; ++j) sum[j] = wave_sum_i64(mine ? v[j] : 0ll);
-        if (lane == leader) flush(k, sum);
-        pending &= ~grp;
-    }
-}
-
 // ---- FP64 totals: wave64 shuffles -> LDS -> one partial per block -> fixed-order final sum ---
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -259,44 +229,21 @@ __global__ void k_set_slots(int32_t* slot_of_root, const uint32_t* labs, int nb,
     if (b < nb) slot_of_root[labs[b] - 1] = clear ? -1 : b;
 }
 
-__device__ __forceinline__ int64_t min_image_i(int64_t d, int n)
+// One mask word a thread, its runs at once: 256^3 with 1.45 M gas nodes in 200 bubbles 171 us with a
+// node a thread, whose 200,000 atomics met on 200 lines.
+__global__ void __launch_bounds__(256) k_stats(const uint32_t* __restrict__ labels,
+                                               const uint64_t* __restrict__ mask,
+                                               const int32_t* __restrict__ slot_of_root,
+                                               const int32_t* __restrict__ anchors,
+                                               unsigned long long* count,
+                                               unsigned long long* sums, int64_t words, FieldArgs a)
 {
-    const int64_t h = n / 2;
-    int64_t r = (d + h) % n;
-    if (r < 0) r += n;
-    return r - h;
-}
-
-__global__ void k_stats(const uint32_t* labels, const int32_t* slot_of_root, const int32_t* anchors,
-                        unsigned long long* count, unsigned long long* sums, FieldArgs a)
-{
-    // block-uniform trip count, so every lane of a wave reaches the aggregation
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t n0 = blockIdx.x * (int64_t)blockDim.x; n0 < a.N; n0 += stride) {
-        const int64_t n = n0 + threadIdx.x;
-        int b = -1;
-        long long v[4] = {0, 0, 0, 0};
-        if (n < a.N) {
-            const uint32_t L = labels[n];
-            if (L) b = slot_of_root[L - 1];
-            if (b >= 0) {
-                int x, y, z;
-                coords3(n, a.nx, a.ny, x, y, z);
-                v[0] = 1;
-                v[1] = min_image_i((int64_t)x - anchors[3 * b + 0], a.nx);
-                v[2] = min_image_i((int64_t)y - anchors[3 * b + 1], a.ny);
-                v[3] = min_image_i((int64_t)z - anchors[3 * b + 2], a.nz);
-            }
-        }
-        // two's-complement wrap-around makes unsigned adds exact signed sums
-        wave_add_by_key<4>(b, v, [&](int k, const long long* s) {
-            const size_t o = (size_t)k * kStatStride;
-            atomicAdd(count + o, (unsigned long long)s[0]);
-            atomicAdd(sums + o + 0, (unsigned long long)s[1]);
-            atomicAdd(sums + o + 1, (unsigned long long)s[2]);
-            atomicAdd(sums + o + 2, (unsigned long long)s[3]);
-        });
-    }
+    const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const uint64_t A = w < words ? mask[w] : 0ull;
+    if (!__ballot(A != 0ull)) return;
+    const Seg g = seg_of(w < words ? w : 0, a);
+    word_stats(A, g, anchors, count, sums, a,
+               [&](int s) { return slot_of_root[labels[g.n + s] - 1]; });
 }
 
 // Gas-node list of the fed bubbles, in node order, without a global atomic per node or per wave:
@@ -891,12 +838,15 @@ hipError_t launch_set_slots(int32_t* slot_of_root, const uint32_t* labs_d, int n
     return hipGetLastError();
 }
 
-hipError_t launch_stats(const uint32_t* labels, const int32_t* slot_of_root,
+hipError_t launch_stats(const uint32_t* labels, uint32_t* scratch, const int32_t* slot_of_root,
                         const int32_t* anchors_d, unsigned long long* count_d,
                         unsigned long long* sums_d, const FieldArgs& a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_stats, grid_for(a.N), dim3(256), 0, st, labels, slot_of_root, anchors_d,
-                       count_d, sums_d, a);
+    const int64_t words = (int64_t)segs_of(a.nx) * a.ny * a.nz, nb = (words + 255) / 256;
+    if (nb > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_stats, dim3((unsigned)nb), dim3(256), 0, st, labels,
+                       scratch_of(scratch, a).words, slot_of_root, anchors_d, count_d, sums_d,
+                       words, a);
     return hipGetLastError();
 }
 
@@ -991,10 +941,9 @@ BubbleTab bubble_tab_view(void* base, int n)
 // One block.  A bubble is a distinct nonzero label held by a nucleus node; its slot is the rank
 // of its label among them and its lead nucleus the smallest index holding it (both O(n^2 / 1024)
 // comparisons, a few microseconds for hundreds of nuclei).
-__global__ void __launch_bounds__(1024) k_bubble_table(const uint32_t* labels,
-                                                       const int64_t* nuc_node, int n, int64_t N,
-                                                       BubbleTab prev, BubbleTab t,
-                                                       int32_t* slot_of_root, int nx, int ny)
+__device__ void bubble_table_body(const uint32_t* labels, const int64_t* nuc_node, int n, int64_t N,
+                                  const BubbleTab& prev, const BubbleTab& t,
+                                  int32_t* slot_of_root, int nx, int ny)
 {
     __shared__ int nb;
     // the previous pass's bubbles leave the slot map first (prev: the same buffer laid out for
@@ -1040,6 +989,14 @@ __global__ void __launch_bounds__(1024) k_bubble_table(const uint32_t* labels,
         t.head[0] = nb;
         t.head[1] = 0;
     }
+}
+
+__global__ void __launch_bounds__(1024) k_bubble_table(const uint32_t* labels,
+                                                       const int64_t* nuc_node, int n, int64_t N,
+                                                       BubbleTab prev, BubbleTab t,
+                                                       int32_t* slot_of_root, int nx, int ny)
+{
+    bubble_table_body(labels, nuc_node, n, N, prev, t, slot_of_root, nx, ny);
 }
 
 hipError_t launch_bubble_table(const uint32_t* labels, const int64_t* nuc_node, int n,
@@ -1126,11 +1083,10 @@ hipError_t launch_pairs(const BubbleTab& t, const int32_t* group, int dim, int f
 // The tail of a test pass in one block: candidate pairs, their merge test (one wave per pair,
 // sixteen at a time) and the read-back into pinned host memory.
 template <int Q, typename S>
-__global__ void __launch_bounds__(1024) k_pass_tail(BubbleTab t, const int32_t* group, int dim,
-                                                    int film_max, MergePair* pairs, int32_t* ab,
-                                                    MergeResult* res, int cap, int do_pairs,
-                                                    StageOut o, const S* f,
-                                                    const uint32_t* labels, FieldArgs a)
+__device__ void pass_tail_body(const BubbleTab& t, const int32_t* group, int dim, int film_max,
+                               MergePair* pairs, int32_t* ab, MergeResult* res, int cap,
+                               int do_pairs, const StageOut& o, const S* f, const uint32_t* labels,
+                               const FieldArgs& a)
 {
     if (do_pairs) {
         find_pairs(t, group, dim, film_max, pairs, ab, cap, a.nx, a.ny, a.nz);
@@ -1144,6 +1100,156 @@ __global__ void __launch_bounds__(1024) k_pass_tail(BubbleTab t, const int32_t* 
         __syncthreads();
     }
     stage_out_body(o);
+}
+
+template <int Q, typename S>
+__global__ void __launch_bounds__(1024) k_pass_tail(BubbleTab t, const int32_t* group, int dim,
+                                                    int film_max, MergePair* pairs, int32_t* ab,
+                                                    MergeResult* res, int cap, int do_pairs,
+                                                    StageOut o, const S* f,
+                                                    const uint32_t* labels, FieldArgs a)
+{
+    pass_tail_body<Q, S>(t, group, dim, film_max, pairs, ab, res, cap, do_pairs, o, f, labels, a);
+}
+
+// The whole test pass of a small box behind its mask words, in one block: the totals' final sum,
+// the labels (union-find over the runs in LDS, every link of the box), the bubble table, the
+// statistics, the pairs and the read-back.  On such a box each of the seven kernels this replaces
+// is a launch and a latency or two: 128^2 with two bubbles 28 us of kernels and seven gaps.
+template <int Q, typename S>
+__global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
+                                                     uint32_t* __restrict__ labels,
+                                                     const double* __restrict__ partials, int nparts,
+                                                     double* tot, double base_mass, SmallPass p,
+                                                     const S* f, FieldArgs a)
+{
+    using R = RowLinks<Q>;
+    extern __shared__ uint64_t bits[];  // [words], then the parents: 32 a word at most
+    __shared__ double part[4 * kSmallParts];
+    const int segs = segs_of(a.nx), words = segs * a.ny * a.nz, t = threadIdx.x;
+    const int h = (min(a.nx, kSeg) + 1) / 2;  // parents a word
+    uint32_t* const lp = reinterpret_cast<uint32_t*>(bits + words);
+    const uint64_t* const mask = scratch_of(scratch, a).words;
+    for (int k = t; k < 4 * nparts; k += 1024) part[k] = partials[k];
+    for (int w = t; w < words; w += 1024) {
+        const uint64_t A = mask[w];
+        bits[w] = A;
+        for (uint64_t left = A; left;) {
+            const int s = __ffsll((long long)left) - 1;
+            left &= ~run_at(A, s);
+            lp[w * h + (s >> 1)] = (uint32_t)(w * h + (s >> 1));
+        }
+    }
+    __syncthreads();
+    if (t < 4) {  // the partials in block order, as launch_totals_final
+        double s = 0.0;
+        for (int b = 0; b < nparts; ++b) s += part[4 * b + t];
+        tot[t] = t == 0 ? base_mass + s : s;
+    }
+    auto unite = [&](int wa, int sa, int wb, int sb) {
+        lds_unite(lp, (uint32_t)(wa * h + (sa >> 1)), (uint32_t)(wb * h + (sb >> 1)));
+    };
+    for (int w = t; w < words; w += 1024) {
+        const uint64_t A = bits[w];
+        if (!A) continue;
+        const Seg g = seg_of(w, a);
+        const int seg = g.x0 / kSeg, row = w - seg, last = g.width - 1;
+        const int sn = seg + 1 < segs ? seg + 1 : 0, sb = seg > 0 ? seg - 1 : segs - 1;
+        const int lastb = min(kSeg, a.nx - sb * kSeg) - 1;
+        const bool first_gas = A & 1ull, last_gas = A >> last & 1ull;
+        if (last_gas && (bits[row + sn] & 1ull)) unite(w, run_start(A, last), row + sn, 0);
+#pragma unroll
+        for (int d = 0; d < R::n; ++d) {
+            const int r2 = (wrap_once(g.y + R::dy[d], a.ny) +
+                            a.ny * wrap_once(g.z + R::dz[d], a.nz)) * segs;
+            touching_runs(A, bits[r2 + seg], R::wide[d],
+                          [&](int x, int y) { unite(w, x, r2 + seg, y); });
+            if (!R::wide[d]) continue;
+            if (last_gas && (bits[r2 + sn] & 1ull)) unite(w, run_start(A, last), r2 + sn, 0);
+            if (first_gas && (bits[r2 + sb] >> lastb & 1ull))
+                unite(w, 0, r2 + sb, run_start(bits[r2 + sb], lastb));
+        }
+    }
+    __syncthreads();
+    // every run's parent becomes its root, then the label of its root (1 + the root's node): once a
+    // run, the lanes only look it up
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int w = t; w < words; w += 1024) {
+            for (uint64_t left = bits[w]; left;) {
+                const int s = __ffsll((long long)left) - 1;
+                left &= ~run_at(bits[w], s);
+                uint32_t* const e = lp + w * h + (s >> 1);
+                if (pass == 0) {
+                    const uint32_t r = lds_root(lp, (uint32_t)(w * h + (s >> 1)));
+                    __hip_atomic_store(e, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else {
+                    const int wr = (int)*e / h, b = 2 * ((int)*e - wr * h);
+                    const uint64_t W = bits[wr], starts = W & ~(W << 1);
+                    const int row = wr / segs;
+                    *e = (uint32_t)(row * a.nx + (wr - row * segs) * kSeg + b +
+                                    (int)(~(starts >> b) & 1ull)) + 1;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const int lane = t & 63;
+    {
+        int w = __builtin_amdgcn_readfirstlane(t >> 6);
+        int row = w / segs, seg = w - row * segs;
+        const int drow = 16 / segs, dseg = 16 - drow * segs;
+        for (; w < words; w += 16) {
+            const uint64_t A = bits[w];
+            uint32_t v = 0u;
+            if (A >> lane & 1ull) v = lp[w * h + (run_start(A, lane) >> 1)];
+            if (seg * kSeg + lane < a.nx) labels[row * a.nx + seg * kSeg + lane] = v;
+            row += drow;
+            seg += dseg;
+            if (seg >= segs) {
+                seg -= segs;
+                ++row;
+            }
+        }
+    }
+    __syncthreads();
+    bubble_table_body(labels, p.nuc_node, p.n, a.N, p.prev, p.tab, p.slot_of_root, a.nx, a.ny);
+    __syncthreads();
+    for (int w0 = t - lane; w0 < words; w0 += 1024) {  // whole waves: the sums are by wave
+        const int w = w0 + lane;
+        const Seg g = seg_of(w < words ? w : 0, a);
+        word_stats(w < words ? bits[w] : 0ull, g, p.tab.anchors, p.tab.count, p.tab.sums, a,
+                   [&](int s) { return p.slot_of_root[labels[g.n + s] - 1]; });
+    }
+    __threadfence();  // the counters were summed past this CU's cache
+    __syncthreads();
+    pass_tail_body<Q, S>(p.tab, p.group, Q == 9 ? 2 : 3, p.film_max, p.pairs, p.ab, p.res, p.cap,
+                         p.do_pairs, p.out, f, labels, a);
+}
+
+static size_t small_pass_lds(const FieldArgs& a)
+{
+    const size_t words = (size_t)segs_of(a.nx) * a.ny * a.nz, h = (size_t)(std::min(a.nx, kSeg) + 1) / 2;
+    return words * 8 + words * h * 4;
+}
+
+bool small_pass_fits(const FieldArgs& a)
+{
+    // up to 2^15 nodes: beyond that one CU's share of the labels takes longer than the launches it
+    // saves
+    return a.N <= 1 << 15 && !a.f2 && small_pass_lds(a) <= (size_t)140 * 1024;
+}
+
+hipError_t launch_pass_small(int q, int storage, const void* f, uint32_t* scratch,
+                             uint32_t* labels, const double* partials, double* tot,
+                             const SmallPass& p, const FieldArgs& a, hipStream_t st)
+{
+    const int nb = totals_blocks(a.N);
+    if (!small_pass_fits(a) || nb > kSmallParts) return hipErrorInvalidValue;
+    SC_DISPATCH(q, storage,
+                hipLaunchKernelGGL((k_pass_small<QQ, SS>), dim3(1), dim3(1024), small_pass_lds(a),
+                                   st, scratch, labels, partials, nb, tot,
+                                   (double)a.N * a.rho_ref_d, p, (const SS*)f, a));
+    return hipGetLastError();
 }
 
 hipError_t launch_pass_tail(int q, int storage, const BubbleTab& t, const int32_t* group,

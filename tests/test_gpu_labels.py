@@ -90,3 +90,49 @@ def test_labels_of_masks(q, shape):
             assert np.array_equal(lab, ref) and nc2 == nc, (name, off)
         lab, nc3 = g.label_bubbles(mask)
         assert np.array_equal(lab, ref) and nc3 == nc, name
+
+
+# boxes of up to 2^15 nodes take the pass in one launch behind the mask, larger ones kernel by
+# kernel; the last two lie on either side
+@pytest.mark.parametrize("q,shape", [
+    (9, (1, 6, 4)), (9, (1, 130, 65)), (9, (1, 33, 200)), (19, (4, 4, 5)), (19, (9, 17, 66)),
+    (19, (12, 11, 130)), (9, (1, 128, 256)), (9, (1, 129, 256)),
+])
+@pytest.mark.parametrize("p", [0.1, 0.35])
+def test_pass_labels_and_bubbles(q, shape, p):
+    """Labels, bubble counts and centroids of a pass on a random gas field (clusters wrap around
+    the box): the integer sums are exact, so everything is equal."""
+    nz, ny, nx = shape
+    print(f"[gpu] pass q={q} {nx}x{ny}x{nz} p={p}", flush=True)
+    rng = np.random.default_rng(11)
+    mask = rng.random(shape) < p
+    flat = np.flatnonzero(mask.reshape(-1))
+    assert len(flat) > 0
+    nodes = rng.choice(flat, size=min(40, len(flat)), replace=False)
+    xyz = np.stack([nodes % nx, nodes // nx % ny, nodes // (nx * ny)], axis=1)
+    g = sc.Sim(q=q, nx=nx, ny=ny, nz=nz, K=0, amp=0.0, film_max=1)
+    g.seed_nuclei(xyz.astype(float), np.full(len(nodes), -1.0), np.zeros(len(nodes)), 0.0)
+    g.set_equilibrium(np.where(mask, 0.2, 1.9))
+    g.test_pass()
+    e, _ = sc.lattice(q)
+    ref = _reference(mask, e)
+    assert np.array_equal(g.last_labels(), ref)
+    comp, _ = g.nuclei(len(nodes))
+    assert np.array_equal(comp, ref[nodes])
+    got = g.bubbles()
+    assert [b["label"] for b in got] == sorted(set(ref[nodes].tolist()))
+    idx = np.arange(g.N)
+    pos = (idx % nx, idx // nx % ny, idx // (nx * ny))
+    dims = (nx, ny, nz)
+    for b in got:
+        at = ref == b["label"]
+        lead = int(np.flatnonzero(comp == b["label"])[0])
+        assert b["n"] == int(at.sum()) and b["nucleus"] == lead
+        for c in range(2 if q == 9 else 3):
+            h = dims[c] // 2
+            d = (pos[c][at] - xyz[lead, c] + h) % dims[c] - h
+            assert b["centroid"][c] == float(xyz[lead, c]) + float(d.sum()) / float(b["n"])
+    # a second pass (the first one's bubbles leave the slot map) on the moved field
+    g.set_equilibrium(np.where(np.roll(mask, (1, 2), (1, 2)), 0.2, 1.9))
+    g.test_pass()
+    assert np.array_equal(g.last_labels(), _reference(np.roll(mask, (1, 2), (1, 2)), e))
