@@ -138,7 +138,7 @@ int totals_blocks(int64_t N);
 hipError_t launch_totals(int q, int storage, const void* f, double* partials, double* out_d,
                          const FieldArgs& a, hipStream_t st);
 
-// Sums the block partials of nb <= 1024 blocks in block order into out_d[4].
+// Sums the block partials of nb <= 1024 blocks in a fixed order into out_d[4].
 hipError_t launch_totals_final(const double* partials, int nb, double* out_d, double base_mass,
                                hipStream_t st);
 
