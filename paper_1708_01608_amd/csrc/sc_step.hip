@@ -524,6 +524,9 @@ __global__ void __launch_bounds__(TX* TY) k_step3d_pipe(const S* __restrict__ sr
 // Same operations in the same order as the marching kernel, so only the substitution differs,
 // and the result does not depend on the marching kernel's tile.
 // ------------------------------------------------------------------------------------------
+template <int Q>
+constexpr int kFixLanes = Q == 19 ? 32 : 16;
+
 template <int Q, typename S, typename A, bool EXT>
 __global__ void __launch_bounds__(256) k_barrier_fix(const S* __restrict__ src,
                                                      S* __restrict__ dst, StepArgs a,
@@ -539,31 +542,39 @@ __global__ void __launch_bounds__(256) k_barrier_fix(const S* __restrict__ src,
                      wrap_once(y - 1, ny), wrap_once(y + 1, ny), z,
                      Q == 19 ? wrap_once(z - 1, nz) : 0, Q == 19 ? wrap_once(z + 1, nz) : 0, g);
     };
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < count; k += gridDim.x * blockDim.x) {
-        const uint32_t n = list[k];
+    // a group of lanes a node: lane i forms the psi the node sees at neighbour i (lane 0 its own)
+    // and all of them the force, so a node waits out one neighbour's loads, not one after the
+    // other's.  A frontier is a few hundred nodes: 37 us a step between two spheres of R = 15 with a
+    // node a lane, 6.4 us so.
+    constexpr int G = kFixLanes<Q>;
+    const int lane = (int)(threadIdx.x & 63), base = lane & ~(G - 1), i0 = lane - base;
+    const int per = (int)(gridDim.x * blockDim.x) / G;
+    // the trip count is the same for the whole wave: every lane stays for the exchange
+    const int first = (int)(blockIdx.x * blockDim.x + threadIdx.x - lane) / G;
+    for (int w = first; w < count; w += per) {
+        const int k = w + base / G;
+        const bool valid = k < count;
+        const uint32_t n = list[valid ? k : w];
         const int x = (int)(n % (uint32_t)nx);
         const uint32_t r = n / (uint32_t)nx;
         const int y = (int)(r % (uint32_t)ny), z = (int)(r / (uint32_t)ny);
         float g[Q];
-        pull(x, y, z, g);
-        const A drho = sum_dev<Q, A>(g);
-        const A pc = psi_f(c.rho_ref + drho);
-        const uint16_t o = ownr[n];
+        A ps = (A)0, drho = (A)0;
+        if (i0 < Q) {
+            const int xx = wrap_once(x + L::ex[i0], nx), yy = wrap_once(y + L::ey[i0], ny);
+            const int zz = Q == 19 ? wrap_once(z + L::ez[i0], nz) : 0;
+            const uint16_t o = ownr[n], on = ownr[xx + (int64_t)nx * (yy + (int64_t)ny * zz)];
+            pull(xx, yy, zz, g);
+            drho = sum_dev<Q, A>(g);
+            ps = psi_f(c.rho_ref + drho);
+            if (o != 0 && on != 0 && on != o) ps = c.psi_l;  // another bubble's lattice
+        }
         A fx, fy, fz;
-        interaction_sum<Q, A>(
-            [&](int i) -> A {
-                const int xx = wrap_once(x + L::ex[i], nx), yy = wrap_once(y + L::ey[i], ny);
-                const int zz = Q == 19 ? wrap_once(z + L::ez[i], nz) : 0;
-                const uint16_t on = ownr[xx + (int64_t)nx * (yy + (int64_t)ny * zz)];
-                if (o != 0 && on != 0 && on != o) return c.psi_l;  // another bubble's lattice
-                float h[Q];
-                pull(xx, yy, zz, h);
-                return psi_f(c.rho_ref + sum_dev<Q, A>(h));
-            },
-            fx, fy, fz);
-        const A gp = -c.G * pc;
-        collide_store<Q, A, S, false, EXT>(dst, N, n, g, drho, gp * fx, gp * fy,
-                                           Q == 19 ? gp * fz : (A)0, c);
+        interaction_sum<Q, A>([&](int i) -> A { return __shfl(ps, base + i, 64); }, fx, fy, fz);
+        const A gp = -c.G * ps;  // (lane 0: the node's own psi)
+        if (valid && i0 == 0)
+            collide_store<Q, A, S, false, EXT>(dst, N, n, g, drho, gp * fx, gp * fy,
+                                               Q == 19 ? gp * fz : (A)0, c);
     }
 }
 
@@ -572,7 +583,8 @@ hipError_t launch_barrier_fix(int q, int storage, int compute, const void* src, 
 {
     if (count <= 0) return hipSuccess;
     if (!a.owner) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)std::min(65535, (count + 255) / 256)), block(256);
+    const int per_block = 256 / (q == 19 ? kFixLanes<19> : kFixLanes<9>);
+    const dim3 grid((unsigned)std::min(65535, (count + per_block - 1) / per_block)), block(256);
     const bool g = a.grav != 0;
     if (storage != SC_STORE_F32) {
         // 16-bit storage: FP32 arithmetic
