@@ -97,6 +97,9 @@ struct sc_sim {
     std::vector<std::vector<int>> bub_nuclei;
     bool have_labels = false;
     int64_t list_count = 0;
+    // the same list as a map, where the step that follows adds the source (FedArgs)
+    DevBuf fed_map;
+    bool fed_ready = false;
 
     // source schedule: add_host[s * nb + b], the mass bubble b's nuclei release at step s of the
     // current chunk
@@ -883,6 +886,16 @@ int ensure_stage(sc_sim* s, int n)
 // groups; pass_enqueue queues every kernel and copy up to the pass's one synchronization (no
 // allocation, no host read of device data, so it can be captured in a graph); pass_finish
 // synchronizes and runs the host registry on what came back.
+// Whether the source of a step goes into the step after it: the plain D3Q19 kernel on FP32 storage
+// (16-bit storage rounds stochastically, and the barrier's fix-up pulls by itself), and enough fed
+// nodes that the map's read by every node (about 12 us at 256^3) is less than the source kernel
+// (4 us and 75 us a million nodes).
+bool source_joins_step(const sc_sim* s, int nb)
+{
+    return s->q == 19 && !s->two && s->p.storage == SC_STORE_F32 && !s->p.barrier &&
+           s->list_count > s->N / 64 && step_fed_fits(s->shape, nb);
+}
+
 int pass_prepare(sc_sim* s, bool with_criterion)
 {
     const int n = (int)s->rad.size();
@@ -1083,6 +1096,7 @@ int pass_finish(sc_sim* s, bool with_criterion, hipEvent_t done = nullptr)
 
     // 4. gas-node list of the bubbles the source feeds until the next pass
     s->list_count = 0;
+    s->fed_ready = false;
     if (nb > 0) {
         std::vector<int32_t> feed((size_t)nb, 0);
         int64_t cap = 0;
@@ -1111,6 +1125,15 @@ int pass_finish(sc_sim* s, bool with_criterion, hipEvent_t done = nullptr)
             HIPX(hipMemcpyAsync(&got, cnt_d, sizeof(got), hipMemcpyDeviceToHost, s->stream));
             HIPX(hipStreamSynchronize(s->stream));
             s->list_count = got;
+            if (source_joins_step(s, nb)) {
+                // (a box without the 2 bytes a node left keeps the source kernel)
+                if (ensure(s, s->fed_map, sizeof(uint16_t) * (size_t)s->N) == SC_OK) {
+                    HIPX(launch_fed_map((uint16_t*)s->fed_map.p, (const uint32_t*)s->list_node.p,
+                                        (const int32_t*)s->list_slot.p, s->list_count, s->N,
+                                        s->stream));
+                    s->fed_ready = true;
+                }
+            }
         }
         if (s->rate > 0.0) TRY(ledger_setup(s, feed));
     }
@@ -1329,7 +1352,7 @@ void release(sc_sim* s)
                       &s->mask8, &s->nodes, &s->list_node, &s->list_slot, &s->add_tab,
                       &s->pair_buf, &s->res_buf, &s->bub_tab, &s->owner, &s->owner2,
                       &s->owner_ids, &s->frontier, &s->ledger, &s->list_scan, &s->btab,
-                      &s->pair_ab})
+                      &s->pair_ab, &s->fed_map})
         dev_free(s, b->p);
     if (s->stage) (void)hipHostFree(s->stage);
     dev_free(s, s->f[0]);
@@ -1742,6 +1765,7 @@ int sc_step(sc_sim* s, int32_t nsteps)
     const FieldArgs fa = field_args(s);
     const int K = s->p.test_every;
     bool queued = false;  // the coming block's steps are already in the stream
+    int owed_pos = -1;    // schedule position whose source the next step adds
     for (int it = 0; it < nsteps; ++it) {
         if (queued || block_graph_ok(s, K, nsteps - it)) {
             // a whole K-step block without source launches: one graph, then the bookkeeping
@@ -1786,7 +1810,17 @@ int sc_step(sc_sim* s, int32_t nsteps)
             continue;
         }
         TRY(prof_begin(s, SC_KERNEL_STEP, &pe));
-        TRY(launch_one_step(s, a, s->cur));
+        if (owed_pos >= 0) {  // with the source of the step before
+            const SourceLedger led = ledger_view(s, owed_pos);
+            const FedArgs fed{(const uint16_t*)s->fed_map.p, led.dm, led.owed, led.nodes, led.gain,
+                              led.nb};
+            HIPX(launch_step_fed(s->compute, s->f[s->cur], s->f[s->cur ^ 1], a, s->shape, fed,
+                                 s->stream));
+            HIPX(launch_source_close(led, s->stream));
+            owed_pos = -1;
+        } else {
+            TRY(launch_one_step(s, a, s->cur));
+        }
         TRY(prof_end(s, pe));
         s->cur ^= 1;
         // blowing-agent source after streaming
@@ -1796,9 +1830,14 @@ int sc_step(sc_sim* s, int32_t nsteps)
         }
         const int nb = (int)s->bub.size();
         if (s->step_active.size() && s->step_active[s->chunk_pos] && s->list_count > 0) {
-            TRY(prof_begin(s, SC_KERNEL_SOURCE, &pe));
             // the agent's gas goes to the gas component when there is one
             if (s->ledger_nb != nb) return fail(SC_E_STATE, "source ledger out of step");
+            if (s->fed_ready && it + 1 < nsteps && !(K > 0 && (s->t + 1) % K == 0)) {
+                owed_pos = s->chunk_pos;  // the next step, which follows at once, adds it
+                count_steps(s, 1);
+                continue;
+            }
+            TRY(prof_begin(s, SC_KERNEL_SOURCE, &pe));
             HIPX(launch_source(s->q, s->p.storage, s->two ? s->fv[s->cur] : s->f[s->cur],
                                (const uint32_t*)s->list_node.p,
                                (const int32_t*)s->list_slot.p, s->list_count,

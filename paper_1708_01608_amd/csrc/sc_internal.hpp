@@ -51,6 +51,19 @@ bool step3d_tile_fits(const StepShape& s);
 bool step_combo_supported(int storage, int compute);
 hipError_t launch_step(int q, int storage, int compute, const void* src, void* dst,
                        const StepArgs& a, const StepShape& s, hipStream_t st);
+// The source of the step before, added by the step that follows (D3Q19, FP32 storage, the plain
+// marching kernel): map[N] holds 1 + the bubble slot of a fed node, 0 elsewhere; the rest as in
+// SourceLedger, whose gains the kernel books (launch_source_close then closes it).
+struct FedArgs {
+    const uint16_t* map;
+    const double *dm, *owed, *nodes;
+    unsigned long long* gain;
+    int nb;
+};
+constexpr int kFedBubbles = 4096;  // bubbles whose share the kernel's LDS holds
+bool step_fed_fits(const StepShape& s, int nb);
+hipError_t launch_step_fed(int compute, const void* src, void* dst, const StepArgs& a,
+                           const StepShape& s, const FedArgs& fed, hipStream_t st);
 bool step2d_multi_fits(const MultiShape& m, int storage, int compute);
 hipError_t launch_step2d_multi(int storage, int compute, const void* src, void* dst,
                                const StepArgs& a, const MultiShape& m, int T, hipStream_t st);
@@ -303,6 +316,8 @@ hipError_t launch_film(int q, int storage, const void* f, const uint32_t* labels
 // Bubble b's gain sits at gain[b * kLedgerGainStride]: one 128-byte line per bubble, since every
 // wave of a bubble's gas nodes adds to it atomically and atomics to one line serialize.
 constexpr int kLedgerGainStride = 16;
+constexpr double kGainUnit = 1.0 / 1099511627776.0;  // 2^-40: gains are summed in these
+constexpr double kGainScale = 1099511627776.0;
 struct SourceLedger {
     const double* dm;          // this step's release of each bubble's nuclei
     const double* nodes;       // n_b, gas nodes listed for the bubble
@@ -312,6 +327,10 @@ struct SourceLedger {
     int nb;
     uint64_t key;              // stochastic-rounding stream (16-bit storage)
 };
+hipError_t launch_source_close(const SourceLedger& led, hipStream_t st);
+// map[N] of FedArgs from the gas list.
+hipError_t launch_fed_map(uint16_t* map, const uint32_t* list_node, const int32_t* list_slot,
+                          int64_t count, int64_t N, hipStream_t st);
 hipError_t launch_source(int q, int storage, void* f, const uint32_t* list_node,
                          const int32_t* list_slot, int64_t count, const SourceLedger& led,
                          int64_t t, const FieldArgs& a, hipStream_t st);

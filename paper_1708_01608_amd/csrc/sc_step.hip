@@ -21,6 +21,7 @@
 
 #include "sc_device.hpp"
 #include "sc_internal.hpp"
+#include "sc_runs.hpp"
 #include "sc_stepcore.hpp"
 
 namespace sc {
@@ -221,10 +222,30 @@ __global__ void __launch_bounds__(512, 4) k_step2d_multi(const S* __restrict__ s
 // D3Q19: a block owns a tw x th tile of an x-y plane (any tw th <= B) and marches `planes` planes
 // in z.  The tile is a launch argument: the host fits it to the box, so that no lane idles where a
 // power of two would overhang it.
+//
+// SRC: the step before is owed its source (Sec. 3: gas added to every fed bubble), which is added to
+// the pulled populations of its nodes here, rounded to FP32 as the stored values would be, and its
+// gain booked once a node (ring nodes are another block's).  On a gas-rich box the source by itself
+// reads and writes 19 scattered rows a bubble row: 115 us beside a step of 552 us (256^3, 1.45 M
+// nodes fed); here it is a 2-byte map entry a node and arithmetic in the waves that hold gas: 571 us
+// for both.
 // ------------------------------------------------------------------------------------------
-template <typename S, typename A, int B, bool NT = false, bool EXT = false>
+__device__ __forceinline__ double feed(float* g, double ab)
+{
+    double gain = 0.0;
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        const double old = (double)g[i];
+        const float nw = (float)(old + lat<19>::wd[i] * ab);
+        gain += (double)nw - old;
+        g[i] = nw;
+    }
+    return gain;
+}
+
+template <typename S, typename A, int B, bool NT = false, bool EXT = false, bool SRC = false>
 __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __restrict__ dst,
-                                              StepArgs a, StepGrid grid)
+                                              StepArgs a, StepGrid grid, FedArgs fed)
 {
     using L = lat<19>;
     extern __shared__ double ring_lds[];
@@ -262,31 +283,63 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
     float cur[19], nxt[19];
     A dcur = (A)0, dnxt = (A)0;
 
+    // what a node of each fed bubble is given (times w_i)
+    double* const give = ring_lds + (4 * psz * sizeof(A) + 7) / 8;
+    if constexpr (SRC) {
+        for (int b = t; b < fed.nb; b += (int)blockDim.x) {
+            const double T = fed.owed[b] + fed.dm[b];
+            give[b] = T == 0.0 ? 0.0 : T / fed.nodes[b];
+        }
+        __syncthreads();
+    }
+    auto slot_at = [&](int xx, int yy, int zz) -> int {  // 1 + the bubble that feeds the node, or 0
+        return fed.map[(uint32_t)xx + (uint32_t)nx * ((uint32_t)yy + (uint32_t)ny * (uint32_t)zz)];
+    };
+    // the node's gain, summed over the wave's nodes of a bubble; every lane of the wave comes here
+    auto book = [&](int m, double gain) {
+        if (!__ballot(m != 0)) return;
+        long long v[1] = {(long long)rint(gain * kGainScale)};
+        wave_add_by_key<1>(m - 1, v, [&](int b, const long long* s) {
+            atomicAdd(fed.gain + (size_t)b * kLedgerGainStride, (unsigned long long)s[0]);
+        });
+    };
+
     {
         const int z = wrap_once(z0 - 1, nz);
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
         if (own) {
             float g[19];
+            const int m = SRC ? slot_at(x, y, z) : 0;
             pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+            if (SRC && m) feed(g, give[m - 1]);
             ps[pc0] = psi_f(c.rho_ref + sum_dev<19, A>(g));
         }
         if (ring) {
             float h[19];
+            const int m = SRC ? slot_at(hx, hy, z) : 0;
             pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
+            if (SRC && m) feed(h, give[m - 1]);
             ps[ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
     }
     {
         const int z = z0;
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
+        int mo = 0;
+        double gain = 0.0;
         if (own) {
+            mo = SRC ? slot_at(x, y, z) : 0;
             pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, cur);
+            if (SRC && mo) gain = feed(cur, give[mo - 1]);
             dcur = sum_dev<19, A>(cur);
             ps[psz + pc0] = psi_f(c.rho_ref + dcur);
         }
+        if constexpr (SRC) book(mo, gain);
         if (ring) {
             float h[19];
+            const int m = SRC ? slot_at(hx, hy, z) : 0;
             pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
+            if (SRC && m) feed(h, give[m - 1]);
             ps[psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
     }
@@ -299,14 +352,21 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
         {
             const int zn = wrap_once(z + 1, nz);
             const int zm = wrap_once(zn - 1, nz), zp = wrap_once(zn + 1, nz);
+            int mo = 0;
+            double gain = 0.0;
             if (own) {
+                mo = SRC ? slot_at(x, y, zn) : 0;
                 pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, zn, zm, zp, ld);
+                if (SRC && mo) gain = feed(ld, give[mo - 1]);
                 dld = sum_dev<19, A>(ld);
                 ps[sn * psz + pc0] = psi_f(c.rho_ref + dld);
             }
+            if constexpr (SRC) book(z + 1 < ze ? mo : 0, gain);  // (plane ze is the next block's)
             if (ring) {
                 float h[19];
+                const int m = SRC ? slot_at(hx, hy, zn) : 0;
                 pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, zn, zm, zp, h);
+                if (SRC && m) feed(h, give[m - 1]);
                 ps[sn * psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
             }
         }
@@ -346,9 +406,11 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
             {
                 const int zn = wrap_once(z + 1, nz);
                 const int zm = wrap_once(zn - 1, nz), zp = wrap_once(zn + 1, nz);
+                int mo = 0;
                 {
                     const int cc = opaque(cell);
                     const int ox = x0 + (cc & 0xffff), oy = y0 + (cc >> 16);
+                    if (SRC) mo = slot_at(ox, oy, zn);
                     pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, nxt);
@@ -358,10 +420,18 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
                     const int rlx = cc & 0xffff, rly = cc >> 16;
                     const int ox = wrap_once(x0 - 1 + rlx, nx), oy = wrap_once(y0 - 1 + rly, ny);
                     float h[19];
+                    const int m = SRC ? slot_at(ox, oy, zn) : 0;
                     pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, h);
+                    if (SRC && m) feed(h, give[m - 1]);
                     ps[sn * psz + pw * rly + rlx] = psi_f(c.rho_ref + sum_dev<19, A>(h));
+                }
+                if constexpr (SRC) {
+                    double gain = 0.0;
+                    if (!own) mo = 0;  // (a lane without a node holds the tile's first)
+                    if (mo) gain = feed(nxt, give[mo - 1]);
+                    book(z + 1 < ze ? mo : 0, gain);  // (plane ze is the next block's)
                 }
                 dnxt = sum_dev<19, A>(nxt);
                 const int cc = opaque(cell);
@@ -701,16 +771,16 @@ static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, con
     if (threads <= B) {                                                                          \
         if (ext && s.variant == 3)                                                               \
             hipLaunchKernelGGL((k_step3d<S, A, B, true, true>), grid, dim3(threads), lds, st,    \
-                               src, dst, a, g);                                                  \
+                               src, dst, a, g, FedArgs{});                                       \
         else if (ext)                                                                            \
             hipLaunchKernelGGL((k_step3d<S, A, B, false, true>), grid, dim3(threads), lds, st,   \
-                               src, dst, a, g);                                                  \
+                               src, dst, a, g, FedArgs{});                                       \
         else if (s.variant == 3)                                                                 \
             hipLaunchKernelGGL((k_step3d<S, A, B, true>), grid, dim3(threads), lds, st, src,     \
-                               dst, a, g);                                                       \
+                               dst, a, g, FedArgs{});                                            \
         else                                                                                     \
             hipLaunchKernelGGL((k_step3d<S, A, B>), grid, dim3(threads), lds, st, src, dst, a,   \
-                               g);                                                               \
+                               g, FedArgs{});                                                    \
         return hipGetLastError();                                                                \
     }
     if (q == 9) {
@@ -727,6 +797,50 @@ static hipError_t step_typed(int q, const S* src, S* dst, const StepArgs& a, con
 #undef SC_L3P
 #undef SC_L3
     return hipErrorInvalidValue;
+}
+
+// The step that also adds the source of the step before (FP32 storage, the plain D3Q19 kernel).
+template <typename A>
+static hipError_t step_fed_typed(const float* src, float* dst, const StepArgs& a,
+                                 const StepShape& s, const FedArgs& fed, hipStream_t st)
+{
+    StepGrid g;
+    g.gx = (a.nx + s.tile_x - 1) / s.tile_x;
+    g.gy = (a.ny + s.tile_y - 1) / s.tile_y;
+    g.gz = (a.nz + a.planes - 1) / a.planes;
+    g.tw = s.tile_x;
+    g.th = s.tile_y;
+    const dim3 grid(g.gx * g.gy * g.gz);
+    const int threads = (s.tile_x * s.tile_y + 63) & ~63;
+    const size_t ring = 4 * sizeof(A) * (size_t)(s.tile_x + 2) * (size_t)(s.tile_y + 2);
+    const size_t lds = ((ring + 7) & ~size_t(7)) + sizeof(double) * (size_t)fed.nb;
+#define SC_LF(B)                                                                                 \
+    if (threads <= B) {                                                                          \
+        if (s.variant == 3)                                                                      \
+            hipLaunchKernelGGL((k_step3d<float, A, B, true, true, true>), grid, dim3(threads),   \
+                               lds, st, src, dst, a, g, fed);                                    \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_step3d<float, A, B, false, true, true>), grid, dim3(threads),  \
+                               lds, st, src, dst, a, g, fed);                                    \
+        return hipGetLastError();                                                                \
+    }
+    SC_LF(256) SC_LF(512) SC_LF(1024)
+#undef SC_LF
+    return hipErrorInvalidValue;
+}
+
+bool step_fed_fits(const StepShape& s, int nb)
+{
+    return step3d_tile_fits(s) && nb >= 1 && nb <= kFedBubbles;
+}
+
+hipError_t launch_step_fed(int compute, const void* src, void* dst, const StepArgs& a,
+                           const StepShape& s, const FedArgs& fed, hipStream_t st)
+{
+    if (!step_fed_fits(s, fed.nb)) return hipErrorInvalidValue;
+    if (compute == SC_COMPUTE_F64)
+        return step_fed_typed<double>((const float*)src, (float*)dst, a, s, fed, st);
+    return step_fed_typed<float>((const float*)src, (float*)dst, a, s, fed, st);
 }
 
 // Region of a tile carried T steps, and what k_step2d_multi needs of it: at most three nodes a

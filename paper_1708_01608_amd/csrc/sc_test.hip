@@ -516,9 +516,6 @@ __device__ __forceinline__ S round_into(double v, double u)
 template <>
 __device__ __forceinline__ float round_into<float>(double v, double) { return (float)v; }
 
-constexpr double kGainUnit = 1.0 / 1099511627776.0;  // 2^-40
-constexpr double kGainScale = 1099511627776.0;
-
 template <int Q, typename S>
 __global__ void k_source(S* f, const uint32_t* list_node, const int32_t* list_slot, int64_t count,
                          SourceLedger led, int64_t t, FieldArgs a)
@@ -578,6 +575,25 @@ __global__ void k_source(S* f, const uint32_t* list_node, const int32_t* list_sl
             atomicAdd(&led.gain[(size_t)kb * kLedgerGainStride], (unsigned long long)s[0]);
         });
     }
+}
+
+// The gas list as a map: 1 + bubble slot of a listed node, 0 elsewhere (16 bytes a thread).
+__global__ void k_fed_clear(uint16_t* map, int64_t N)
+{
+    const int64_t words = N / 8;
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < words;
+         k += (int64_t)gridDim.x * blockDim.x)
+        reinterpret_cast<uint4*>(map)[k] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == 0)
+        for (int64_t n = words * 8 + threadIdx.x; n < N; n += blockDim.x) map[n] = 0;
+}
+
+__global__ void k_fed_map(uint16_t* map, const uint32_t* list_node, const int32_t* list_slot,
+                          int64_t count)
+{
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < count;
+         k += (int64_t)gridDim.x * blockDim.x)
+        map[list_node[k]] = (uint16_t)(list_slot[k] + 1);
 }
 
 // Closes the step's ledger once every node has added: owed_b = T_b - gain_b, gains back to zero.
@@ -1273,7 +1289,21 @@ hipError_t launch_source(int q, int storage, void* f, const uint32_t* list_node,
     SC_DISPATCH(q, storage,
                 hipLaunchKernelGGL((k_source<QQ, SS>), grid_for(count), dim3(256), 0, st, (SS*)f,
                                    list_node, list_slot, count, led, t, a));
+    return launch_source_close(led, st);
+}
+
+hipError_t launch_source_close(const SourceLedger& led, hipStream_t st)
+{
     hipLaunchKernelGGL(k_source_close, dim3(1), dim3(256), 0, st, led);
+    return hipGetLastError();
+}
+
+hipError_t launch_fed_map(uint16_t* map, const uint32_t* list_node, const int32_t* list_slot,
+                          int64_t count, int64_t N, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_fed_clear, grid_for((N + 7) / 8), dim3(256), 0, st, map, N);
+    hipLaunchKernelGGL(k_fed_map, grid_for(count), dim3(256), 0, st, map, list_node, list_slot,
+                       count);
     return hipGetLastError();
 }
 
