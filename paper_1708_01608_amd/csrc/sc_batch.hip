@@ -1,6 +1,6 @@
 // sc_batch.hip -- many independent two-bubble D2Q9 boxes in one persistent kernel (gfx950).
 //
-// Each workgroup (256 threads) takes the next box from an atomic work queue and runs it to the
+// Each workgroup takes the next box from an atomic work queue and runs it to the
 // end: fill and paint (Sec. 3.1), time steps (Fig. 1 step 6), and every K steps a test pass
 // (gas labelling, two-bubble statistics, the film walk and the FP64 pressure-Laplacian criterion
 // of Sec. 3.1 / Sec. 4).  A box stops at the first criterion firing, at the first test pass where
@@ -24,7 +24,8 @@
 
 namespace sc {
 
-constexpr int kBatchThreads = 256;
+constexpr int kBatchThreads = 256;  // of a workgroup, and the widest box
+constexpr int kWideThreads = 768;   // of a workgroup when the boxes are few (batch_threads)
 constexpr uint32_t kNone = 0xffffffffu;
 
 struct BatchInst {
@@ -72,15 +73,14 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
-constexpr int kWaves = kBatchThreads / 64;
-
 // ---- fill and paint (every node liquid plus noise, two balls of gas) -------------------------
+template <int NTH>
 __device__ void batch_init(float* f, const BatchInst& in)
 {
 #pragma clang fp contract(off)
     using L = lat<9>;
     const int nx = in.nx, ny = in.ny, N = nx * ny;
-    for (int n = threadIdx.x; n < N; n += kBatchThreads) {
+    for (int n = threadIdx.x; n < N; n += NTH) {
         const int x = n % nx, y = n / nx;
         bool gas = false;
         for (int b = 0; b < 2; ++b) {
@@ -99,20 +99,20 @@ __device__ void batch_init(float* f, const BatchInst& in)
 }
 
 // ---- one time step of a whole box ------------------------------------------------------------
-// The nodes of a box are walked in blocks of rb = max(1, 256 RB / nx) rows: a block has
-// rb * nx <= 256 RB node slots j = t + 256 r (r < RB), slot j holding column j % nx of the
+// The nodes of a box are walked in blocks of rb = max(1, NTH RB / nx) rows: a block has
+// rb * nx <= NTH RB node slots j = t + NTH r (r < RB), slot j holding column j % nx of the
 // block's row j / nx, so narrow boxes keep every lane busy.  Blocks are numbered virtually:
 // block b holds rows w = (b - 1) rb + j / nx (row w mod ny of the box), so block 0 is the
 // prologue (the rb rows before row 0) and blocks past the end wrap to the first rows.  psi of
 // block b lives in LDS ring slot b mod 4.  Iteration b (1 <= b <= nblk) loads block b + 1 and
 // collides block b; its one barrier separates the writes of slot (b+1) mod 4 from the reads of
 // block b - 3, done in iteration b - 2.
-template <typename A, int RB>
+template <typename A, int RB, int NTH>
 __device__ void batch_step(const float* __restrict__ src, float* __restrict__ dst, int nx, int ny,
                            const Coef<A>& c, A* __restrict__ ps)
 {
     using L = lat<9>;
-    constexpr int W = kBatchThreads * RB;  // node slots per block (and LDS entries per ring slot)
+    constexpr int W = NTH * RB;  // node slots per block (and LDS entries per ring slot)
     const int N = nx * ny;
     const int rb = max(1, W / nx);
     const int nblk = (ny + rb - 1) / rb;
@@ -121,7 +121,7 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
     bool act[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-        const int j = t + kBatchThreads * r;
+        const int j = t + NTH * r;
         row[r] = j / nx;
         col[r] = j - row[r] * nx;
         act[r] = row[r] < rb;
@@ -137,7 +137,7 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
         pull_node<9>(src, N, nx, ny, col[r], xm[r], xp[r], y, wrap_once(y - 1, ny),
                         wrap_once(y + 1, ny), 0, 0, 0, g);
         const A d = sum_dev<9, A>(g);
-        ps[(blk & 3) * W + t + kBatchThreads * r] = psi_f(c.rho_ref + d);
+        ps[(blk & 3) * W + t + NTH * r] = psi_f(c.rho_ref + d);
         return d;
     };
 #pragma unroll
@@ -159,7 +159,7 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
             const int y = (blk - 1) * rb + row[r];
             if (act[r] && y < ny) {
                 // row starts of rows y - 1, y, y + 1 in the ring
-                const int j0 = t + kBatchThreads * r - col[r];
+                const int j0 = t + NTH * r - col[r];
                 const int rc = sb + j0;
                 const int ru = row[r] + 1 < rb ? rc + nx : sn;
                 const int rd = row[r] > 0 ? rc - nx : sp + (rb - 1) * nx;
@@ -192,7 +192,7 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
 // and leaves those of step t + 1 (rounded to the storage's FP32, as a store would) in LDS, stage B
 // pulls from there and stores step t + 2.  A box is as wide as the block, so neither stage needs a
 // halo in x, and in y only the blocks before the first and after the last row are done twice.
-// Blocks of rb = 256 / nx rows as in batch_step, one node a lane.  Between two barriers
+// Blocks of rb = NTH / nx rows as in batch_step, one node a lane.  Between two barriers
 //   A collides block i          (psi of i - 1 .. i + 1)  -> populations of block i in LDS
 //   A loads block i + 2         -> its psi at the end, behind the rest of the interval's work
 //   B collides block i - 4      (psi of i - 5 .. i - 3)  -> global memory
@@ -200,13 +200,13 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
 // so everything read was written before the barrier and four ring slots of each kind suffice.
 // One step at a time is bound by HBM and by its one load latency per barrier; this sweep moves
 // half the bytes and is bound by the FP64 arithmetic (figures at k_batch).
-template <typename A>
+template <typename A, int NTH>
 __device__ void batch_step2(const float* __restrict__ src, float* __restrict__ dst, int nx, int ny,
                             const Coef<A>& c, A* __restrict__ psa, A* __restrict__ psb,
                             float* __restrict__ mid)
 {
     using L = lat<9>;
-    constexpr int W = kBatchThreads;
+    constexpr int W = NTH;
     const int N = nx * ny;
     const int rb = max(1, W / nx);
     const int nblk = (ny + rb - 1) / rb;
@@ -366,16 +366,18 @@ __device__ __forceinline__ int min_img_i(int d, int n)
     return r - h;
 }
 
+template <int NTH>
 struct Scratch {
-    long long i[kWaves][6];  // per wave: count, x and y offset sums of both bubbles
-    double d[kWaves][3];     // per wave: M, Jx, Jy
+    long long i[NTH / 64][6];  // per wave: count, x and y offset sums of both bubbles
+    double d[NTH / 64][3];     // per wave: M, Jx, Jy
     int flag;
 };
 
 // Labels the gas (rho < theta, FP64), gathers the two bubbles and, if asked, applies the film
 // criterion.  Returns (uniformly) whether the box stops.  Thread 0 updates `o`.
+template <int NTH>
 __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, int K, int film_max,
-                           int64_t step, bool criterion, BatchOut& o, Scratch& sh)
+                           int64_t step, bool criterion, BatchOut& o, Scratch<NTH>& sh)
 {
 #pragma clang fp contract(off)
     using L = lat<9>;
@@ -388,11 +390,11 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
     // wait out a full memory latency.
     double M = 0.0, Jx = 0.0, Jy = 0.0;
     constexpr int U1 = 2;
-    for (int n0 = t; n0 < N; n0 += U1 * kBatchThreads) {
+    for (int n0 = t; n0 < N; n0 += U1 * NTH) {
         float g[U1][9];
 #pragma unroll
         for (int u = 0; u < U1; ++u) {
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             if (n < N) {
                 const int x = n % nx, y = n / nx;
 #pragma unroll
@@ -403,7 +405,7 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
         }
 #pragma unroll
         for (int u = 0; u < U1; ++u) {
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             if (n < N) {
                 double r = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
@@ -426,7 +428,7 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
     // which becomes its parent; a run that began before the segment (the node before it gas, in
     // the same row: the carry into lane 0) continues from that node.  x-links then need no union,
     // except the periodic one from x = nx - 1 to 0.
-    for (int n0 = t; n0 < ((N + 63) & ~63); n0 += kBatchThreads) {
+    for (int n0 = t; n0 < ((N + 63) & ~63); n0 += NTH) {
         const int lane = n0 & 63;
         const int seg = n0 - lane;
         const bool gas = n0 < N && ld_par(par, n0) != kNone;
@@ -444,18 +446,18 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
     // (x = 0 counts as a start, so every link across the periodic boundary qualifies): only those
     // are united, about one union per run instead of one per link
     constexpr int U2 = 8;
-    for (int n0 = t; n0 < N; n0 += U2 * kBatchThreads) {
+    for (int n0 = t; n0 < N; n0 += U2 * NTH) {
         // gas or liquid never changes in this pass: one mask bit per gas node of the group
         unsigned gas = 0;
 #pragma unroll
         for (int u = 0; u < U2; ++u) {
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             if (n < N && ld_par(par, n) != kNone) gas |= 1u << u;
         }
         while (gas) {
             const int u = __builtin_ctz(gas);
             gas &= gas - 1;
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             const int x = n % nx, y = n / nx;
             const bool s0 = x == 0 || ld_par(par, n - 1) == kNone;
 #pragma unroll
@@ -493,17 +495,17 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
     }
     long long cnt[2] = {0, 0}, sx[2] = {0, 0}, sy[2] = {0, 0};
     constexpr int U3 = 8;
-    for (int n0 = t; n0 < N; n0 += U3 * kBatchThreads) {
+    for (int n0 = t; n0 < N; n0 += U3 * NTH) {
         unsigned gas = 0;
 #pragma unroll
         for (int u = 0; u < U3; ++u) {
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             if (n < N && par[n] != kNone) gas |= 1u << u;
         }
         while (gas) {
             const int u = __builtin_ctz(gas);
             gas &= gas - 1;
-            const int n = n0 + u * kBatchThreads;
+            const int n = n0 + u * NTH;
             const uint32_t p = batch_find(par, (uint32_t)n);
             const int y = n / nx, x = n - y * nx;
             for (int b = 0; b < 2; ++b) {
@@ -538,12 +540,12 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         tot_i[k] = sh.i[0][k];
-        for (int w = 1; w < kWaves; ++w) tot_i[k] += sh.i[w][k];
+        for (int w = 1; w < NTH / 64; ++w) tot_i[k] += sh.i[w][k];
     }
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         tot_d[k] = sh.d[0][k];
-        for (int w = 1; w < kWaves; ++w) tot_d[k] += sh.d[w][k];
+        for (int w = 1; w < NTH / 64; ++w) tot_d[k] += sh.d[w][k];
     }
     const double tM = tot_d[0], tJx = tot_d[1], tJy = tot_d[2];
 
@@ -648,16 +650,17 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
 // without (62 -> 89); two and four slots take one step a sweep and hold 256 registers (736 ms and
 // about 400 ms).  Waves per SIMD the compiler must fit (the second launch bound): one box per
 // workgroup leaves latency to hide, so with one slot the registers are capped for three waves (a
-// few spills; the rings' 53 KB of LDS allow three workgroups a CU too); more slots need two.
-template <typename A, int RB>
-__global__ void __launch_bounds__(kBatchThreads, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
+// few spills; the rings' 53 KB of LDS allow three workgroups of 256 a CU too, or one of 768);
+// more slots need two.
+template <typename A, int RB, int NTH>
+__global__ void __launch_bounds__(NTH, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
 {
-    __shared__ A ps[4 * RB * kBatchThreads];
+    __shared__ A ps[4 * RB * NTH];
     // one slot a lane: the second stage's psi and the populations between the stages
-    constexpr int kMid = RB == 1 ? 4 * kBatchThreads : 1;
+    constexpr int kMid = RB == 1 ? 4 * NTH : 1;
     __shared__ A psb[kMid];
     __shared__ float mid[9 * kMid];
-    __shared__ Scratch sh;
+    __shared__ Scratch<NTH> sh;
     __shared__ BatchOut s_out;
     __shared__ int s_idx;
     for (;;) {
@@ -683,9 +686,9 @@ __global__ void __launch_bounds__(kBatchThreads, RB == 1 ? 3 : 2) k_batch(BatchA
             o.totals[0] = o.totals[1] = o.totals[2] = 0.0;
         }
 
-        batch_init(f0, in);
+        batch_init<NTH>(f0, in);
         __syncthreads();
-        bool stop = batch_test(f0, par, in, b.K, b.film_max, 0, false, o, sh);
+        bool stop = batch_test<NTH>(f0, par, in, b.K, b.film_max, 0, false, o, sh);
         int cur = 0;
         int64_t step = 0;
         while (!stop && step < b.max_steps) {
@@ -694,13 +697,13 @@ __global__ void __launch_bounds__(kBatchThreads, RB == 1 ? 3 : 2) k_batch(BatchA
             if constexpr (RB == 1)
                 two = step + 2 <= b.max_steps && (b.K <= 0 || step % b.K + 2 <= b.K);
             if (two)
-                batch_step2<A>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps, psb, mid);
+                batch_step2<A, NTH>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps, psb, mid);
             else
-                batch_step<A, RB>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps);
+                batch_step<A, RB, NTH>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps);
             cur ^= 1;
             step += two ? 2 : 1;
             if (b.K > 0 && step % b.K == 0)
-                stop = batch_test(cur ? f1 : f0, par, in, b.K, b.film_max, step, true, o, sh);
+                stop = batch_test<NTH>(cur ? f1 : f0, par, in, b.K, b.film_max, step, true, o, sh);
         }
         if (threadIdx.x == 0) {
             o.steps_run = step;
@@ -733,6 +736,7 @@ struct sc_batch {
     int n = 0;
     int K = 10, film_max = 8, max_steps = 5000, compute = SC_COMPUTE_F64;
     int rb = 1;  // rows per thread per iteration of the box step
+    int threads = kBatchThreads;  // of a workgroup of the one-slot kernel
     hipStream_t stream = nullptr;
     bool own_stream = false;
     sc_allocator alloc{};
@@ -786,28 +790,56 @@ void brelease(sc_batch* b)
 
 namespace {
 
-hipError_t batch_occupancy(int compute, int rb, int* per_cu)
+// Threads of a workgroup of the one-slot kernel, by the number of boxes.  Three workgroups of 256
+// or one of 768 fill a CU (three waves a SIMD, the registers' and the LDS's limit), and then the
+// FP64 pipe is the bound of both.  With few boxes a CU has fewer than three, and the run ends when
+// the largest box does: the wide workgroup advances that one faster.  With many boxes the narrow
+// one wins by its shorter pipeline (nblk + 6 intervals a sweep, nblk = ny / rows).  Measured, 200
+// steps with a pass every 10, 256 against 768 threads (ms, FP64 | FP32 arithmetic): 32 boxes 49 /
+// 31 | 44 / 22; 512 60 / 37 | 56 / 30; 1024 74 / 57; 1536 87.3 / 84.7; 2048 110 / 110 | 97 / 93;
+// 4096 201 / 214 | 183 / 182.  384 and 512 threads were slower than the better of the two
+// everywhere (164 and 123 ms at 2048).
+int batch_threads(int n)
 {
-#define SC_OCC(A, RB) return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_batch<A, RB>, kBatchThreads, 0)
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return kBatchThreads;
+    return n <= 6 * cus ? kWideThreads : kBatchThreads;
+}
+
+hipError_t batch_occupancy(int compute, int rb, int threads, int* per_cu)
+{
+#define SC_OCC(A, RB, NTH) \
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_batch<A, RB, NTH>, NTH, 0)
+#define SC_OCCS(A)                                                                               \
+    if (rb == 1 && threads == kWideThreads) SC_OCC(A, 1, kWideThreads);                                         \
+    if (rb == 1) SC_OCC(A, 1, kBatchThreads);                                                    \
+    if (rb == 2) SC_OCC(A, 2, kBatchThreads);                                                    \
+    SC_OCC(A, 4, kBatchThreads)
     if (compute == SC_COMPUTE_F32) {
-        if (rb == 1) SC_OCC(float, 1);
-        if (rb == 2) SC_OCC(float, 2);
-        SC_OCC(float, 4);
+        SC_OCCS(float);
     }
-    if (rb == 1) SC_OCC(double, 1);
-    if (rb == 2) SC_OCC(double, 2);
-    SC_OCC(double, 4);
+    SC_OCCS(double);
+#undef SC_OCCS
 #undef SC_OCC
 }
 
-void batch_launch(int compute, int rb, int grid, hipStream_t st, const BatchArgs& a)
+void batch_launch(int compute, int rb, int threads, int grid, hipStream_t st, const BatchArgs& a)
 {
-#define SC_LB(A, RB) hipLaunchKernelGGL((k_batch<A, RB>), dim3(grid), dim3(kBatchThreads), 0, st, a)
+#define SC_LB(A, RB, NTH) \
+    hipLaunchKernelGGL((k_batch<A, RB, NTH>), dim3(grid), dim3(NTH), 0, st, a)
+#define SC_LBS(A)                                                                                \
+    if (rb == 1 && threads == kWideThreads) SC_LB(A, 1, kWideThreads);                                          \
+    else if (rb == 1) SC_LB(A, 1, kBatchThreads);                                                \
+    else if (rb == 2) SC_LB(A, 2, kBatchThreads);                                                \
+    else SC_LB(A, 4, kBatchThreads)
     if (compute == SC_COMPUTE_F32) {
-        if (rb == 1) SC_LB(float, 1); else if (rb == 2) SC_LB(float, 2); else SC_LB(float, 4);
+        SC_LBS(float);
     } else {
-        if (rb == 1) SC_LB(double, 1); else if (rb == 2) SC_LB(double, 2); else SC_LB(double, 4);
+        SC_LBS(double);
     }
+#undef SC_LBS
 #undef SC_LB
 }
 
@@ -852,6 +884,7 @@ int sc_batch_create(int32_t n, const sc_batch_instance* inst, int32_t test_every
     b->film_max = film_max;
     b->max_steps = max_steps;
     b->compute = compute == SC_COMPUTE_F32 ? SC_COMPUTE_F32 : SC_COMPUTE_F64;
+    b->threads = batch_threads(n);
     if (allocator) {
         b->alloc = *allocator;
         b->has_alloc = true;
@@ -945,11 +978,11 @@ int sc_batch_run(sc_batch* b, sc_batch_result* results, double* kernel_ms)
         a.K = b->K;
         a.film_max = b->film_max;
         a.max_steps = b->max_steps;
-        BHIP(batch_occupancy(b->compute, b->rb, &per_cu));
+        BHIP(batch_occupancy(b->compute, b->rb, b->threads, &per_cu));
         const int grid = std::max(1, std::min(b->n, std::max(1, per_cu) * std::max(1, cus)));
         BHIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
         hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, b->stream, (unsigned int*)b->d_counter);
-        batch_launch(b->compute, b->rb, grid, b->stream, a);
+        batch_launch(b->compute, b->rb, b->threads, grid, b->stream, a);
         hipError_t le = hipGetLastError();
         hipError_t ce = hipStreamEndCapture(b->stream, &b->graph);
         if (le != hipSuccess) return set_error(SC_E_DEVICE, std::string("batch launch: ") + hipGetErrorString(le));
