@@ -184,27 +184,65 @@ __global__ void __launch_bounds__(1024) k_march3d(const S* __restrict__ f, Field
     }
 }
 
+// Tile and planes a block.  A block of p planes goes through p + 2 of them (the values before and
+// after its own), each one load latency and its share of the CU's work: about 2 us, and 3 us for
+// 1024 nodes resident on the CU, the ring's included.  A large box wants one full block a CU and
+// as many planes as that leaves (256^3: 4 rows, 64 planes; with 8 planes 429 instead of 365 us a
+// call); a small one wants the CUs filled by thin chunks and low tiles (p and its Laplacian, then
+// rho and u, us a call with its synchronisation, against tiles of 1024 nodes and 4 planes:
+// 32^3 54 + 55 -> 44 + 43, 60 x 81 x 71 62 + 58 -> 47 + 48, 128^3 82 + 78 -> 74 + 77).  Tiles whose ring has more nodes than
+// the tile itself are left out (a ring node a thread).
+StepGrid march_tile(const FieldArgs& a, int values, int* planes)
+{
+    StepGrid g;
+    const int parts = (a.nx + 255) / 256;
+    g.tw = (a.nx + parts - 1) / parts;  // the row in equal parts of at most 256 nodes
+    g.gx = (a.nx + g.tw - 1) / g.tw;
+    const int top = std::max(1, std::min(1024 / g.tw, a.ny));
+    double best = -1.0;
+    int th = 0;
+    auto consider = [&](int h, int p) {
+        const int gy = (a.ny + h - 1) / h, gz = (a.nz + p - 1) / p;
+        const int64_t blocks = (int64_t)g.gx * gy * gz;
+        const int threads = (g.tw * h + 63) & ~63;
+        const int lds = values * 32 * (g.tw + 2) * (h + 2);
+        const int fit = std::max(1, std::min(1024 / threads, 160 * 1024 / lds));
+        const int64_t k = std::min<int64_t>(fit, (blocks + 255) / 256);
+        const int64_t rounds = (blocks + 256 * k - 1) / (256 * k);
+        const double nodes = (double)k * (threads + 2 * (g.tw + 2) + 2 * h);
+        const double cost = (double)rounds * (p + 2) * (2.0 + 3.0 * nodes / 1024.0);
+        if (best < 0.0 || cost < best) {
+            best = cost;
+            th = h;
+            *planes = p;
+        }
+    };
+    for (int h = top; h >= 1; h -= std::max(1, top / 32)) {
+        if (g.tw * h < 2 * (g.tw + 2) + 2 * h) break;
+        const int tiles = g.gx * ((a.ny + h - 1) / h);
+        const int chunks = std::max(1, std::min(a.nz, 256 / tiles));
+        consider(h, (a.nz + chunks - 1) / chunks);
+        for (int p : {1, 2, 3, 4, 6, 8})
+            if (p <= a.nz) consider(h, p);
+    }
+    if (th == 0) {  // no tile holds its ring: lanes idle
+        g.tw = 32;
+        th = 8;
+        g.gx = (a.nx + g.tw - 1) / g.tw;
+        *planes = std::min(4, a.nz);
+    }
+    g.th = th;
+    g.gy = (a.ny + th - 1) / th;
+    g.gz = (a.nz + *planes - 1) / *planes;
+    return g;
+}
+
 template <int MODE>
 hipError_t march3d(int storage, const void* f, const FieldOut& o, const FieldArgs& a,
                    hipStream_t st)
 {
-    // the row cut into equal tiles of at most 256 nodes, the rows 1024 threads then hold (four at
-    // least for a ring of at most one node a thread), and planes for one block a CU: a chunk costs
-    // two planes of values besides its own
-    StepGrid g;
-    const int parts = (a.nx + 255) / 256;
-    g.tw = (a.nx + parts - 1) / parts;
-    g.th = std::min(1024 / g.tw, a.ny);
-    g.th = (a.ny + (a.ny + g.th - 1) / g.th - 1) / ((a.ny + g.th - 1) / g.th);
-    if (g.tw * g.th < 2 * (g.tw + 2) + 2 * g.th) {  // a tile too small for its ring: lanes idle
-        g.tw = 32;
-        g.th = 8;
-    }
-    g.gx = (a.nx + g.tw - 1) / g.tw;
-    g.gy = (a.ny + g.th - 1) / g.th;
-    const int chunks = std::max(1, std::min((a.nz + 3) / 4, 256 / (g.gx * g.gy)));
-    const int planes = (a.nz + chunks - 1) / chunks;
-    g.gz = (a.nz + planes - 1) / planes;
+    int planes = 0;
+    const StepGrid g = march_tile(a, MODE == kMixFields ? 2 : 1, &planes);
     const dim3 grid(g.gx * g.gy * g.gz), block((g.tw * g.th + 63) & ~63);
     const size_t lds = (MODE == kMixFields ? 8 : 4) * sizeof(double) * (size_t)(g.tw + 2) *
                        (size_t)(g.th + 2);
