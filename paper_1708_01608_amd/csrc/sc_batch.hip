@@ -107,6 +107,16 @@ __device__ void batch_init(float* f, const BatchInst& in)
 // block b lives in LDS ring slot b mod 4.  Iteration b (1 <= b <= nblk) loads block b + 1 and
 // collides block b; its one barrier separates the writes of slot (b+1) mod 4 from the reads of
 // block b - 3, done in iteration b - 2.
+// A pointer into global memory that all lanes hold alike, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T* wave_pointer(T* p)
+{
+    const uint64_t v = (uint64_t)p;
+    return (T*)(SC_GLOBAL T*)(
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
+}
+
 template <typename A, int RB, int NTH>
 __device__ void batch_step(const float* __restrict__ src, float* __restrict__ dst, int nx, int ny,
                            const Coef<A>& c, A* __restrict__ ps)
@@ -173,7 +183,8 @@ __device__ void batch_step(const float* __restrict__ src, float* __restrict__ ds
                     },
                     fx, fy, fz);
                 const A gp = -c.G * pc;
-                collide_store<9, A, float>(dst, N, (uint32_t)(col[r] + nx * y), cur[r], dcur[r],
+                collide_store<9, A, float, false, false, false, true>(
+                    dst, N, (uint32_t)(col[r] + nx * y), cur[r], dcur[r],
                                            gp * fx, gp * fy, (A)0, c);
             }
         }
@@ -274,7 +285,8 @@ __device__ void batch_step2(const float* __restrict__ src, float* __restrict__ d
             if (i >= 5 && yb < ny) {
                 A fx, fy;
                 force(psb, i - 4, fx, fy);
-                collide_store<9, A, float>(dst, N, (uint32_t)(col + nx * yb), cb, dcb, fx, fy,
+                collide_store<9, A, float, false, false, false, true>(
+                    dst, N, (uint32_t)(col + nx * yb), cb, dcb, fx, fy,
                                            (A)0, c);
             }
 #pragma unroll
@@ -640,7 +652,8 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
         sh.flag = stop ? 1 : 0;
     }
     __syncthreads();
-    const bool stop = sh.flag != 0;
+    // (the wave's: with a lane's answer the caller's loop, and the buffers it swaps, were a lane's)
+    const bool stop = __builtin_amdgcn_readfirstlane(sh.flag) != 0;
     __syncthreads();
     return stop;
 }
@@ -696,10 +709,12 @@ __global__ void __launch_bounds__(NTH, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
             bool two = false;
             if constexpr (RB == 1)
                 two = step + 2 <= b.max_steps && (b.K <= 0 || step % b.K + 2 <= b.K);
+            float* const from = wave_pointer(cur ? f1 : f0);
+            float* const to = wave_pointer(cur ? f0 : f1);
             if (two)
-                batch_step2<A, NTH>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps, psb, mid);
+                batch_step2<A, NTH>(from, to, in.nx, in.ny, c, ps, psb, mid);
             else
-                batch_step<A, RB, NTH>(cur ? f1 : f0, cur ? f0 : f1, in.nx, in.ny, c, ps);
+                batch_step<A, RB, NTH>(from, to, in.nx, in.ny, c, ps);
             cur ^= 1;
             step += two ? 2 : 1;
             if (b.K > 0 && step % b.K == 0)

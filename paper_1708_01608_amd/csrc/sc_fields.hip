@@ -90,11 +90,11 @@ __global__ void __launch_bounds__(1024) k_march3d(const S* __restrict__ f, Field
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
         float g[19];
         if (own) {
-            pull_node<19>(f, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+            pull_plane<19>(f, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
             ml = moments19(g);
             double rv = 0.0;
             if (MODE != kFields && f2) {
-                pull_node<19>(f2, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+                pull_plane<19>(f2, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
                 mv = moments19(g);
                 rv = a.rho_ref2 + mv.s;
             }
@@ -102,11 +102,11 @@ __global__ void __launch_bounds__(1024) k_march3d(const S* __restrict__ f, Field
             if (V == 2) v1[k * psz + pc0] = rv;
         }
         if (ring) {
-            pull_node<19>(f, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, g);
+            pull_plane<19>(f, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, g);
             const double rl = a.rho_ref_d + sum_dev<19, double>(g);
             double rv = 0.0;
             if (MODE != kFields && f2) {
-                pull_node<19>(f2, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, g);
+                pull_plane<19>(f2, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, g);
                 rv = a.rho_ref2 + sum_dev<19, double>(g);
             }
             v0[k * psz + ph0] = value(rl, rv);

@@ -310,14 +310,14 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
         if (own) {
             float g[19];
             const int m = SRC ? slot_at(x, y, z) : 0;
-            pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+            pull_march<19, A>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
             if (SRC && m) feed(g, give[m - 1]);
             ps[pc0] = psi_f(c.rho_ref + sum_dev<19, A>(g));
         }
         if (ring) {
             float h[19];
             const int m = SRC ? slot_at(hx, hy, z) : 0;
-            pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
+            pull_march<19, A>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
             if (SRC && m) feed(h, give[m - 1]);
             ps[ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
         double gain = 0.0;
         if (own) {
             mo = SRC ? slot_at(x, y, z) : 0;
-            pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, cur);
+            pull_march<19, A>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, cur);
             if (SRC && mo) gain = feed(cur, give[mo - 1]);
             dcur = sum_dev<19, A>(cur);
             ps[psz + pc0] = psi_f(c.rho_ref + dcur);
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
         if (ring) {
             float h[19];
             const int m = SRC ? slot_at(hx, hy, z) : 0;
-            pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
+            pull_march<19, A>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
             if (SRC && m) feed(h, give[m - 1]);
             ps[psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
         }
@@ -356,7 +356,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
             double gain = 0.0;
             if (own) {
                 mo = SRC ? slot_at(x, y, zn) : 0;
-                pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, zn, zm, zp, ld);
+                pull_march<19, A>(src, N, nx, ny, x, xm, xp, y, ym, yp, zn, zm, zp, ld);
                 if (SRC && mo) gain = feed(ld, give[mo - 1]);
                 dld = sum_dev<19, A>(ld);
                 ps[sn * psz + pc0] = psi_f(c.rho_ref + dld);
@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
             if (ring) {
                 float h[19];
                 const int m = SRC ? slot_at(hx, hy, zn) : 0;
-                pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, zn, zm, zp, h);
+                pull_march<19, A>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, zn, zm, zp, h);
                 if (SRC && m) feed(h, give[m - 1]);
                 ps[sn * psz + ph0] = psi_f(c.rho_ref + sum_dev<19, A>(h));
             }
@@ -381,8 +381,8 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
                 },
                 fx, fy, fz);
             const A gp = -c.G * pc;
-            collide_store<19, A, S, NT, EXT>(dst, N, (uint32_t)(x + nx * (y + ny * z)), co, dco,
-                                            gp * fx, gp * fy, gp * fz, c);
+            collide_store<19, A, S, NT, EXT, false, !kWide<A>>(
+                dst, N, (uint32_t)(x + nx * (y + ny * z)), co, dco, gp * fx, gp * fy, gp * fz, c);
         }
     };
     if constexpr (!std::is_same<A, double>::value) {
@@ -411,7 +411,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
                     const int cc = opaque(cell);
                     const int ox = x0 + (cc & 0xffff), oy = y0 + (cc >> 16);
                     if (SRC) mo = slot_at(ox, oy, zn);
-                    pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
+                    pull_march<19, A>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, nxt);
                 }
@@ -421,7 +421,7 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
                     const int ox = wrap_once(x0 - 1 + rlx, nx), oy = wrap_once(y0 - 1 + rly, ny);
                     float h[19];
                     const int m = SRC ? slot_at(ox, oy, zn) : 0;
-                    pull_node<19>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
+                    pull_march<19, A>(src, N, nx, ny, ox, wrap_once(ox - 1, nx),
                                   wrap_once(ox + 1, nx), oy, wrap_once(oy - 1, ny),
                                   wrap_once(oy + 1, ny), zn, zm, zp, h);
                     if (SRC && m) feed(h, give[m - 1]);
@@ -453,8 +453,9 @@ __global__ void __launch_bounds__(B) k_step3d(const S* __restrict__ src, S* __re
                     fx, fy, fz);
                 const A gp = -c.G * pc;
                 const int ox = x0 + ltx, oy = y0 + lty;
-                collide_store<19, A, S, NT, EXT, true>(dst, N, (uint32_t)(ox + nx * (oy + ny * z)),
-                                                      cur, dcur, gp * fx, gp * fy, gp * fz, c);
+                collide_store<19, A, S, NT, EXT, true>(
+                    dst, N, (uint32_t)(ox + nx * (oy + ny * z)), cur, dcur, gp * fx, gp * fy,
+                    gp * fz, c);
             }
 #pragma unroll
             for (int i = 0; i < 19; ++i) cur[i] = nxt[i];
@@ -524,7 +525,7 @@ __global__ void __launch_bounds__(TX* TY) k_step3d_pipe(const S* __restrict__ sr
         const int z = wrap_once(z0 - 1 + k, nz);
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
         if (own) {
-            pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, pre);
+            pull_march<19, A>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, pre);
             const A d = sum_dev<19, A>(pre);
             ps[k][ty + 1][tx + 1] = psi_f(c.rho_ref + d);
             if (k == 1) {
@@ -538,7 +539,7 @@ __global__ void __launch_bounds__(TX* TY) k_step3d_pipe(const S* __restrict__ sr
             }
         }
         if (ring) {
-            pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, hpre);
+            pull_march<19, A>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, hpre);
             ps[k][hly][hlx] = psi_f(c.rho_ref + sum_dev<19, A>(hpre));
         }
     }
@@ -554,8 +555,8 @@ __global__ void __launch_bounds__(TX* TY) k_step3d_pipe(const S* __restrict__ sr
         if (more) {
             const int z2 = wrap_once(z + 2 >= nz ? z + 2 - nz : z + 2, nz);
             const int zm = wrap_once(z2 - 1, nz), zp = wrap_once(z2 + 1, nz);
-            if (own) pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z2, zm, zp, pf);
-            if (ring) pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z2, zm, zp, hpre);
+            if (own) pull_march<19, A>(src, N, nx, ny, x, xm, xp, y, ym, yp, z2, zm, zp, pf);
+            if (ring) pull_march<19, A>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z2, zm, zp, hpre);
         }
         if (own) {
             const A pc = ps[s][ty + 1][tx + 1];
@@ -567,8 +568,8 @@ __global__ void __launch_bounds__(TX* TY) k_step3d_pipe(const S* __restrict__ sr
                 },
                 fx, fy, fz);
             const A gp = -c.G * pc;
-            collide_store<19, A, S, true>(dst, N, (uint32_t)(x + nx * (y + ny * z)), co, dco,
-                                          gp * fx, gp * fy, gp * fz, c);
+            collide_store<19, A, S, true, false, false, !kWide<A>>(
+                dst, N, (uint32_t)(x + nx * (y + ny * z)), co, dco, gp * fx, gp * fy, gp * fz, c);
         }
         if (more) {
             if (own) {

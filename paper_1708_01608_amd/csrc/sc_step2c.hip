@@ -327,7 +327,7 @@ __global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
     auto load_plane = [&](int z, int k, int k3, float* g) {
         const int zm = wrap_once(z - 1, nz), zp = wrap_once(z + 1, nz);
         if (own) {
-            pull_node<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+            pull_plane<19>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
             ra[k * psz + pc0] = sum_dev<19, A>(g);
             if (k3 >= 0) {
                 A jx, jy, jz;
@@ -340,7 +340,7 @@ __global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
         }
         if (ring) {
             float h[19];
-            pull_node<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
+            pull_plane<19>(src, N, nx, ny, hx, hxm, hxp, hy, hym, hyp, z, zm, zp, h);
             ra[k * psz + ph0] = sum_dev<19, A>(h);
         }
     };
@@ -374,9 +374,9 @@ __global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
             interaction_sum<19, A>(
                 [&](int i) { return rb[slot(i) * psz + pc0 + L::ey[i] * pw + L::ex[i]]; }, sx, sy,
                 sz);
-            relax_store<19, A, S, NT>(dst, N, (uint32_t)(x + nx * (y + ny * z)), cur, da,
-                                      ref_a + da, fmad(ka, sx, upx), fmad(ka, sy, upy),
-                                      fmad(ka, sz, upz), ia);
+            relax_store<19, A, S, NT, false, true>(
+                dst, N, (uint32_t)(x + nx * (y + ny * z)), cur, da, ref_a + da, fmad(ka, sx, upx),
+                fmad(ka, sy, upy), fmad(ka, sz, upz), ia);
         }
 #pragma unroll
         for (int i = 0; i < 19; ++i) cur[i] = nxt[i];

@@ -24,6 +24,17 @@ __device__ __forceinline__ float opaque(float v)
     return v;
 }
 
+// The same for a pointer that every lane of the wave shares, kept in scalar registers: an access at
+// its sum with a 32-bit offset a lane then takes the scalar-base form, and the scalar unit makes the
+// base where it is used (all bases of a node do not fit the scalar registers at once).
+// (Global memory by type: opaque, it could be any.)
+#define SC_GLOBAL __attribute__((address_space(1)))
+__device__ __forceinline__ SC_GLOBAL char* scalar_base(SC_GLOBAL char* p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 struct StepGrid {
     int gx, gy, gz;  // tiles along x, y and plane chunks
     int tw, th;      // tile width and height in nodes
@@ -74,6 +85,52 @@ __device__ __forceinline__ void pull_node(const S* __restrict__ src, int64_t N, 
         const char* base = reinterpret_cast<const char*>(src + (int64_t)i * N);
         g[i] = load_f(*reinterpret_cast<const S*>(base + off));
     }
+}
+
+// The same for a node of a plane that the whole wave works on (z, zm and zp are the wave's): the
+// plane goes into the scalar base, and what is left a lane is nine offsets of its row, which a
+// marching block computes once.
+template <int Q, typename S>
+__device__ __forceinline__ void pull_plane(const S* __restrict__ src, int64_t N, int nx, int ny,
+                                           int x, int xm, int xp, int y, int ym, int yp, int z,
+                                           int zm, int zp, float* g)
+{
+    using L = lat<Q>;
+    const int64_t plane = (int64_t)nx * ny * (int64_t)sizeof(S);
+    const uint32_t xo[3] = {(uint32_t)xp, (uint32_t)x, (uint32_t)xm};  // by -e_x: +1 -> xm
+    const uint32_t yo[3] = {(uint32_t)yp * nx, (uint32_t)y * nx, (uint32_t)ym * nx};
+    const int64_t zo[3] = {zp * plane, z * plane, zm * plane};
+    uint32_t at[3][3];  // opaque: extended to 64 bits ahead of a loop, they would not fit the form
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        at[k / 3][k % 3] =
+            (uint32_t)opaque((int)((xo[k % 3] + yo[k / 3]) * (uint32_t)sizeof(S)));
+    SC_GLOBAL char* dir = (SC_GLOBAL char*)src;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        SC_GLOBAL char* base = scalar_base(dir + zo[L::ez[i] + 1]);
+        g[i] = load_f(*(const SC_GLOBAL S*)(base + at[L::ey[i] + 1][L::ex[i] + 1]));
+        dir += N * (int64_t)sizeof(S);
+    }
+}
+
+// The pull of the one-component marching kernels.  With FP32 arithmetic the issue of instructions
+// takes half their time: plane bases save 39 of 306 vector instructions a node (bf16 203 x 150 x 121
+// 86 -> 83 us a step with its share of the pass, f16 512^3 2.40 -> 2.35 ms).  With FP64 arithmetic
+// they are bound by memory, and the scalar additions between the loads only hold those up (256^3
+// 518 -> 523 us): one offset a load there.  (The mixture's kernels gain with both: 256^3 FP64 1.10 ->
+// 1.07 ms.)
+template <typename A>
+constexpr bool kWide = std::is_same<A, double>::value;
+template <int Q, typename A, typename S>
+__device__ __forceinline__ void pull_march(const S* __restrict__ src, int64_t N, int nx, int ny,
+                                           int x, int xm, int xp, int y, int ym, int yp, int z,
+                                           int zm, int zp, float* g)
+{
+    if constexpr (kWide<A>)
+        pull_node<Q>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
+    else
+        pull_plane<Q>(src, N, nx, ny, x, xm, xp, y, ym, yp, z, zm, zp, g);
 }
 
 // Index of the lattice velocity (dx, dy, dz) in lat<Q> (compile time).
@@ -216,7 +273,8 @@ __device__ __forceinline__ A e_dot(int i, A ux, A uy, A uz)
 //   g_i* = g_i + omega (w_i (drho + rho P_i) - g_i)
 // with P of an opposite pair sharing its even part (P_i = S + 3 e.u, P_ibar = S - 3 e.u,
 // S = 4.5 (e.u)^2 - 1.5 u^2): three FMAs a direction instead of five.
-template <int Q, typename A, typename S, bool NT = false, bool RECVT = false>
+// MEM: dst is global memory that the whole wave shares (false: LDS, or a pointer of the lane's).
+template <int Q, typename A, typename S, bool NT = false, bool RECVT = false, bool MEM = false>
 __device__ __forceinline__ void relax_store(S* __restrict__ dst, int64_t N, uint32_t lane,
                                             const float* g, A drho, A rho, A ux, A uy, A uz,
                                             A omega)
@@ -224,14 +282,23 @@ __device__ __forceinline__ void relax_store(S* __restrict__ dst, int64_t N, uint
     constexpr bool three = Q == 19;
     const A usq15 = (A)1.5 * (three ? ux * ux + uy * uy + uz * uz : ux * ux + uy * uy);
     const uint32_t boff = lane * (uint32_t)sizeof(S);
+    SC_GLOBAL char* dir = (SC_GLOBAL char*)dst;
+    // population i's entry of the node; the directions are asked in order
+    auto entry = [&](int i) -> S* {
+        if constexpr (MEM) {
+            dir = scalar_base(i == 0 ? dir : dir + N * (int64_t)sizeof(S));
+            return (S*)(dir + boff);
+        } else {
+            return reinterpret_cast<S*>(reinterpret_cast<char*>(dst + (int64_t)i * N) + boff);
+        }
+    };
     if constexpr (sizeof(S) == 2) {
         // rest population, then the opposite pairs (i odd, i + 1 its reverse)
         auto put_one = [&](int i, A P) {
             const A gi = (A)g[i];
             const A feq = weight<Q, A>(i) * fmad(rho, P, drho);
             const A gs = fmad(omega, feq - gi, gi);
-            char* base = reinterpret_cast<char*>(dst + (int64_t)i * N);
-            put<NT, S>(reinterpret_cast<S*>(base + boff), store_f<S>((float)gs));
+            put<NT, S>(entry(i), store_f<S>((float)gs));
         };
         put_one(0, -usq15);
 #pragma unroll
@@ -255,14 +322,14 @@ __device__ __forceinline__ void relax_store(S* __restrict__ dst, int64_t N, uint
         if constexpr (std::is_same<A, float>::value) h = fmad(-weight_lo<Q>(i), drho, h);
         const A d = fmad(w * rho, P, -h);
         const A gs = fmad(omega, d, gi);
-        char* base = reinterpret_cast<char*>(dst + (int64_t)i * N);
-        put<NT, S>(reinterpret_cast<S*>(base + boff), store_f<S>((float)gs));
+        put<NT, S>(entry(i), store_f<S>((float)gs));
     }
 }
 
 // Forced collision of one component: velocity-shift forcing u_eq = (j + tau F) / rho, then the
 // BGK relaxation and the store.
-template <int Q, typename A, typename S, bool NT = false, bool EXT = false, bool RECVT = false>
+template <int Q, typename A, typename S, bool NT = false, bool EXT = false, bool RECVT = false,
+          bool MEM = false>
 __device__ __forceinline__ void collide_store(S* __restrict__ dst, int64_t N, uint32_t lane,
                                               const float* g, A drho, A Fx, A Fy, A Fz,
                                               const Coef<A>& c)
@@ -290,7 +357,7 @@ __device__ __forceinline__ void collide_store(S* __restrict__ dst, int64_t N, ui
     const A ux = fmad(c.tau, Fx, jx) * inv;
     const A uy = fmad(c.tau, Fy, jy) * inv;
     const A uz = three ? fmad(c.tau, Fz, jz) * inv : (A)0;
-    relax_store<Q, A, S, NT, RECVT>(dst, N, lane, g, drho, rho, ux, uy, uz, c.omega);
+    relax_store<Q, A, S, NT, RECVT, MEM>(dst, N, lane, g, drho, rho, ux, uy, uz, c.omega);
 }
 
 }  // namespace sc
