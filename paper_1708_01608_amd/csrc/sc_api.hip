@@ -1749,7 +1749,7 @@ static void count_steps(sc_sim* s, int m)
 // and so few nuclei that every pair is tested in the pass itself (more pairs than the buffers hold
 // are walked again on the populations of the pass).  The host's part of the pass, some 20 us of
 // waking, registry and launching, then runs beside them: 128^2 with a pass every 10 steps
-// 644 -> 484 us for 100 steps.
+// 644 -> 549 us for 100 steps.
 static bool pass_leaves_steps(const sc_sim* s)
 {
     const int64_t n = (int64_t)s->rad.size();
@@ -1832,7 +1832,9 @@ int sc_step(sc_sim* s, int32_t nsteps)
         if (s->step_active.size() && s->step_active[s->chunk_pos] && s->list_count > 0) {
             // the agent's gas goes to the gas component when there is one
             if (s->ledger_nb != nb) return fail(SC_E_STATE, "source ledger out of step");
-            if (s->fed_ready && it + 1 < nsteps && !(K > 0 && (s->t + 1) % K == 0)) {
+            // (the tile asked again: tuning since the pass may have chosen a pipelined one)
+            if (s->fed_ready && step_fed_fits(s->shape, nb) && it + 1 < nsteps &&
+                !(K > 0 && (s->t + 1) % K == 0)) {
                 owed_pos = s->chunk_pos;  // the next step, which follows at once, adds it
                 count_steps(s, 1);
                 continue;
