@@ -351,7 +351,7 @@ double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
                              (runs * (2 * run + edge_ld + edge_st) +
                               0.25 * 2 * (tw * es + edge_ld) + 2 * th * 128 * 0.32);
         const double work = (double)((blocks + 255) / 256) * (bw + 0.6 * ring_waves * (mix ? 2 : 1)) *
-                            0.32 * (f64 ? 1.0 : 0.6);
+                            0.32 * (es == 4 ? 1.0 : 0.6);
         return std::max({mix ? 4.3 : 3.6, bytes / 5.9e6, work});
     };
     double t = (double)(nb / slots) * plane(slots);
