@@ -321,8 +321,8 @@ StepShape default_shape(const sc_params& p)
 // marching its planes (and the prologue's) at the slowest of the plane latency, the memory
 // traffic and the arithmetic of a round's blocks.  The constants were fitted to the measured
 // times of some 8,000 shapes on 25 boxes of 48^3 to 300 x 200 x 100 and 256^3, one and two
-// components, FP32 and 16-bit storage: the shape it picks is on average 1% (one component up to
-// 5%) slower than the fastest of those measured.
+// components, FP32 and 16-bit storage, and 13,000 on 14 boxes from 32 nodes wide on: the shape it
+// picks is on average 1 to 3% slower than the fastest of those measured (one component, at worst 16%).
 double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
 {
     const bool mix = p.components == 2, f64 = compute == SC_COMPUTE_F64;
@@ -352,7 +352,15 @@ double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
                               0.25 * 2 * (tw * es + edge_ld) + 2 * th * 128 * 0.32);
         const double work = (double)((blocks + 255) / 256) * (bw + 0.6 * ring_waves * (mix ? 2 : 1)) *
                             0.32 * (es == 4 ? 1.0 : 0.6);
-        return std::max({mix ? 4.3 : 3.6, bytes / 5.9e6, work});
+        const double lat = mix ? 4.3 : 3.6, mem = bytes / 5.9e6;
+        // large boxes of narrow rows: the three overlap less, and a block of many waves, which all
+        // wait at its barrier, overlaps least (40 x 250 x 250 FP64 129 -> 95 us a step, 60 x 250 x
+        // 240 173 -> 147, FP16 32 x 300 x 300 54 -> 47; small boxes and wider ones pick worse this
+        // way: FP16 64^3 9.5 -> 10.9, boxes of 96 .. 264 a row by 4%)
+        if (!mix && p.nx <= 80 && (int64_t)p.nx * p.ny * p.nz > 650000)
+            return std::pow(std::pow(lat, 8) + std::pow(mem, 8) + std::pow(work, 8), 0.125) *
+                   (1.0 + 0.3 * waves / 16.0);
+        return std::max({lat, mem, work});
     };
     double t = (double)(nb / slots) * plane(slots);
     if (nb % slots) t += plane(nb % slots);
