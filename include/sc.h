@@ -314,7 +314,9 @@ int sc_profile_read(struct sc_sim* sim, int32_t kernel_class, double* ms, int64_
 
 /* Autotuner of the step kernel.  Times every candidate (tile_x, tile_y, tile_z, variant) on the
  * current state with HIP events -- each trial launch reads the current populations and writes the
- * spare buffer, so the simulation is unchanged -- and keeps the fastest for this handle.  The
+ * spare buffer, so the simulation is unchanged -- and keeps the fastest for this handle.  (The tile
+ * that D3Q19 boxes get by default is fitted to the box and not among them: on small or ragged boxes
+ * it is the faster one, by up to four times at 48^3.)  The
  * choice is remembered for later handles of the same lattice, box, storage, compute type and
  * component count in this process (two components tune their own fused kernel's shapes).  trials >= 1 launches per candidate; out[cap] (may be NULL) receives the timings
  * in candidate order, *n_out the candidate count. */
