@@ -230,14 +230,14 @@ __global__ void __launch_bounds__(kTileWords) k_label_local(uint32_t* scratch,
         if (!A || jy >= T::RY || jz < 0 || jz >= T::RZ) continue;
         const int u = jz * T::RY + jy;
         touching_runs(A, bits[u], R::wide[d], [&](int sa, int sb) {
-            lds_unite(lp, (uint32_t)(t * 32 + (sa >> 1)), (uint32_t)(u * 32 + (sb >> 1)));
+            union_unite(LdsParents{lp}, (uint32_t)(t * 32 + (sa >> 1)), (uint32_t)(u * 32 + (sb >> 1)));
         });
     }
     __syncthreads();
     for (uint64_t left = A; left;) {
         const int s = __ffsll((long long)left) - 1;
         left &= ~run_at(A, s);
-        const uint32_t e = lds_root(lp, (uint32_t)(t * 32 + (s >> 1)));
+        const uint32_t e = union_root_halving(LdsParents{lp}, (uint32_t)(t * 32 + (s >> 1)));
         const int w = (int)(e >> 5), h = 2 * (int)(e & 31);
         // the start of the root's run is at bit h or h + 1 of its word: the one that is gas and
         // has no gas before it

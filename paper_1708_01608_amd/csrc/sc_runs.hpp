@@ -4,6 +4,7 @@
 
 #include "sc_device.hpp"
 #include "sc_internal.hpp"
+#include "sc_union.hpp"
 
 namespace sc {
 
@@ -72,37 +73,21 @@ __device__ __forceinline__ Seg seg_of(int64_t w, const FieldArgs& a)
 }
 
 // ---- union-find in LDS -----------------------------------------------------------------------
-__device__ __forceinline__ uint32_t lds_load(const uint32_t* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// The walk to a root halves its path: a visited entry is relinked to its grandparent, an ancestor
-// with a smaller index, so concurrent unions stay correct.
-__device__ __forceinline__ uint32_t lds_root(uint32_t* lp, uint32_t x)
-{
-    while (true) {
-        const uint32_t p = lds_load(lp + x);
-        if (p == x) return x;
-        const uint32_t g = lds_load(lp + p);
-        if (g == p) return p;
-        __hip_atomic_store(lp + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        x = g;
+struct LdsParents {
+    uint32_t* p;
+    __device__ __forceinline__ uint32_t load(uint32_t i) const
+    {
+        return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-}
-
-__device__ __forceinline__ void lds_unite(uint32_t* lp, uint32_t a, uint32_t b)
-{
-    while (true) {
-        a = lds_root(lp, a);
-        b = lds_root(lp, b);
-        if (a == b) return;
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(lp + b, a);
-        if (old == b) return;
-        b = old;
+    __device__ __forceinline__ void store(uint32_t i, uint32_t v) const
+    {
+        __hip_atomic_store(p + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-}
+    __device__ __forceinline__ uint32_t min(uint32_t i, uint32_t v) const
+    {
+        return atomicMin(p + i, v);
+    }
+};
 
 // Calls link(sa, sb) once for every pair of touching runs of two adjacent rows: sa, sb the first
 // bits of the runs of words A and B; `wide` rows touch diagonally too.

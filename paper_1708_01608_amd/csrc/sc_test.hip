@@ -1163,7 +1163,7 @@ __global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
         tot[t] = t == 0 ? base_mass + s : s;
     }
     auto unite = [&](int wa, int sa, int wb, int sb) {
-        lds_unite(lp, (uint32_t)(wa * h + (sa >> 1)), (uint32_t)(wb * h + (sb >> 1)));
+        union_unite(LdsParents{lp}, (uint32_t)(wa * h + (sa >> 1)), (uint32_t)(wb * h + (sb >> 1)));
     };
     for (int w = t; w < words; w += 1024) {
         const uint64_t A = bits[w];
@@ -1196,8 +1196,7 @@ __global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
                 left &= ~run_at(bits[w], s);
                 uint32_t* const e = lp + w * h + (s >> 1);
                 if (pass == 0) {
-                    const uint32_t r = lds_root(lp, (uint32_t)(w * h + (s >> 1)));
-                    __hip_atomic_store(e, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    union_settle(LdsParents{lp}, (uint32_t)(w * h + (s >> 1)));
                 } else {
                     const int wr = (int)*e / h, b = 2 * ((int)*e - wr * h);
                     const uint64_t W = bits[wr], starts = W & ~(W << 1);
