@@ -28,17 +28,29 @@ namespace sc {
 
 namespace {
 
-template <int Q>
+// Rows of a tile, and the lanes a word is split over in the two kernels that unite.  FINE: where the
+// tiles do not fill the chip, its lanes would idle while one walks the up to 32 runs of a word of a
+// fine mask (random masks, microseconds a call, coarse and fine: 64^3 30% gas 149 -> 100, 1000^2
+// 60% 214 -> 94); on large boxes the idle lanes of words with a run or two cost more than they
+// give (256^3, 200 balls: 2, 4 and 8 lanes a word 110, 119, 133).
+template <int Q, bool FINE>
 struct LabelTile;
 template <>
-struct LabelTile<9> {
-    static constexpr int RY = 256, RZ = 1;
+struct LabelTile<9, false> {
+    static constexpr int RY = 256, RZ = 1, PARTS = 2, CROSS = 2;
 };
 template <>
-struct LabelTile<19> {
-    static constexpr int RY = 16, RZ = 16;
+struct LabelTile<9, true> {
+    static constexpr int RY = 128, RZ = 1, PARTS = 8, CROSS = 8;
 };
-constexpr int kTileWords = 256;
+template <>
+struct LabelTile<19, false> {
+    static constexpr int RY = 16, RZ = 16, PARTS = 2, CROSS = 2;
+};
+template <>
+struct LabelTile<19, true> {
+    static constexpr int RY = 16, RZ = 16, PARTS = 4, CROSS = 8;
+};
 
 // ---- mask words ----------------------------------------------------------------------------------
 // A wave takes kMaskWords segments a turn, loads first.
@@ -175,51 +187,44 @@ __device__ __forceinline__ uint32_t load_parent(const uint32_t* parent, uint32_t
     return __hip_atomic_load(parent + (c >> 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// parents only decrease and always point inside the same set, so a stale read is still an ancestor;
-// atomicMin links root b under a and reports a concurrent re-link through its result.
-__device__ void unite(uint32_t* parent, uint32_t a, uint32_t b)
-{
-    while (true) {
-        while (true) {
-            if (a == b) return;
-            const uint32_t pa = load_parent(parent, a), pb = load_parent(parent, b);
-            if (pa == a && pb == b) break;
-            a = pa;
-            b = pb;
-        }
-        if (a > b) { const uint32_t t = a; a = b; b = t; }
-        const uint32_t old = atomicMin(parent + (b >> 1), a);
-        if (old == b) return;
-        b = old;
+struct GlobalParents {
+    uint32_t* p;
+    __device__ __forceinline__ uint32_t load(uint32_t c) const { return load_parent(p, c); }
+    __device__ __forceinline__ void store(uint32_t c, uint32_t v) const
+    {
+        __hip_atomic_store(p + (c >> 1), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-}
+    __device__ __forceinline__ uint32_t min(uint32_t c, uint32_t v) const
+    {
+        return atomicMin(p + (c >> 1), v);
+    }
+};
 
-// One word a thread; the index of a run in LDS is its word's index times 32 plus half its first
+// PARTS threads a word; the index of a run in LDS is its word's index times 32 plus half its first
 // bit, which follows the global order, so a local root is the smallest node of its local set.
 // Bound by the latency of the LDS chains.
-template <int Q>
-__global__ void __launch_bounds__(kTileWords) k_label_local(uint32_t* scratch,
-                                                            uint32_t* zero_counter, FieldArgs a)
+template <int Q, bool FINE, typename T = LabelTile<Q, FINE>>
+__global__ void __launch_bounds__(T::RY * T::RZ * T::PARTS)
+k_label_local(uint32_t* scratch, uint32_t* zero_counter, FieldArgs a)
 {
-    using T = LabelTile<Q>;
     using R = RowLinks<Q>;
-    static_assert(T::RY * T::RZ == kTileWords, "one word a thread");
-    __shared__ uint64_t bits[kTileWords];
-    __shared__ uint32_t lp[kTileWords * (kSeg / 2)];
+    constexpr int kWords = T::RY * T::RZ;
+    __shared__ uint64_t bits[kWords];
+    __shared__ uint32_t lp[kWords * (kSeg / 2)];
     // the component counter of the flatten that follows starts at zero
     if (zero_counter && blockIdx.x == 0 && threadIdx.x == 0) *zero_counter = 0u;
     const LabelScratch sc = scratch_of(scratch, a);
     const int segs = segs_of(a.nx), gy = (a.ny + T::RY - 1) / T::RY;
-    const int b = blockIdx.x, t = threadIdx.x;
+    const int b = blockIdx.x, t = threadIdx.x / T::PARTS, part = threadIdx.x % T::PARTS;
     const int seg = b % segs, y0 = ((b / segs) % gy) * T::RY, z0 = (b / (segs * gy)) * T::RZ;
     const int iy = t % T::RY, iz = t / T::RY;
     const bool in = y0 + iy < a.ny && z0 + iz < a.nz;
     const uint32_t r = (uint32_t)(y0 + iy) + (uint32_t)a.ny * (uint32_t)(z0 + iz);
     const uint64_t A = in ? sc.words[(size_t)r * segs + seg] : 0ull;
-    bits[t] = A;
-    for (uint64_t left = A; left;) {
+    const uint64_t starts = run_starts<T::PARTS>(A, part);
+    if (part == 0) bits[t] = A;
+    for (uint64_t left = starts; left; left &= left - 1) {
         const int s = __ffsll((long long)left) - 1;
-        left &= ~run_at(A, s);
         lp[t * 32 + (s >> 1)] = (uint32_t)(t * 32 + (s >> 1));
     }
     if (!__syncthreads_or(A != 0ull)) return;
@@ -227,45 +232,47 @@ __global__ void __launch_bounds__(kTileWords) k_label_local(uint32_t* scratch,
     for (int d = 0; d < R::n; ++d) {
         const int jy = iy + R::dy[d], jz = iz + R::dz[d];
         // a row outside the box has no bits, so only the tile's own edges need a test
-        if (!A || jy >= T::RY || jz < 0 || jz >= T::RZ) continue;
+        if (!starts || jy >= T::RY || jz < 0 || jz >= T::RZ) continue;
         const int u = jz * T::RY + jy;
-        touching_runs(A, bits[u], R::wide[d], [&](int sa, int sb) {
+        touching_runs(A, bits[u], starts, R::wide[d], [&](int sa, int sb) {
             union_unite(LdsParents{lp}, (uint32_t)(t * 32 + (sa >> 1)), (uint32_t)(u * 32 + (sb >> 1)));
         });
     }
     __syncthreads();
-    for (uint64_t left = A; left;) {
+    for (uint64_t left = starts; left; left &= left - 1) {
         const int s = __ffsll((long long)left) - 1;
-        left &= ~run_at(A, s);
         const uint32_t e = union_root_halving(LdsParents{lp}, (uint32_t)(t * 32 + (s >> 1)));
         const int w = (int)(e >> 5), h = 2 * (int)(e & 31);
         // the start of the root's run is at bit h or h + 1 of its word: the one that is gas and
         // has no gas before it
-        const uint64_t W = bits[w], starts = W & ~(W << 1);
-        const int x = seg * kSeg + h + (int)(~(starts >> h) & 1ull);
+        const uint64_t W = bits[w], first = W & ~(W << 1);
+        const int x = seg * kSeg + h + (int)(~(first >> h) & 1ull);
         const uint32_t rr = (uint32_t)(y0 + w % T::RY) + (uint32_t)a.ny * (uint32_t)(z0 + w / T::RY);
         sc.parent[(size_t)r * sc.half + ((seg * kSeg + s) >> 1)] = code_of(rr, x, sc.half);
     }
 }
 
-// The links the tiles could not see, one word a thread: to the next segment, to rows of other
+// The links the tiles could not see, CROSS threads a word: to the next segment, to rows of other
 // tiles, and around the box.  Bound by the latency of the parents' loads, which go past the L2s
 // of the eight XCDs: both ends are followed together, and a pair of parents just united by this
 // thread is not looked up again.
-template <int Q>
+template <int Q, bool FINE>
 __global__ void __launch_bounds__(256) k_label_cross(uint32_t* scratch, int64_t words, FieldArgs a)
 {
-    using T = LabelTile<Q>;
+    using T = LabelTile<Q, FINE>;
     using R = RowLinks<Q>;
-    const int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, w = i / T::CROSS;
     if (w >= words) return;
+    const int part = (int)(i % T::CROSS);
     const LabelScratch sc = scratch_of(scratch, a);
     const uint64_t A = sc.words[w];
     if (!A) return;
+    const uint64_t starts = run_starts<T::CROSS>(A, part);
     const Seg g = seg_of(w, a);
     const uint32_t segs = (uint32_t)segs_of(a.nx), seg = (uint32_t)g.x0 / kSeg;
     const int last = g.width - 1;
-    const bool first_gas = A & 1ull, last_gas = A >> last & 1ull;
+    // the ends of the word: the first lane takes the links of both
+    const bool first_gas = part == 0 && (A & 1ull), last_gas = part == 0 && (A >> last & 1ull);
     const uint32_t sn = seg + 1 < segs ? seg + 1 : 0, sb = seg > 0 ? seg - 1 : segs - 1;
     const int wb = min(kSeg, a.nx - (int)sb * kSeg);  // width of the segment before
     uint32_t la = 0u, lb = 0u;
@@ -277,7 +284,7 @@ __global__ void __launch_bounds__(256) k_label_cross(uint32_t* scratch, int64_t 
         la = pa;
         lb = pb;
         have = true;
-        unite(sc.parent, pa, pb);
+        union_unite(GlobalParents{sc.parent}, pa, pb);
     };
     auto word = [&](uint32_t r, uint32_t s) { return sc.words[(size_t)r * segs + s]; };
     if (last_gas && (word(g.r, sn) & 1ull))
@@ -290,7 +297,7 @@ __global__ void __launch_bounds__(256) k_label_cross(uint32_t* scratch, int64_t 
         if (here && !(R::wide[d] && (first_gas || last_gas))) continue;
         const uint32_t r2 = (uint32_t)wrap_once(y, a.ny) + (uint32_t)a.ny * (uint32_t)wrap_once(z, a.nz);
         if (!here)
-            touching_runs(A, word(r2, seg), R::wide[d],
+            touching_runs(A, word(r2, seg), starts, R::wide[d],
                           [&](int sa, int sb2) { link(g.r, g.x0 + sa, r2, g.x0 + sb2); });
         if (!R::wide[d]) continue;
         if (last_gas && (word(r2, sn) & 1ull))
@@ -446,20 +453,36 @@ hipError_t mask_rho_any(int q, int storage, const void* f, uint32_t* scratch, do
     return hipGetLastError();
 }
 
+template <int Q, bool FINE>
+int64_t label_tiles(const FieldArgs& a)
+{
+    using T = LabelTile<Q, FINE>;
+    return (int64_t)segs_of(a.nx) * ((a.ny + T::RY - 1) / T::RY) * ((a.nz + T::RZ - 1) / T::RZ);
+}
+
+template <int Q, bool FINE>
+hipError_t unite_words(uint32_t* scratch, uint32_t* ncomp, int64_t words, const FieldArgs& a,
+                       hipStream_t st)
+{
+    using T = LabelTile<Q, FINE>;
+    const int64_t tiles = label_tiles<Q, FINE>(a), cross = (words * T::CROSS + 255) / 256;
+    if (tiles > 0x7fffffff || cross > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_label_local<Q, FINE>), dim3((unsigned)tiles),
+                       dim3(T::RY * T::RZ * T::PARTS), 0, st, scratch, ncomp, a);
+    hipLaunchKernelGGL((k_label_cross<Q, FINE>), dim3((unsigned)cross), dim3(256), 0, st, scratch,
+                       words, a);
+    return hipGetLastError();
+}
+
 template <int Q>
 hipError_t label_words(uint32_t* lab, uint32_t* scratch, uint32_t* ncomp, const FieldArgs& a,
                        hipStream_t st)
 {
-    using T = LabelTile<Q>;
     const int64_t words = words_of(a);
-    const int64_t tiles = (int64_t)segs_of(a.nx) * ((a.ny + T::RY - 1) / T::RY) *
-                          ((a.nz + T::RZ - 1) / T::RZ);
-    const int64_t cross = (words + 255) / 256;
-    if (tiles > 0x7fffffff || cross > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_label_local<Q>), dim3((unsigned)tiles), dim3(kTileWords), 0, st, scratch,
-                       ncomp, a);
-    hipLaunchKernelGGL((k_label_cross<Q>), dim3((unsigned)cross), dim3(256), 0, st, scratch, words,
-                       a);
+    const hipError_t e = label_tiles<Q, false>(a) <= 256
+                             ? unite_words<Q, true>(scratch, ncomp, words, a, st)
+                             : unite_words<Q, false>(scratch, ncomp, words, a, st);
+    if (e != hipSuccess) return e;
     // one word a wave while the waves do not fill the chip (its latencies are then the bound); few
     // enough blocks that their counts do not queue at the one counter
     const int fw = words < 16384 ? 1 : 4;

@@ -89,17 +89,25 @@ struct LdsParents {
     }
 };
 
+// The run starts of a word that fall to one of PARTS lanes: a word of a bubble has one run or two, one
+// of a fine mask up to 32, which a single lane would unite one after the other.
+template <int PARTS>
+__device__ __forceinline__ uint64_t run_starts(uint64_t w, int part)
+{
+    return w & ~(w << 1) & (~0ull >> (64 - kSeg / PARTS) << kSeg / PARTS * part);
+}
+
 // Calls link(sa, sb) once for every pair of touching runs of two adjacent rows: sa, sb the first
-// bits of the runs of words A and B; `wide` rows touch diagonally too.
+// bits of the runs of words A and B, sa among `starts`; `wide` rows touch diagonally too.
 template <typename F>
-__device__ __forceinline__ void touching_runs(uint64_t A, uint64_t B, bool wide, F link)
+__device__ __forceinline__ void touching_runs(uint64_t A, uint64_t B, uint64_t starts, bool wide,
+                                              F link)
 {
     const uint64_t reach = wide ? (A | A << 1 | A >> 1) : A;
     if (!(reach & B)) return;
-    for (uint64_t left = A; left;) {
-        const int sa = __ffsll((long long)left) - 1;
+    for (; starts; starts &= starts - 1) {
+        const int sa = __ffsll((long long)starts) - 1;
         const uint64_t run = run_at(A, sa);
-        left &= ~run;
         uint64_t hit = B & (wide ? (run | run << 1 | run >> 1) : run);
         while (hit) {
             const int sb = run_start(B, __ffsll((long long)hit) - 1);

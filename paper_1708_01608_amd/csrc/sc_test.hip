@@ -1178,7 +1178,7 @@ __global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
         for (int d = 0; d < R::n; ++d) {
             const int r2 = (wrap_once(g.y + R::dy[d], a.ny) +
                             a.ny * wrap_once(g.z + R::dz[d], a.nz)) * segs;
-            touching_runs(A, bits[r2 + seg], R::wide[d],
+            touching_runs(A, bits[r2 + seg], A & ~(A << 1), R::wide[d],
                           [&](int x, int y) { unite(w, x, r2 + seg, y); });
             if (!R::wide[d]) continue;
             if (last_gas && (bits[r2 + sn] & 1ull)) unite(w, run_start(A, last), r2 + sn, 0);

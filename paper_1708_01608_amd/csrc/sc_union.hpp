@@ -26,13 +26,23 @@ __device__ __forceinline__ uint32_t union_root_halving(M m, uint32_t x)
     }
 }
 
+// Joins the sets of a and b.  Both ends are followed together, so that their loads are in flight at
+// once, and both paths are halved: where many links join one large set, the roots of its parts form
+// long chains.
 template <typename M>
 __device__ __forceinline__ void union_unite(M m, uint32_t a, uint32_t b)
 {
     while (true) {
-        a = union_root_halving(m, a);
-        b = union_root_halving(m, b);
-        if (a == b) return;
+        while (true) {
+            if (a == b) return;
+            const uint32_t pa = m.load(a), pb = m.load(b);
+            if (pa == a && pb == b) break;
+            const uint32_t ga = m.load(pa), gb = m.load(pb);
+            if (pa != a && ga != pa) m.store(a, ga);
+            if (pb != b && gb != pb) m.store(b, gb);
+            a = ga;
+            b = gb;
+        }
         if (a > b) { const uint32_t t = a; a = b; b = t; }
         const uint32_t old = m.min(b, a);
         if (old == b) return;

@@ -175,6 +175,19 @@ int main()
                     &orders);
                 report("unite", a, b, bad, orders);
             }
+    // two unions that halve a path while they meet at its end
+    {
+        const long bad = wrong_orders(
+            Parents{0, 0, 1, 3},
+            {[](Mem m) { sc::union_unite(m, 2, 3); }, [](Mem m) { sc::union_unite(m, 3, 2); }},
+            [](const Parents& p) {
+                bool good = true;
+                for (uint32_t i = 0; i < 4; ++i) good = good && root_of(p, i) == 0;
+                return good;
+            },
+            &orders);
+        report("halve", 2, 3, bad, orders);
+    }
     std::printf("%ld orders, %ld cases wrong\n", total, failed);
     return failed ? 1 : 0;
 }

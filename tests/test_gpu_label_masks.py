@@ -42,3 +42,10 @@ def test_many_components_do_not_queue_at_the_counter():
     # 65,536 words hold single nodes: with an atomic a wave, 290 us of a 395 us call
     empty, thin = _times(19, (4, 512, 512), (0.0, 0.02))
     assert thin < 2.5 * empty
+
+
+@pytest.mark.parametrize("q,shape,most", [(9, (4096, 130, 1), 4.0), (19, (64, 64, 64), 6.5)])
+def test_fine_masks_are_not_walked_by_one_lane_a_word(q, shape, most):
+    # 60% of the nodes at random: up to 32 runs a word, one set all over the box
+    empty, fine = _times(q, shape, (0.0, 0.6))
+    assert fine < most * empty
