@@ -53,31 +53,61 @@ struct LabelTile<19, true> {
 };
 
 // ---- mask words ----------------------------------------------------------------------------------
-// A wave takes kMaskWords segments a turn, loads first.
+// Rows of at most 32 nodes leave most of a wave idle if it takes them one by one, so NARROW packs as
+// many as fit: the lanes of a wave are `rows` rows of 2^lg lanes.  Microseconds a call, one row and
+// several a wave: 4 x 512 x 512 from the density 125 -> 46, from bytes (balls) 74 -> 43, test pass
+// 133 -> 41; 16 x 256 x 256 55 -> 45, 58 -> 54, 53 -> 41.
+struct Lanes {
+    int lg, rows, sub, x;  // rows a wave takes at once, and this lane's row and column
+};
+template <bool NARROW>
+__device__ __forceinline__ Lanes lanes_of(int nx)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    if (!NARROW) return Lanes{6, 1, 0, lane};
+    const int lg = 32 - __clz(nx - 1);
+    return Lanes{lg, kSeg >> lg, lane >> lg, lane & ((1 << lg) - 1)};
+}
+// The word of row `sub` out of a wave's ballot.
+__device__ __forceinline__ uint64_t word_of_row(uint64_t ballot, int sub, int lg)
+{
+    return ballot >> (sub << lg) & below(1 << lg);
+}
+
+// A wave takes kMaskWords segments (or groups of rows) a turn, loads first.
 constexpr int kMaskWords = 8;
 
+template <bool NARROW>
 __global__ void __launch_bounds__(256) k_mask_bytes(const uint8_t* __restrict__ mask,
                                                     uint64_t* __restrict__ out, int64_t words,
                                                     FieldArgs a)
 {
     const int lane = (int)(threadIdx.x & 63);
+    const Lanes ln = lanes_of<NARROW>(a.nx);
     const int64_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 4 * (int64_t)blockIdx.x;
-    for (int64_t w0 = wave * kMaskWords; w0 < words; w0 += 4 * (int64_t)gridDim.x * kMaskWords) {
+    const int64_t step = kMaskWords * ln.rows;
+    for (int64_t w0 = wave * step; w0 < words; w0 += 4 * (int64_t)gridDim.x * step) {
         bool gas[kMaskWords];
 #pragma unroll
         for (int u = 0; u < kMaskWords; ++u) {
             gas[u] = false;
-            if (w0 + u >= words) continue;
-            const Seg g = seg_of(w0 + u, a);
-            if (lane < g.width) gas[u] = mask[g.n + lane] != 0;
+            const int64_t w = w0 + u * ln.rows + ln.sub;
+            if (w >= words) continue;
+            const Seg g = seg_of(w, a);
+            if (ln.x < g.width) gas[u] = mask[g.n + ln.x] != 0;
         }
         uint64_t mine = 0ull;
 #pragma unroll
         for (int u = 0; u < kMaskWords; ++u) {
             const uint64_t m = __ballot(gas[u]);
-            if (lane == u) mine = m;
+            if (NARROW) {
+                const int64_t w = w0 + u * ln.rows + lane;
+                if (lane < ln.rows && w < words) out[w] = word_of_row(m, lane, ln.lg);
+            } else if (lane == u) {
+                mine = m;
+            }
         }
-        if (lane < kMaskWords && w0 + lane < words) out[w0 + lane] = mine;
+        if (!NARROW && lane < kMaskWords && w0 + lane < words) out[w0 + lane] = mine;
     }
 }
 
@@ -117,7 +147,7 @@ __device__ __forceinline__ double wave_sum(double v)
 // block the sums of the pulled values and their momenta: the pulled values are a permutation of the
 // stored ones, so these are the totals of the populations.  Two segments a turn, loads of both
 // first (one wave carries many, and would otherwise wait out a full memory latency each).
-template <int Q, typename S, bool TOTALS>
+template <int Q, typename S, bool TOTALS, bool NARROW>
 __global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
                                                   uint64_t* __restrict__ out,
                                                   double* __restrict__ partials, int64_t words,
@@ -127,15 +157,19 @@ __global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
     const int lane = (int)(threadIdx.x & 63);
     const int64_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 4 * (int64_t)blockIdx.x;
     double m = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-    for (int64_t w0 = wave * 2; w0 < words; w0 += 8 * (int64_t)gridDim.x) {
+    const Lanes ln = lanes_of<NARROW>(a.nx);
+    for (int64_t w0 = wave * 2 * ln.rows; w0 < words; w0 += 8 * (int64_t)gridDim.x * ln.rows) {
         float g[2][Q];
-        Seg sg[2];
+        bool on[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (w0 + u >= words) continue;
-            sg[u] = seg_of(w0 + u, a);
-            const int x = sg[u].x0 + lane, y = sg[u].y, z = sg[u].z;
-            if (lane < sg[u].width)
+            const int64_t w = w0 + u * ln.rows + ln.sub;
+            on[u] = false;
+            if (w >= words) continue;
+            const Seg sg = seg_of(w, a);
+            const int x = sg.x0 + ln.x, y = sg.y, z = sg.z;
+            on[u] = ln.x < sg.width;
+            if (on[u])
                 pull_node<Q>(f, a.N, a.nx, a.ny, x, wrap_once(x - 1, a.nx), wrap_once(x + 1, a.nx),
                              y, wrap_once(y - 1, a.ny), wrap_once(y + 1, a.ny), z,
                              Q == 19 ? wrap_once(z - 1, a.nz) : 0,
@@ -143,9 +177,9 @@ __global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (w0 + u >= words) continue;
+            if (w0 + u * ln.rows >= words) continue;
             bool gas = false;
-            if (lane < sg[u].width) {
+            if (on[u]) {
                 double s = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
@@ -163,7 +197,12 @@ __global__ void __launch_bounds__(256) k_mask_rho(const S* __restrict__ f,
                 jz += sz;
             }
             const uint64_t mask = __ballot(gas);
-            if (lane == 0) out[w0 + u] = mask;
+            if (NARROW) {
+                const int64_t w = w0 + u * ln.rows + lane;
+                if (lane < ln.rows && w < words) out[w] = word_of_row(mask, lane, ln.lg);
+            } else if (lane == 0) {
+                out[w0 + u] = mask;
+            }
         }
     }
     if constexpr (TOTALS) {
@@ -316,39 +355,52 @@ constexpr int kFlatBlocks = 2048;
 
 // Labels from the words and the parents.  Bound by the write of the labels; most segments hold no
 // gas and are filled with zeros at once, the others' walks to their roots go side by side.
-template <int FW>
+template <int FW, bool NARROW>
 __global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ lab,
                                                        uint32_t* scratch, uint32_t* ncomp,
                                                        int64_t words, FieldArgs a)
 {
     const LabelScratch sc = scratch_of(scratch, a);
     const int lane = (int)(threadIdx.x & 63);
+    const Lanes ln = lanes_of<NARROW>(a.nx);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) + 4 * (int)blockIdx.x);
     const uint32_t segs = (uint32_t)segs_of(a.nx);
     unsigned roots = 0;
-    for (int64_t w0 = (int64_t)wave * FW; w0 < words; w0 += 4 * (int64_t)gridDim.x * FW) {
+    const int64_t step = FW * ln.rows;
+    for (int64_t w0 = (int64_t)wave * step; w0 < words; w0 += 4 * (int64_t)gridDim.x * step) {
         uint64_t A[FW];
-#pragma unroll
-        for (int u = 0; u < FW; ++u) A[u] = w0 + u < words ? sc.words[w0 + u] : 0ull;
-#pragma unroll
-        for (int u = 0; u < FW; ++u)  // the same in every lane: scalar, so that its tests are branches
-            A[u] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)A[u]) |
-                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(A[u] >> 32)) << 32;
         // row and first column of the segments, and where their labels start
         uint32_t row[FW];
         int x0[FW];
-        uint32_t rr = __builtin_amdgcn_readfirstlane((uint32_t)w0 / segs);
-        uint32_t ss = (uint32_t)w0 - rr * segs;
         bool any = false;
+        if constexpr (NARROW) {  // a row a lane group: one segment each
 #pragma unroll
-        for (int u = 0; u < FW; ++u) {
-            row[u] = rr;
-            x0[u] = (int)ss * kSeg;
-            if (++ss == segs) {
-                ss = 0;
-                ++rr;
+            for (int u = 0; u < FW; ++u) {
+                const int64_t w = w0 + u * ln.rows + ln.sub;
+                A[u] = w < words ? sc.words[w] : 0ull;
+                row[u] = (uint32_t)w;
+                x0[u] = 0;
+                any |= A[u] != 0ull;
             }
-            any |= A[u] != 0ull;
+        } else {
+#pragma unroll
+            for (int u = 0; u < FW; ++u) A[u] = w0 + u < words ? sc.words[w0 + u] : 0ull;
+#pragma unroll
+            for (int u = 0; u < FW; ++u)  // the same in every lane: scalar, so that its tests are branches
+                A[u] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)A[u]) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(A[u] >> 32)) << 32;
+            uint32_t rr = __builtin_amdgcn_readfirstlane((uint32_t)w0 / segs);
+            uint32_t ss = (uint32_t)w0 - rr * segs;
+#pragma unroll
+            for (int u = 0; u < FW; ++u) {
+                row[u] = rr;
+                x0[u] = (int)ss * kSeg;
+                if (++ss == segs) {
+                    ss = 0;
+                    ++rr;
+                }
+                any |= A[u] != 0ull;
+            }
         }
         uint32_t v[FW];
 #pragma unroll
@@ -361,7 +413,7 @@ __global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ la
                 r[u] = 0u;
                 s[u] = 0;
                 if (!A[u]) continue;
-                s[u] = run_start(A[u], lane);
+                s[u] = run_start(A[u], ln.x);
                 r[u] = code_of(row[u], x0[u] + s[u], sc.half);
             }
             bool more = true;
@@ -371,7 +423,7 @@ __global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ la
 #pragma unroll
                 for (int u = 0; u < FW; ++u) {
                     p[u] = r[u];
-                    if (A[u] && (A[u] >> lane & 1ull)) p[u] = sc.parent[r[u] >> 1];
+                    if (A[u] && (A[u] >> ln.x & 1ull)) p[u] = sc.parent[r[u] >> 1];
                 }
 #pragma unroll
                 for (int u = 0; u < FW; ++u) {
@@ -381,15 +433,15 @@ __global__ void __launch_bounds__(256) k_label_flatten(uint32_t* __restrict__ la
             }
 #pragma unroll
             for (int u = 0; u < FW; ++u) {
-                if (!A[u] || !(A[u] >> lane & 1ull)) continue;
+                if (!A[u] || !(A[u] >> ln.x & 1ull)) continue;
                 v[u] = node_of_code(r[u], sc.half, a.nx) + 1;
-                if (s[u] == lane && r[u] == code_of(row[u], x0[u] + lane, sc.half)) ++roots;
+                if (s[u] == ln.x && r[u] == code_of(row[u], x0[u] + ln.x, sc.half)) ++roots;
             }
         }
 #pragma unroll
         for (int u = 0; u < FW; ++u)
-            if (w0 + u < words && x0[u] + lane < a.nx)
-                lab[(int64_t)row[u] * a.nx + x0[u] + lane] = v[u];
+            if (w0 + u * ln.rows + ln.sub < words && x0[u] + ln.x < a.nx)
+                lab[(int64_t)row[u] * a.nx + x0[u] + ln.x] = v[u];
     }
     // one atomic a block that found any
 #pragma unroll
@@ -422,6 +474,14 @@ __global__ void __launch_bounds__(256) k_totals_final(const double* __restrict__
     if (lane == 0) out[c] = (c == 0) ? base_mass + s : s;
 }
 
+bool narrow_rows(const FieldArgs& a) { return a.nx <= kSeg / 2; }
+int rows_a_wave(const FieldArgs& a)  // as lanes_of
+{
+    int p = 1;
+    while (p < a.nx && p < kSeg) p *= 2;
+    return kSeg / p;
+}
+
 int64_t words_of(const FieldArgs& a) { return (int64_t)segs_of(a.nx) * a.ny * a.nz; }
 
 dim3 word_grid(int64_t words, int per_block)
@@ -434,8 +494,12 @@ template <int Q, typename S, bool TOTALS>
 void mask_rho(const void* f, uint32_t* scratch, double* partials, int nb, const FieldArgs& a,
               hipStream_t st)
 {
-    hipLaunchKernelGGL((k_mask_rho<Q, S, TOTALS>), dim3(nb), dim3(256), 0, st, (const S*)f,
-                       scratch_of(scratch, a).words, partials, words_of(a), a);
+    if (narrow_rows(a))
+        hipLaunchKernelGGL((k_mask_rho<Q, S, TOTALS, true>), dim3(nb), dim3(256), 0, st,
+                           (const S*)f, scratch_of(scratch, a).words, partials, words_of(a), a);
+    else
+        hipLaunchKernelGGL((k_mask_rho<Q, S, TOTALS, false>), dim3(nb), dim3(256), 0, st,
+                           (const S*)f, scratch_of(scratch, a).words, partials, words_of(a), a);
 }
 
 template <bool TOTALS>
@@ -485,12 +549,18 @@ hipError_t label_words(uint32_t* lab, uint32_t* scratch, uint32_t* ncomp, const 
     if (e != hipSuccess) return e;
     // one word a wave while the waves do not fill the chip (its latencies are then the bound); few
     // enough blocks that their counts do not queue at the one counter
-    const int fw = words < 16384 ? 1 : 4;
-    const dim3 grid((unsigned)std::min<int64_t>((words + 4 * fw - 1) / (4 * fw), kFlatBlocks));
-    if (fw == 1)
-        hipLaunchKernelGGL(k_label_flatten<1>, grid, dim3(256), 0, st, lab, scratch, ncomp, words, a);
+    const bool narrow = narrow_rows(a);
+    const int64_t turns = (words + rows_a_wave(a) - 1) / rows_a_wave(a);
+    const int fw = turns < 16384 ? 1 : 4;
+    const dim3 grid((unsigned)std::min<int64_t>((turns + 4 * fw - 1) / (4 * fw), kFlatBlocks)), block(256);
+    if (narrow && fw == 1)
+        hipLaunchKernelGGL((k_label_flatten<1, true>), grid, block, 0, st, lab, scratch, ncomp, words, a);
+    else if (narrow)
+        hipLaunchKernelGGL((k_label_flatten<4, true>), grid, block, 0, st, lab, scratch, ncomp, words, a);
+    else if (fw == 1)
+        hipLaunchKernelGGL((k_label_flatten<1, false>), grid, block, 0, st, lab, scratch, ncomp, words, a);
     else
-        hipLaunchKernelGGL(k_label_flatten<4>, grid, dim3(256), 0, st, lab, scratch, ncomp, words, a);
+        hipLaunchKernelGGL((k_label_flatten<4, false>), grid, block, 0, st, lab, scratch, ncomp, words, a);
     return hipGetLastError();
 }
 
@@ -537,8 +607,11 @@ hipError_t launch_mask_from_bytes(const uint8_t* mask_d, uint32_t* scratch, cons
     if (a.nx % kSeg == 0 && (uintptr_t)mask_d % 16 == 0)
         hipLaunchKernelGGL(k_mask_bytes16, word_grid(words, 64), dim3(256), 0, st,
                            (const uint4*)mask_d, scratch_of(scratch, a).words, words);
+    else if (narrow_rows(a))
+        hipLaunchKernelGGL(k_mask_bytes<true>, word_grid(words, 4 * kMaskWords * rows_a_wave(a)),
+                           dim3(256), 0, st, mask_d, scratch_of(scratch, a).words, words, a);
     else
-        hipLaunchKernelGGL(k_mask_bytes, word_grid(words, 4 * kMaskWords), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_mask_bytes<false>, word_grid(words, 4 * kMaskWords), dim3(256), 0, st,
                            mask_d, scratch_of(scratch, a).words, words, a);
     return hipGetLastError();
 }
