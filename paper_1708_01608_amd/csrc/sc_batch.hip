@@ -25,7 +25,7 @@
 namespace sc {
 
 constexpr int kBatchThreads = 256;  // of a workgroup, and the widest box
-constexpr int kWideThreads = 768;   // of a workgroup when the boxes are few (batch_threads)
+constexpr int kWideThreads = 768;   // of a workgroup when the boxes are few (batch_shape)
 constexpr uint32_t kNone = 0xffffffffu;
 
 struct BatchInst {
@@ -665,6 +665,15 @@ __device__ bool batch_test(const float* f, uint32_t* par, const BatchInst& in, i
 // workgroup leaves latency to hide, so with one slot the registers are capped for three waves (a
 // few spills; the rings' 53 KB of LDS allow three workgroups of 256 a CU too, or one of 768);
 // more slots need two.
+//
+// A sweep of two steps takes six intervals beside those of the rows, so a box of few row blocks is
+// better off with single steps: from kTwoBlocks blocks on it takes two.  200 steps with a pass every
+// 10, one step and two a sweep: 768 threads, 512 boxes of 32^2 (2 blocks) 2.0 / 3.0 ms, 64^2 (6) 4.2
+// / 5.1, 96^2 (12) 7.2 / 7.4, 2,000 boxes of 96^2 13.3 / 13.0; 256 threads, 2,000 boxes of 16^2 (1)
+// 3.1 / 3.3, 32^2 (4) 3.7 / 3.6, with FP32 arithmetic 2.9 / 1.9 and 3.3 / 2.4.
+template <typename A, int NTH>
+constexpr int kTwoBlocks = NTH == kWideThreads ? 12 : (sizeof(A) == 8 ? 4 : 1);
+
 template <typename A, int RB, int NTH>
 __global__ void __launch_bounds__(NTH, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
 {
@@ -704,11 +713,13 @@ __global__ void __launch_bounds__(NTH, RB == 1 ? 3 : 2) k_batch(BatchArgs b)
         bool stop = batch_test<NTH>(f0, par, in, b.K, b.film_max, 0, false, o, sh);
         int cur = 0;
         int64_t step = 0;
+        const int rows = max(1, NTH / in.nx);  // (the wave's: see `stop`)
+        const int blocks = __builtin_amdgcn_readfirstlane((in.ny + rows - 1) / rows);
         while (!stop && step < b.max_steps) {
             // two steps a sweep up to the next test pass, a last odd one by itself
             bool two = false;
             if constexpr (RB == 1)
-                two = step + 2 <= b.max_steps && (b.K <= 0 || step % b.K + 2 <= b.K);
+                two = blocks >= kTwoBlocks<A, NTH> && step + 2 <= b.max_steps && (b.K <= 0 || step % b.K + 2 <= b.K);
             float* const from = wave_pointer(cur ? f1 : f0);
             float* const to = wave_pointer(cur ? f0 : f1);
             if (two)
@@ -751,7 +762,7 @@ struct sc_batch {
     int n = 0;
     int K = 10, film_max = 8, max_steps = 5000, compute = SC_COMPUTE_F64;
     int rb = 1;  // rows per thread per iteration of the box step
-    int threads = kBatchThreads;  // of a workgroup of the one-slot kernel
+    int threads = kBatchThreads;  // of a workgroup of the one-slot kernel (batch_shape)
     hipStream_t stream = nullptr;
     bool own_stream = false;
     sc_allocator alloc{};
@@ -805,22 +816,30 @@ void brelease(sc_batch* b)
 
 namespace {
 
-// Threads of a workgroup of the one-slot kernel, by the number of boxes.  Three workgroups of 256
-// or one of 768 fill a CU (three waves a SIMD, the registers' and the LDS's limit), and then the
-// FP64 pipe is the bound of both.  With few boxes a CU has fewer than three, and the run ends when
-// the largest box does: the wide workgroup advances that one faster.  With many boxes the narrow
-// one wins by its shorter pipeline (nblk + 6 intervals a sweep, nblk = ny / rows).  Measured, 200
-// steps with a pass every 10, 256 against 768 threads (ms, FP64 | FP32 arithmetic): 32 boxes 49 /
-// 31 | 44 / 22; 512 60 / 37 | 56 / 30; 1024 74 / 57; 1536 87.3 / 84.7; 2048 110 / 110 | 97 / 93;
-// 4096 201 / 214 | 183 / 182.  384 and 512 threads were slower than the better of the two
-// everywhere (164 and 123 ms at 2048).
-int batch_threads(int n)
+// Slots a lane and threads of a workgroup, by the number of boxes and the nodes of the largest.
+// Three workgroups of 256 or one of 768 fill a CU (three waves a SIMD, the registers' and the LDS's
+// limit), and then the FP64 pipe is the bound of both.  With few boxes a CU has fewer than three,
+// and the run ends when the largest box does: the wide workgroup advances that one faster.  With
+// many boxes the narrow one wins by its shorter pipeline (nblk + 6 intervals a sweep, nblk = ny /
+// rows).  Measured, 200 steps with a pass every 10, 256 against 768 threads (ms, FP64 | FP32
+// arithmetic): boxes of 64 .. 256 a side, 32 of them 49 / 31 | 44 / 22; 512 60 / 37 | 56 / 30; 1024
+// 74 / 57; 1536 87.3 / 84.7; 2048 110 / 110 | 97 / 93; 4096 201 / 214 | 183 / 182.  384 and 512
+// threads were slower than the better of the two everywhere (164 and 123 ms at 2048).  Boxes of up
+// to 48^2 are a few row blocks: the narrow one as soon as there is more than one a CU (512 of 48^2
+// 0.32 / 0.42).  The smallest are one block, and the latency of a step is all: two slots a lane, of
+// which the compiler interleaves the loads and which no register cap makes spill (4 to 64 boxes of
+// 16^2, one slot and two 0.84 / 0.72, 512 of 32^2 2.2 / 2.0; 2,000 of 16^2 3.1 / 2.1, of 32^2 3.6 / 4.3).
+struct BatchShape {
+    int rb, threads;
+};
+BatchShape batch_shape(int n, int64_t nodes)
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return kBatchThreads;
-    return n <= 6 * cus ? kWideThreads : kBatchThreads;
+        return BatchShape{1, kBatchThreads};
+    if (nodes <= 24 * 24 || (nodes <= 32 * 32 && n <= 3 * cus)) return BatchShape{2, kBatchThreads};
+    return BatchShape{1, n <= (nodes <= 48 * 48 ? 1 : 6) * cus ? kWideThreads : kBatchThreads};
 }
 
 hipError_t batch_occupancy(int compute, int rb, int threads, int* per_cu)
@@ -899,13 +918,13 @@ int sc_batch_create(int32_t n, const sc_batch_instance* inst, int32_t test_every
     b->film_max = film_max;
     b->max_steps = max_steps;
     b->compute = compute == SC_COMPUTE_F32 ? SC_COMPUTE_F32 : SC_COMPUTE_F64;
-    b->threads = batch_threads(n);
     if (allocator) {
         b->alloc = *allocator;
         b->has_alloc = true;
     }
     b->inst.resize(n);
     size_t off = 0, loff = 0;
+    int64_t largest = 0;
     for (int k = 0; k < n; ++k) {
         const sc_batch_instance& I = inst[k];
         BatchInst& d = b->inst[k];
@@ -925,7 +944,11 @@ int sc_batch_create(int32_t n, const sc_batch_instance* inst, int32_t test_every
         off += 2 * 9 * N;
         off = (off + 63) & ~size_t(63);  // 256-byte aligned buffers
         loff += (N + 63) & ~size_t(63);
+        largest = std::max(largest, (int64_t)N);
     }
+    const BatchShape shape = batch_shape(n, largest);
+    b->rb = shape.rb;
+    b->threads = shape.threads;
     b->pool_floats = off;
     b->lab_count = loff;
     // largest boxes first: the queue order of a longest-first schedule
