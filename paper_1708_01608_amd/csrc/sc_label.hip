@@ -30,14 +30,15 @@ namespace {
 
 // Rows of a tile, and the lanes a word is split over in the two kernels that unite.  FINE: where the
 // tiles do not fill the chip, its lanes would idle while one walks the up to 32 runs of a word of a
-// fine mask (random masks, microseconds a call, coarse and fine: 64^3 30% gas 149 -> 100, 1000^2
-// 60% 214 -> 94); on large boxes the idle lanes of words with a run or two cost more than they
-// give (256^3, 200 balls: 2, 4 and 8 lanes a word 110, 119, 133).
+// fine mask (random masks, microseconds a call, a lane a word and so: 64^3 30% gas 250 -> 94, 1000^2
+// 60% 218 -> 94); on large boxes the idle lanes of words with a run or two cost more than they give
+// (256^3, 200 balls, lanes in the tiles and between them: 2 and 1 107 us, 2 and 2 110, 4 and 2 118,
+// 4 and 8 133).
 template <int Q, bool FINE>
 struct LabelTile;
 template <>
 struct LabelTile<9, false> {
-    static constexpr int RY = 256, RZ = 1, PARTS = 2, CROSS = 2;
+    static constexpr int RY = 256, RZ = 1, PARTS = 2, CROSS = 1;
 };
 template <>
 struct LabelTile<9, true> {
@@ -45,7 +46,7 @@ struct LabelTile<9, true> {
 };
 template <>
 struct LabelTile<19, false> {
-    static constexpr int RY = 16, RZ = 16, PARTS = 2, CROSS = 2;
+    static constexpr int RY = 16, RZ = 16, PARTS = 2, CROSS = 1;
 };
 template <>
 struct LabelTile<19, true> {

@@ -138,7 +138,7 @@ struct RowLinks<19> {
 // Per-node contributions to per-bubble counters arrive from many nodes of the same bubble at
 // once; one atomic per node onto a few hundred addresses serialises.  The lanes of a wave that
 // carry the same key (a bubble slot, >= 0) sum their values with a butterfly and one lane adds the
-// sum: one atomic per distinct key per wave.  Integer sums, so the result does not depend on the
+// sum: one atomic per key and wave.  Integer sums, so the result does not depend on the
 // grouping.  Every lane of the wave must call these (the loops below are wave-uniform).
 __device__ __forceinline__ long long wave_sum_i64(long long v)
 {
@@ -147,21 +147,32 @@ __device__ __forceinline__ long long wave_sum_i64(long long v)
     return v;
 }
 
-template <int M, typename Flush>
+// Where a wave meets many bubbles, one after the other is a long serial chain (a butterfly of four
+// sums some 0.5 us), and few of its atomics meet on one address anyway: keys of up to FEW lanes, and
+// all behind the first TURNS, add lane by lane.
+template <int M, int FEW = 0, int TURNS = 64, typename Flush>
 __device__ __forceinline__ void wave_add_by_key(int key, const long long (&v)[M], Flush flush)
 {
     const int lane = (int)(threadIdx.x & 63);
     unsigned long long pending = __ballot(key >= 0);
-    while (pending) {
+    for (int turn = 0; pending; ++turn) {
+        if (TURNS < 64 && turn == TURNS) {
+            if (pending >> lane & 1ull) flush(key, v);
+            return;
+        }
         const int leader = __ffsll(pending) - 1;
         const int k = __shfl(key, leader, 64);
         const bool mine = key == k;
         const unsigned long long grp = __ballot(mine);
+        pending &= ~grp;
+        if (FEW > 0 && __popcll(grp) <= FEW) {
+            if (mine) flush(k, v);
+            continue;
+        }
         long long sum[M];
 #pragma unroll
         for (int j = 0; j < M; ++j) sum[j] = wave_sum_i64(mine ? v[j] : 0ll);
         if (lane == leader) flush(k, sum);
-        pending &= ~grp;
     }
 }
 
@@ -188,9 +199,12 @@ __device__ __forceinline__ void run_stats(int x, int y, int z, int len, const in
     v[3] = (long long)len * min_image_i(z - anchor[2], a.nz);
 }
 
-// Adds the runs of one word a lane (A: 0 for none) to their bubbles' counters, one atomic per bubble
-// and wave and round; slot(s) is the bubble of the run that starts at bit s, or negative.
-template <typename F>
+// Adds the runs of one word a lane (A: 0 for none) to their bubbles' counters; slot(s) is the bubble
+// of the run that starts at bit s, or negative.  FEW and TURNS as above: in a box of many small
+// bubbles that one block goes through, the chain is all (128^2 with 102 bubbles, a pass 235 us with
+// every key in turn, 181 with 4 and 4, 201 with 1 and 8); large boxes hold few bubbles a wave, and
+// their atomics count (512 x 512 x 256, 300 bubbles of R = 25: 1,915, 2,025, 1,880 us).
+template <int FEW, int TURNS, typename F>
 __device__ __forceinline__ void word_stats(uint64_t A, const Seg& g, const int32_t* anchors,
                                            unsigned long long* count, unsigned long long* sums,
                                            const FieldArgs& a, F slot)
@@ -206,7 +220,7 @@ __device__ __forceinline__ void word_stats(uint64_t A, const Seg& g, const int32
             if (b >= 0) run_stats(g.x0 + s, g.y, g.z, __popcll(run), anchors + 3 * b, a, v);
         }
         // two's-complement wrap-around makes unsigned adds exact signed sums
-        wave_add_by_key<4>(b, v, [&](int k, const long long* s) {
+        wave_add_by_key<4, FEW, TURNS>(b, v, [&](int k, const long long* s) {
             const size_t o = (size_t)k * kStatStride;
             atomicAdd(count + o, (unsigned long long)s[0]);
             atomicAdd(sums + o + 0, (unsigned long long)s[1]);

@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(256) k_stats(const uint32_t* __restrict__ labe
     const uint64_t A = w < words ? mask[w] : 0ull;
     if (!__ballot(A != 0ull)) return;
     const Seg g = seg_of(w < words ? w : 0, a);
-    word_stats(A, g, anchors, count, sums, a,
+    word_stats<1, 8>(A, g, anchors, count, sums, a,
                [&](int s) { return slot_of_root[labels[g.n + s] - 1]; });
 }
 
@@ -1232,7 +1232,7 @@ __global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
     for (int w0 = t - lane; w0 < words; w0 += 1024) {  // whole waves: the sums are by wave
         const int w = w0 + lane;
         const Seg g = seg_of(w < words ? w : 0, a);
-        word_stats(w < words ? bits[w] : 0ull, g, p.tab.anchors, p.tab.count, p.tab.sums, a,
+        word_stats<4, 4>(w < words ? bits[w] : 0ull, g, p.tab.anchors, p.tab.count, p.tab.sums, a,
                    [&](int s) { return p.slot_of_root[labels[g.n + s] - 1]; });
     }
     __threadfence();  // the counters were summed past this CU's cache
