@@ -317,58 +317,83 @@ StepShape default_shape(const sc_params& p)
     return sh;
 }
 
-// Estimated time (us) of one D3Q19 step launch with this tile: rounds of resident blocks, each
-// marching its planes (and the prologue's) at the slowest of the plane latency, the memory
-// traffic and the arithmetic of a round's blocks.  The constants were fitted to the measured
+// Estimated time (us) of one D3Q19 step launch with this tile, by planes a block: rounds of resident
+// blocks, each marching its planes (and the prologue's) at the slowest of the plane latency, the
+// memory traffic and the arithmetic of a round's blocks.  The constants were fitted to the measured
 // times of some 8,000 shapes on 25 boxes of 48^3 to 300 x 200 x 100 and 256^3, one and two
 // components, FP32 and 16-bit storage, and 13,000 on 14 boxes from 32 nodes wide on: the shape it
 // picks is on average 1 to 3% slower than the fastest of those measured (one component, at worst 16%).
-double shape3d_cost(const sc_params& p, int compute, const StepShape& s)
-{
-    const bool mix = p.components == 2, f64 = compute == SC_COMPUTE_F64;
-    const bool nt = s.variant == 3 || s.variant == 5;
-    const double es = (double)storage_bytes(p.storage), pops = mix ? 38 : 19;
-    const int tw = s.tile_x, th = s.tile_y;
-    const int waves = (tw * th + 63) / 64, ring_waves = (2 * (tw + 2) + 2 * th + 63) / 64;
-    const int bw = mix ? 2 * waves : waves;
-    int res = std::max(1, 16 / bw);  // blocks a CU holds: 16 waves of at most 128 registers
-    if (mix) {
-        const size_t lds = mix3d_split_lds(tw, th, f64 ? sizeof(double) : sizeof(float));
-        res = std::max(1, std::min(res, (int)((size_t)160 * 1024 / lds)));
+// (What does not depend on the planes is formed once a tile: sc_create tries some ten thousand
+// shapes.  300 x 9 x 300 313 -> 29 us of host time, 203 x 150 x 121 122 -> 28.)
+class Shape3dCost {
+public:
+    Shape3dCost(const sc_params& p, int compute, int tw, int th, int variant)
+    {
+        const bool f64 = compute == SC_COMPUTE_F64;
+        mix = p.components == 2;
+        nt = variant == 3 || variant == 5;
+        es = (double)storage_bytes(p.storage);
+        pops = mix ? 38 : 19;
+        waves = (tw * th + 63) / 64;
+        const int ring_waves = (2 * (tw + 2) + 2 * th + 63) / 64;
+        const int bw = mix ? 2 * waves : waves;
+        int res = std::max(1, 16 / bw);  // blocks a CU holds: 16 waves of at most 128 registers
+        if (mix) {
+            const size_t lds = mix3d_split_lds(tw, th, f64 ? sizeof(double) : sizeof(float));
+            res = std::max(1, std::min(res, (int)((size_t)160 * 1024 / lds)));
+        }
+        tiles = (uint32_t)((p.nx + tw - 1) / tw) * (uint32_t)((p.ny + th - 1) / th);
+        slots = 256u * (uint32_t)res;
+        // beyond what the last-level cache holds, stores that bypass L2 pay; rows that start and end
+        // inside a cache line cost the shared line again, for such stores most of all
+        resident = (double)p.nx * p.ny * p.nz * 2 * pops * es < 230e6;
+        const int bytes_el = (int)storage_bytes(p.storage);
+        aligned = (int64_t)p.nx * bytes_el % 128 == 0 && tw * bytes_el % 128 == 0;
+        const double edge_ld = aligned ? 0.0 : 0.65 * 128;
+        const double edge_st = aligned ? 0.0 : (nt ? 1.8 : 1.0) * 128;
+        const double runs = tw == p.nx ? 1 : th, run = tw == p.nx ? tw * th * es : tw * es;
+        block_bytes = runs * (2 * run + edge_ld + edge_st) + 0.25 * 2 * (tw * es + edge_ld) +
+                      2 * th * 128 * 0.32;
+        block_waves = bw + 0.6 * ring_waves * (mix ? 2 : 1);
+        narrow = !mix && p.nx <= 80 && (int64_t)p.nx * p.ny * p.nz > 650000;
+        full = plane(slots);
     }
-    const int64_t nb = (int64_t)((p.nx + tw - 1) / tw) * ((p.ny + th - 1) / th) *
-                       ((p.nz + s.tile_z - 1) / s.tile_z);
-    const int64_t slots = 256 * (int64_t)res;
-    // beyond what the last-level cache holds, stores that bypass L2 pay; rows that start and end
-    // inside a cache line cost the shared line again, for such stores most of all
-    const bool resident = (double)p.nx * p.ny * p.nz * 2 * pops * es < 230e6;
-    const int bytes_el = (int)storage_bytes(p.storage);
-    const bool aligned = (int64_t)p.nx * bytes_el % 128 == 0 && tw * bytes_el % 128 == 0;
-    const double edge_ld = aligned ? 0.0 : 0.65 * 128, edge_st = aligned ? 0.0 : (nt ? 1.8 : 1.0) * 128;
-    const double runs = tw == p.nx ? 1 : th, run = tw == p.nx ? tw * th * es : tw * es;
-    auto plane = [&](int64_t blocks) {
-        const double bytes = pops * (double)blocks *
-                             (runs * (2 * run + edge_ld + edge_st) +
-                              0.25 * 2 * (tw * es + edge_ld) + 2 * th * 128 * 0.32);
-        const double work = (double)((blocks + 255) / 256) * (bw + 0.6 * ring_waves * (mix ? 2 : 1)) *
-                            0.32 * (es == 4 ? 1.0 : 0.6);
+    // tile_z planes a block, `parts` blocks along z (fewer blocks than nodes: 32 bits)
+    double operator()(int tile_z, int parts) const
+    {
+        const uint32_t nb = tiles * (uint32_t)parts, rounds = nb / slots, rest = nb - rounds * slots;
+        double t = (double)rounds * full;
+        if (rest) t += plane(rest);
+        t *= tile_z + 1.3;
+        if (resident && nt) t *= 1.06;
+        if (!resident && aligned && !nt) t *= 1.05;
+        return t;
+    }
+
+private:
+    double plane(uint32_t blocks) const
+    {
+        const double bytes = pops * (double)blocks * block_bytes;
+        const double work =
+            (double)((blocks + 255) / 256) * block_waves * 0.32 * (es == 4 ? 1.0 : 0.6);
         const double lat = mix ? 4.3 : 3.6, mem = bytes / 5.9e6;
         // large boxes of narrow rows: the three overlap less, and a block of many waves, which all
         // wait at its barrier, overlaps least (40 x 250 x 250 FP64 129 -> 95 us a step, 60 x 250 x
         // 240 173 -> 147, FP16 32 x 300 x 300 54 -> 47; small boxes and wider ones pick worse this
         // way: FP16 64^3 9.5 -> 10.9, boxes of 96 .. 264 a row by 4%)
-        if (!mix && p.nx <= 80 && (int64_t)p.nx * p.ny * p.nz > 650000)
-            return std::pow(std::pow(lat, 8) + std::pow(mem, 8) + std::pow(work, 8), 0.125) *
+        if (narrow) {
+            auto pow8 = [](double v) { v *= v; v *= v; return v * v; };
+            return std::sqrt(std::sqrt(std::sqrt(pow8(lat) + pow8(mem) + pow8(work)))) *
                    (1.0 + 0.3 * waves / 16.0);
+        }
         return std::max({lat, mem, work});
-    };
-    double t = (double)(nb / slots) * plane(slots);
-    if (nb % slots) t += plane(nb % slots);
-    t *= s.tile_z + 1.3;
-    if (resident && nt) t *= 1.06;
-    if (!resident && aligned && !nt) t *= 1.05;
-    return t;
-}
+    }
+
+    int waves;
+    bool mix, nt, resident, aligned, narrow;
+    uint32_t tiles, slots;
+    double es, pops, block_bytes, block_waves, full;
+};
 
 // Tile of an untuned box.  D3Q19: the box's row cut into equal parts, as many rows as the block
 // then has threads for, cut evenly too, and equal chunks of planes; the cheapest by the estimate
@@ -396,7 +421,15 @@ StepShape fitted_shape(const sc_params& p, int compute)
     if (p.lattice != SC_D3Q19) return best;
     const bool mix = p.components == 2;
     const size_t es = compute == SC_COMPUTE_F64 ? sizeof(double) : sizeof(float);
+    // every distinct number of planes ceil(nz / gz), gz = 1, 2, .., of at most 512
+    std::vector<std::pair<int, int>> chunks;  // planes, blocks along z
+    for (int gz = std::max(1, (p.nz + 511) / 512); gz <= p.nz;) {
+        const int tz = (p.nz + gz - 1) / gz;
+        chunks.emplace_back(tz, (p.nz + tz - 1) / tz);
+        gz = tz > 1 ? (p.nz + tz - 2) / (tz - 1) : p.nz + 1;
+    }
     double cost = 1e300;
+    std::vector<std::pair<int, int>> seen;  // tiles of smaller blocks
     for (int b : {128, 256, 384, 512, 768, 1024}) {
         if (mix && b > 512) break;
         int last_tw = 0;
@@ -406,20 +439,19 @@ StepShape fitted_shape(const sc_params& p, int compute)
             if (tw > b / 3 || tw == last_tw) continue;
             last_tw = tw;
             const int rows = b / tw, gy = (p.ny + rows - 1) / rows, th = (p.ny + gy - 1) / gy;
-            // every distinct number of planes ceil(nz / gz), gz = 1, 2, ..
-            for (int tz = p.nz, gz = 1; tz > 0; gz = tz > 1 ? (p.nz + tz - 2) / (tz - 1) : p.nz + 1,
-                     tz = gz <= p.nz ? (p.nz + gz - 1) / gz : 0) {
-                if (tz > 512) continue;
+            const StepShape plain{tw, th, 1, mix ? 4 : 1}, nt{tw, th, 1, mix ? 5 : 3};
+            if (!(mix ? mix3d_tile_fits(plain, es) : step3d_tile_fits(plain))) continue;
+            if (std::find(seen.begin(), seen.end(), std::make_pair(tw, th)) != seen.end()) continue;
+            seen.emplace_back(tw, th);
+            const Shape3dCost c1(p, compute, tw, th, plain.variant), c3(p, compute, tw, th, nt.variant);
+            for (const auto& z : chunks)
                 for (int v : {1, 3}) {
-                    const StepShape s{tw, th, tz, mix ? v + (v == 1 ? 3 : 2) : v};
-                    if (!(mix ? mix3d_tile_fits(s, es) : step3d_tile_fits(s))) continue;
-                    const double c = shape3d_cost(p, compute, s);
+                    const double c = v == 1 ? c1(z.first, z.second) : c3(z.first, z.second);
                     if (c < cost) {
                         cost = c;
-                        best = s;
+                        best = StepShape{tw, th, z.first, v == 1 ? plain.variant : nt.variant};
                     }
                 }
-            }
         }
     }
     return best;
@@ -466,6 +498,7 @@ MultiShape multi_shape(const sc_params& p, int compute)
             for (int y = 4; y <= 64; y += 4)
                 for (int npt = 1; npt <= 3; ++npt) {
                     const int nodes = (x + 4 * T - 2) * (y + 4 * T - 2);
+                    if (nodes > npt * 512) continue;
                     const int threads = ((nodes + npt - 1) / npt + 63) & ~63;
                     const MultiShape m{T, x, y, threads};
                     if (!step2d_multi_fits(m, p.storage, compute)) continue;
