@@ -314,12 +314,14 @@ int sc_profile_read(struct sc_sim* sim, int32_t kernel_class, double* ms, int64_
 
 /* Autotuner of the step kernel.  Times every candidate (tile_x, tile_y, tile_z, variant) on the
  * current state with HIP events -- each trial launch reads the current populations and writes the
- * spare buffer, so the simulation is unchanged -- and keeps the fastest for this handle.  (The tile
- * that D3Q19 boxes get by default is fitted to the box and not among them: on small or ragged boxes
- * it is the faster one, by up to four times at 48^3.)  The
+ * spare buffer, so the simulation is unchanged -- and keeps the fastest for this handle.  The
  * choice is remembered for later handles of the same lattice, box, storage, compute type and
- * component count in this process (two components tune their own fused kernel's shapes).  trials >= 1 launches per candidate; out[cap] (may be NULL) receives the timings
- * in candidate order, *n_out the candidate count. */
+ * component count in this process (two components tune their own fused kernel's shapes).  trials
+ * >= 1 launches per candidate; out[cap] (may be NULL) receives the timings in candidate order,
+ * *n_out the candidate count.  The shape that the handle came with, and the one that a box gets by
+ * default (in D3Q19 a tile fitted to it, on small or ragged boxes up to four times as fast as any
+ * candidate), are timed as well: one of them that beats all candidates is kept, and stands in out
+ * in place of the slowest entry there, so that the smallest time is always the kept shape's. */
 typedef struct sc_tune_entry {
     int32_t tile_x, tile_y, tile_z, variant;
     double us_per_launch;

@@ -511,8 +511,7 @@ MultiShape multi_shape(const sc_params& p, int compute)
     return best;
 }
 
-// Shapes chosen by sc_autotune, per (lattice, nx, ny, nz, storage, compute, components), for
-// this process.
+// What sc_autotune chose, per (lattice, nx, ny, nz, storage, compute, components), for this process.
 using TuneKey = std::tuple<int, int, int, int, int, int, int>;
 std::mutex g_tune_mu;
 std::map<TuneKey, StepShape> g_tuned;
@@ -2501,33 +2500,58 @@ int sc_autotune(sc_sim* s, int32_t trials, sc_tune_entry* out, int32_t cap, int3
     hipEvent_t e0, e1;
     HIPX(hipEventCreate(&e0));
     HIPX(hipEventCreate(&e1));
-    double best = 1e300;
-    StepShape best_shape = s->shape;
-    int k = 0;
     int rc = SC_OK;
-    for (const StepShape& sh : cand) {
-        if (!(s->two ? step2c_shape_supported(s->q, sh) : step_shape_supported(s->q, sh))) continue;
-        if (s->grav && sh.variant == 2) continue;  // no pipelined gravity kernel
-        // one untimed launch, then `trials` timed launches
-        hipError_t e = launch(sh);
+    // microseconds a launch: one untimed, then `trials` timed (rc tells of an error)
+    auto time = [&](auto&& one) {
+        hipError_t e = one();
         if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
-        for (int r = 0; r < trials && e == hipSuccess; ++r) e = launch(sh);
+        for (int r = 0; r < trials && e == hipSuccess; ++r) e = one();
         if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-        if (e != hipSuccess) {
-            rc = device_fail(s, e, "autotune trial");
-            break;
+        if (e != hipSuccess) rc = device_fail(s, e, "autotune trial");
+        return 1e3 * ms / trials;
+    };
+    double best = 1e300;
+    StepShape best_shape = s->shape;
+    int k = 0, slowest = -1;
+    for (const StepShape& sh : cand) {
+        if (!(s->two ? step2c_shape_supported(s->q, sh) : step_shape_supported(s->q, sh))) continue;
+        if (s->grav && sh.variant == 2) continue;  // no pipelined gravity kernel
+        const double us = time([&] { return launch(sh); });
+        if (rc != SC_OK) break;
+        if (k < cap) {
+            out[k] = sc_tune_entry{sh.tile_x, sh.tile_y, sh.tile_z, sh.variant, us};
+            if (slowest < 0 || us > out[slowest].us_per_launch) slowest = k;
         }
-        const double us = 1e3 * ms / trials;
-        if (k < cap) out[k] = sc_tune_entry{sh.tile_x, sh.tile_y, sh.tile_z, sh.variant, us};
         ++k;
         if (us < best) {
             best = us;
             best_shape = sh;
         }
     }
+    // the shapes that the handle has, and gets by default, stand against the candidates
+    auto same = [](const StepShape& x, const StepShape& y) {
+        return x.tile_x == y.tile_x && x.tile_y == y.tile_y && x.tile_z == y.tile_z &&
+               x.variant == y.variant;
+    };
+    std::vector<StepShape> own{fitted_shape(s->p, s->compute)};
+    if (!same(own[0], s->shape)) own.push_back(s->shape);
+    bool kept = false;
+    for (const StepShape& sh : own) {
+        if (rc != SC_OK ||
+            std::any_of(cand.begin(), cand.end(), [&](const StepShape& c) { return same(c, sh); }))
+            continue;
+        const double us = time([&] { return launch(sh); });
+        if (rc != SC_OK || us >= best) continue;
+        best = us;
+        best_shape = sh;
+        kept = true;
+    }
+    if (rc == SC_OK && kept && slowest >= 0)
+        out[slowest] = sc_tune_entry{best_shape.tile_x, best_shape.tile_y, best_shape.tile_z,
+                                     best_shape.variant, best};
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != SC_OK) return rc;
