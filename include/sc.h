@@ -321,7 +321,9 @@ int sc_profile_read(struct sc_sim* sim, int32_t kernel_class, double* ms, int64_
  * *n_out the candidate count.  The shape that the handle came with, and the one that a box gets by
  * default (in D3Q19 a tile fitted to it, on small or ragged boxes up to four times as fast as any
  * candidate), are timed as well: one of them that beats all candidates is kept, and stands in out
- * in place of the slowest entry there, so that the smallest time is always the kept shape's. */
+ * in place of the slowest entry there, so that the smallest time is always the kept shape's.  One
+ * component in D2Q9 also times several steps a launch and takes them, where steps follow one
+ * another, unless a single step of the kept shape is faster; out lists single steps only. */
 typedef struct sc_tune_entry {
     int32_t tile_x, tile_y, tile_z, variant;
     double us_per_launch;

@@ -514,7 +514,11 @@ MultiShape multi_shape(const sc_params& p, int compute)
 // What sc_autotune chose, per (lattice, nx, ny, nz, storage, compute, components), for this process.
 using TuneKey = std::tuple<int, int, int, int, int, int, int>;
 std::mutex g_tune_mu;
-std::map<TuneKey, StepShape> g_tuned;
+struct Tuned {
+    StepShape shape;
+    MultiShape multi;
+};
+std::map<TuneKey, Tuned> g_tuned;
 
 TuneKey tune_key(const sc_params& p, int compute)
 {
@@ -1481,7 +1485,10 @@ int sc_create(const sc_params* p, sc_sim** out)
         s->multi = multi_shape(*p, s->compute);
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(tune_key(*p, s->compute));
-        if (it != g_tuned.end()) s->shape = it->second;
+        if (it != g_tuned.end()) {
+            s->shape = it->second.shape;
+            s->multi = it->second.multi;
+        }
     }
     s->grav = p->gravity[0] != 0.0 || p->gravity[1] != 0.0 ||
               (p->lattice == SC_D3Q19 && p->gravity[2] != 0.0);
@@ -2552,13 +2559,23 @@ int sc_autotune(sc_sim* s, int32_t trials, sc_tune_entry* out, int32_t cap, int3
     if (rc == SC_OK && kept && slowest >= 0)
         out[slowest] = sc_tune_entry{best_shape.tile_x, best_shape.tile_y, best_shape.tile_z,
                                      best_shape.variant, best};
+    // in 2D, several steps a launch against single ones
+    MultiShape multi = multi_shape(s->p, s->compute);
+    if (rc == SC_OK && multi.T > 1) {
+        const double us = time([&] {
+            return launch_step2d_multi(s->p.storage, s->compute, s->f[s->cur], s->f[s->cur ^ 1], a,
+                                       multi, multi.T, s->stream);
+        });
+        if (us >= best * multi.T) multi = MultiShape{1, 0, 0, 0};
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != SC_OK) return rc;
     s->shape = best_shape;
+    s->multi = multi;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[tune_key(s->p, s->compute)] = best_shape;
+        g_tuned[tune_key(s->p, s->compute)] = Tuned{best_shape, multi};
     }
     if (n_out) *n_out = k;
     return SC_OK;

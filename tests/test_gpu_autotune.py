@@ -1,12 +1,24 @@
 """The tuner keeps what is fastest, the shape a box has by default included: the fitted tile of a small
-D3Q19 box (which no candidate comes near), for the handle and for the ones that follow it; and its
-table's smallest time is the kept shape's."""
+D3Q19 box (which no candidate comes near), and the several steps a launch of a D2Q9 box; for the
+handle and for the ones that follow it; and its table's smallest time is the kept shape's."""
+import time
+
 import numpy as np
 import pytest
 
 from paper_1708_01608_amd import sc, workloads
 
 pytestmark = pytest.mark.gpu
+
+
+def _step_us(g, n=400):
+    g.step(n)
+    best = 1e9
+    for _ in range(5):
+        t0 = time.perf_counter()
+        g.step(n)
+        best = min(best, time.perf_counter() - t0)
+    return best / n * 1e6
 
 
 @pytest.mark.parametrize("kw,count", [
@@ -34,3 +46,23 @@ def test_the_fitted_tile_is_kept_when_it_is_the_fastest(kw, count):
     for x in (g, h, s):
         x.close()
 
+
+@pytest.mark.parametrize("compute", ["f64", "f32"])
+def test_several_steps_a_launch_stand_against_single_ones(compute):
+    box = dict(q=9, nx=130, ny=126, tau=0.9, K=0, compute=compute)
+    g = sc.Sim(**box)
+    fast = _step_us(g)
+    g.autotune(trials=20)
+    h = sc.Sim(**box)
+    s = sc.Sim(**box, tile=(64, 1, 4), variant=1)
+    slow = _step_us(s)
+    s.autotune(trials=20)
+    times = [_step_us(x) for x in (g, h, s)]
+    print(f"[gpu] 130 x 126 {compute}: {fast:.2f} us a step by default, {slow:.2f} with a tile given; "
+          f"tuned {[round(t, 2) for t in times]}", flush=True)
+    assert slow > 1.5 * fast and max(times) < 1.25 * fast
+    ref = sc.Sim(**box, tile=(64, 1, 4), variant=1)
+    ref.step(s.t)
+    assert np.array_equal(ref.get_populations(), s.get_populations())
+    for x in (g, h, s, ref):
+        x.close()
