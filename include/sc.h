@@ -84,7 +84,11 @@ typedef struct sc_params {
     const sc_allocator* allocator; /* NULL: hipMalloc / hipFree */
     int32_t tile_x, tile_y, tile_z; /* step-kernel tile; 0 selects the default (all four fields 0:
                                        in D3Q19 a tile fitted to the box, of any width and height,
-                                       which sc_step_config reports but no field here accepts) */
+                                       which sc_step_config reports and which is accepted here for
+                                       boxes of the same size, with any tile_z; in D2Q9 with one
+                                       component also several steps a launch, where steps follow
+                                       one another: a tile given here means single steps, and
+                                       sc_step_config reports the single steps' tile) */
     int32_t step_variant;      /* 0 default, 1 plain marching, 2 software-pipelined (D3Q19),
                                   3 plain with non-temporal population stores; with two
                                   components also 4 and 5 (D3Q19, one component per wave) */

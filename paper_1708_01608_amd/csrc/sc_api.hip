@@ -558,8 +558,10 @@ std::vector<StepShape> tune_candidates_2c(int q, int nz)
     return c;
 }
 
-// Explicit tile and variant from the parameters, defaults filling the fields left at zero.
-StepShape shape_from_params(const sc_params& p)
+// Explicit tile and variant from the parameters, defaults filling the fields left at zero.  False if
+// no kernel runs them.  Besides the fixed tiles, a D3Q19 box takes the ones that sc_step_config
+// reports of a box of its size (fitted, by storage and arithmetic type), with any number of planes.
+bool shape_from_params(const sc_params& p, StepShape* out)
 {
     StepShape sh = default_shape(p);
     if (p.tile_x) sh.tile_x = p.tile_x;
@@ -567,7 +569,23 @@ StepShape shape_from_params(const sc_params& p)
     if (p.lattice == SC_D2Q9) sh.tile_y = 1;
     if (p.tile_z) sh.tile_z = p.tile_z;
     if (p.step_variant) sh.variant = p.step_variant;
-    return sh;
+    *out = sh;
+    const bool mix = p.components == 2;
+    if (mix ? step2c_shape_supported(p.lattice, sh) : step_shape_supported(p.lattice, sh)) return true;
+    if (p.lattice != SC_D3Q19 || !p.tile_x || !p.tile_y) return false;
+    const int types[][2] = {{SC_STORE_F32, SC_COMPUTE_F64}, {SC_STORE_F32, SC_COMPUTE_F32},
+                            {SC_STORE_F16, SC_COMPUTE_F32}};
+    for (const auto& t : types) {
+        if (mix && t[0] == SC_STORE_F32 && t[1] == SC_COMPUTE_F32) continue;
+        sc_params q = p;
+        q.storage = t[0];
+        const StepShape f = fitted_shape(q, t[1]);
+        if (f.tile_x != sh.tile_x || f.tile_y != sh.tile_y) continue;
+        if (!p.step_variant) out->variant = f.variant;
+        const size_t es = p.storage == SC_STORE_F32 ? sizeof(double) : sizeof(float);
+        return mix ? mix3d_tile_fits(*out, es) : step3d_tile_fits(*out);
+    }
+    return false;
 }
 
 int prof_begin(sc_sim* s, int cls, hipEvent_t* out_b)
@@ -1387,10 +1405,8 @@ int validate(const sc_params* p)
     if (p->allocator && (!p->allocator->alloc || !p->allocator->free))
         return fail(SC_E_INVAL, "allocator needs alloc and free");
     if (p->tile_x || p->tile_y || p->tile_z || p->step_variant) {
-        StepShape sh = shape_from_params(*p);
-        const bool ok = p->components == 2 ? step2c_shape_supported(p->lattice, sh)
-                                           : step_shape_supported(p->lattice, sh);
-        if (!ok) return fail(SC_E_INVAL, "unsupported step tile");
+        StepShape sh;
+        if (!shape_from_params(*p, &sh)) return fail(SC_E_INVAL, "unsupported step tile");
     }
     return SC_OK;
 }
@@ -1479,8 +1495,9 @@ int sc_create(const sc_params* p, sc_sim** out)
     s->compute = p->compute != SC_COMPUTE_AUTO
                      ? p->compute
                      : (p->storage == SC_STORE_F32 ? SC_COMPUTE_F64 : SC_COMPUTE_F32);
-    s->shape = shape_from_params(*p);
-    if (!(p->tile_x || p->tile_y || p->tile_z || p->step_variant)) {
+    if (p->tile_x || p->tile_y || p->tile_z || p->step_variant) {
+        (void)shape_from_params(*p, &s->shape);  // (validated)
+    } else {
         s->shape = fitted_shape(*p, s->compute);
         s->multi = multi_shape(*p, s->compute);
         std::lock_guard<std::mutex> lk(g_tune_mu);
