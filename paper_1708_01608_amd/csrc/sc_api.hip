@@ -60,6 +60,7 @@ struct sc_sim {
     int cur = 0;
     StepShape shape{};
     MultiShape multi{1, 0, 0, 0};
+    bool coef_once = false;  // Step2cArgs::k_l
     int64_t t = 0;
     int latched = 0;
 
@@ -245,6 +246,12 @@ Step2cArgs step2c_args(const sc_sim* s)
     a.tau_l = s->p.tau;
     a.tau_v = s->tau_v;
     a.Gx = s->p.G_cross;
+    auto k = [&](double tau) {
+        if (s->compute == SC_COMPUTE_F64 || s->coef_once) return -(tau * s->p.G_cross);
+        return (double)(-(float)tau * (float)s->p.G_cross);
+    };
+    a.k_l = k(s->p.tau);
+    a.k_v = k(s->tau_v);
     a.ref_l = s->rho_ref;
     a.ref_v = s->rho_ref_v;
     return a;
@@ -517,6 +524,7 @@ std::mutex g_tune_mu;
 struct Tuned {
     StepShape shape;
     MultiShape multi;
+    bool coef_once;
 };
 std::map<TuneKey, Tuned> g_tuned;
 
@@ -586,6 +594,12 @@ bool shape_from_params(const sc_params& p, StepShape* out)
         return mix ? mix3d_tile_fits(*out, es) : step3d_tile_fits(*out);
     }
     return false;
+}
+
+// A fixed tile of the mixture's kernel with one component a wave (Step2cArgs::k_l).
+bool split_tile(const sc_params& p, const StepShape& s)
+{
+    return p.components == 2 && s.variant >= 4 && step2c_shape_supported(p.lattice, s);
 }
 
 int prof_begin(sc_sim* s, int cls, hipEvent_t* out_b)
@@ -1497,6 +1511,7 @@ int sc_create(const sc_params* p, sc_sim** out)
                      : (p->storage == SC_STORE_F32 ? SC_COMPUTE_F64 : SC_COMPUTE_F32);
     if (p->tile_x || p->tile_y || p->tile_z || p->step_variant) {
         (void)shape_from_params(*p, &s->shape);  // (validated)
+        s->coef_once = split_tile(*p, s->shape);
     } else {
         s->shape = fitted_shape(*p, s->compute);
         s->multi = multi_shape(*p, s->compute);
@@ -1505,6 +1520,7 @@ int sc_create(const sc_params* p, sc_sim** out)
         if (it != g_tuned.end()) {
             s->shape = it->second.shape;
             s->multi = it->second.multi;
+            s->coef_once = it->second.coef_once;
         }
     }
     s->grav = p->gravity[0] != 0.0 || p->gravity[1] != 0.0 ||
@@ -2588,11 +2604,15 @@ int sc_autotune(sc_sim* s, int32_t trials, sc_tune_entry* out, int32_t cap, int3
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != SC_OK) return rc;
+    if (!kept)
+        s->coef_once = split_tile(s->p, best_shape);
+    else if (!same(best_shape, s->shape))
+        s->coef_once = false;  // back to the default's tile
     s->shape = best_shape;
     s->multi = multi;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[tune_key(s->p, s->compute)] = Tuned{best_shape, multi};
+        g_tuned[tune_key(s->p, s->compute)] = Tuned{best_shape, multi, s->coef_once};
     }
     if (n_out) *n_out = k;
     return SC_OK;

@@ -77,6 +77,12 @@ struct Step2cArgs {
     int planes;  // set by launch_step2c from the shape
     int64_t N;
     double tau_l, tau_v, Gx;
+    // tau_a F_a / rho_a = k_a (sum over the other component), k_a = -tau_a Gx.  With FP32 arithmetic
+    // an FP32 value: the product of the factors rounded to FP32, or, where the caller gave a tile of
+    // the kernel with one component a wave or had the tuner choose it, the FP64 product rounded once.
+    // (Both are as these calls have always had them; an ulp apart, they give other roundings of
+    // 16-bit populations.)
+    double k_l, k_v;
     double ref_l, ref_v;  // storage shifts of the two components (0 with FP32 storage)
 };
 bool step2c_shape_supported(int q, const StepShape& s);

@@ -43,15 +43,16 @@ __device__ __forceinline__ void momentum(const float* g, A& jx, A& jy, A& jz)
 
 template <typename A>
 struct MixCoef {
-    A tau_l, tau_v, il, iv, Gx;  // il = 1 / tau_l, iv = 1 / tau_v
-    A ref_l, ref_v;              // storage shifts of the liquid and the gas component
+    A il, iv;        // 1 / tau_l, 1 / tau_v
+    A kl, kv;        // tau_a F_a / rho_a = k_a (sum over the other component): rho_a cancels
+    A ref_l, ref_v;  // storage shifts of the liquid and the gas component
 };
 
 template <typename A>
 __device__ __forceinline__ MixCoef<A> mix_coef(const Step2cArgs& a)
 {
-    return MixCoef<A>{(A)a.tau_l, (A)a.tau_v, (A)(1.0 / a.tau_l), (A)(1.0 / a.tau_v), (A)a.Gx,
-                      (A)a.ref_l, (A)a.ref_v};
+    return MixCoef<A>{(A)(1.0 / a.tau_l), (A)(1.0 / a.tau_v), (A)a.k_l, (A)a.k_v, (A)a.ref_l,
+                      (A)a.ref_v};
 }
 
 // Collision of both components of one node and the stores.  drl, drv are the density
@@ -71,12 +72,10 @@ __device__ __forceinline__ void mix_collide(S* __restrict__ dl, S* __restrict__ 
     const A upx = fmad(jlx, c.il, jvx * c.iv) * iden;
     const A upy = fmad(jly, c.il, jvy * c.iv) * iden;
     const A upz = fmad(jlz, c.il, jvz * c.iv) * iden;
-    // tau_a F_a / rho_a = -tau_a Gx (sum over the other component): rho_a cancels
-    const A kl = -c.tau_l * c.Gx, kv = -c.tau_v * c.Gx;
-    relax_store<Q, A, S, NT>(dl, N, lane, gl, drl, rl, fmad(kl, slx, upx), fmad(kl, sly, upy),
-                             fmad(kl, slz, upz), c.il);
-    relax_store<Q, A, S, NT>(dv, N, lane, gv, drv, rv, fmad(kv, svx, upx), fmad(kv, svy, upy),
-                             fmad(kv, svz, upz), c.iv);
+    relax_store<Q, A, S, NT>(dl, N, lane, gl, drl, rl, fmad(c.kl, slx, upx), fmad(c.kl, sly, upy),
+                             fmad(c.kl, slz, upz), c.il);
+    relax_store<Q, A, S, NT>(dv, N, lane, gv, drv, rv, fmad(c.kv, svx, upx), fmad(c.kv, svy, upy),
+                             fmad(c.kv, svz, upz), c.iv);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -297,7 +296,7 @@ __global__ void __launch_bounds__(B) k_mix3d_split(const S* __restrict__ sl,
     S* __restrict__ dst = comp ? dv : dl;
     const A il = (A)(1.0 / a.tau_l), iv = (A)(1.0 / a.tau_v);
     const A ia = comp ? iv : il;
-    const A ka = -(A)(comp ? a.tau_v : a.tau_l) * (A)a.Gx;  // tau_a F_a / rho_a = ka sum(rho_b)
+    const A ka = (A)(comp ? a.k_v : a.k_l);  // tau_a F_a / rho_a = ka sum(rho_b)
     const A ref_l = (A)a.ref_l, ref_v = (A)a.ref_v, ref_a = comp ? ref_v : ref_l;
     const int ty = t / tw, tx = t - ty * tw;
     const int x0 = bx * tw, y0 = by * th, z0 = bz * a.planes;
