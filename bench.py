@@ -306,6 +306,8 @@ def run_batch(args):
                      "unit": "GB/s", "frac": round(m["achieved"] / HBM_PEAK_GBS, 4),
                      "traffic": batch_traffic_from_profile(compute, m["rows_per_thread"],
                                                            m["node_steps"]),
+                     # (what a step by itself must move; the kernel takes two steps a sweep, and
+                     # `traffic` is what it was measured to move)
                      "kernel": "k_batch", "bytes_per_node_step": 72,
                      "kernel_ms": round(m["kms"] / args.steps, 3)},
         "one_by_one_MLUPS": round(m["one_by_one"], 1) if m["one_by_one"] is not None else None,
@@ -446,6 +448,9 @@ def main():
             "bytes_per_launch": bytes_per_launch,
             "avg_launch_us": round(avg_s * 1e6, 2),
             "launches": r["launches"],
+            # a launch here is a time step, and bytes_per_launch what a step by itself must move: in
+            # one-component 2D several steps share a launch, which moves less than their sum
+            "launch": "time step",
         },
         "stencil_only_MLUPS": round(spec.N / avg_s / 1e6, 1),
         "breakdown_ms": {

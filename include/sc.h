@@ -312,7 +312,10 @@ int sc_test_pass(struct sc_sim* sim);
 
 /* Per-kernel-class timing with HIP events on the simulation's stream: enable != 0 starts
  * recording (and clears the counters); sc_profile_read returns the summed kernel time in ms and
- * the launch count of one class since then. */
+ * the launch count of one class since then.  SC_KERNEL_STEP counts a time step as one launch, also
+ * where several D2Q9 steps share one; SC_KERNEL_SOURCE counts the steps that feed bubbles, and where
+ * a D3Q19 step adds the source of the step before (many fed nodes on FP32 storage), its time is that
+ * of closing the ledger, the rest is in the step's. */
 int sc_profile(struct sc_sim* sim, int32_t enable);
 int sc_profile_read(struct sc_sim* sim, int32_t kernel_class, double* ms, int64_t* launches);
 

@@ -36,7 +36,7 @@ struct DevBuf {
 struct ProfRec {
     hipEvent_t a, b;
     int cls;
-    int launches = 1;  // kernel launches between a and b (a K-step graph records K)
+    int launches = 1;  // SC_KERNEL_STEP: time steps between a and b; else 1
 };
 
 }  // namespace
@@ -1903,6 +1903,8 @@ int sc_step(sc_sim* s, int32_t nsteps)
                               led.nb};
             HIPX(launch_step_fed(s->compute, s->f[s->cur], s->f[s->cur ^ 1], a, s->shape, fed,
                                  s->stream));
+            TRY(prof_end(s, pe));
+            TRY(prof_begin(s, SC_KERNEL_SOURCE, &pe));  // (what is left of it)
             HIPX(launch_source_close(led, s->stream));
             owed_pos = -1;
         } else {
