@@ -965,10 +965,6 @@ int ensure_stage(sc_sim* s, int n)
     return SC_OK;
 }
 
-// The test pass in three parts.  pass_prepare allocates what the pass needs and stages the merge
-// groups; pass_enqueue queues every kernel and copy up to the pass's one synchronization (no
-// allocation, no host read of device data, so it can be captured in a graph); pass_finish
-// synchronizes and runs the host registry on what came back.
 // Whether the source of a step goes into the step after it: the plain D3Q19 kernel on FP32 storage
 // (16-bit storage rounds stochastically, and the barrier's fix-up pulls by itself), and enough fed
 // nodes that the map's read by every node (about 12 us at 256^3) is less than the source kernel
@@ -979,6 +975,10 @@ bool source_joins_step(const sc_sim* s, int nb)
            s->list_count > s->N / 64 && step_fed_fits(s->shape, nb);
 }
 
+// The test pass in three parts.  pass_prepare allocates what the pass needs and stages the merge
+// groups; pass_enqueue queues every kernel and copy up to the pass's one synchronization (no
+// allocation, no host read of device data, so it can be captured in a graph); pass_finish
+// synchronizes and runs the host registry on what came back.
 int pass_prepare(sc_sim* s, bool with_criterion)
 {
     const int n = (int)s->rad.size();

@@ -827,8 +827,9 @@ namespace {
 // threads were slower than the better of the two everywhere (164 and 123 ms at 2048).  Boxes of up
 // to 48^2 are a few row blocks: the narrow one as soon as there is more than one a CU (512 of 48^2
 // 0.32 / 0.42).  The smallest are one block, and the latency of a step is all: two slots a lane, of
-// which the compiler interleaves the loads and which no register cap makes spill (4 to 64 boxes of
-// 16^2, one slot and two 0.84 / 0.72, 512 of 32^2 2.2 / 2.0; 2,000 of 16^2 3.1 / 2.1, of 32^2 3.6 / 4.3).
+// which the compiler interleaves the loads and which no register cap makes spill (one slot in single
+// steps and two: 64 boxes of 16^2 0.84 / 0.59, 512 of 32^2 2.0 / 1.6, 2,000 of 16^2 3.1 / 2.0; 2,000
+// of 32^2 3.6 / 4.2).
 struct BatchShape {
     int rb, threads;
 };

@@ -178,10 +178,6 @@ hipError_t launch_labels(int q, uint32_t* labels, uint32_t* scratch, uint32_t* n
                          const FieldArgs& a, hipStream_t st);
 
 // Bubble statistics and the merge test.
-hipError_t launch_gather_labels(const uint32_t* labels, const int64_t* nodes_d, uint32_t* out_d,
-                                int n, int64_t N, hipStream_t st);
-hipError_t launch_set_slots(int32_t* slot_of_root, const uint32_t* labels_of_bubbles_d, int nb,
-                            int clear, hipStream_t st);
 // scratch: of the labelling that wrote these labels (its mask words).
 hipError_t launch_stats(const uint32_t* labels, uint32_t* scratch, const int32_t* slot_of_root,
                         const int32_t* anchors_d, unsigned long long* count_d,
@@ -268,10 +264,7 @@ struct StageOut {
     MergeResult* dst_res;
     int n, ledger_nb, npairs;
 };
-hipError_t launch_stage_out(const StageOut& o, hipStream_t st);
 
-// The tail of a test pass in one block: with do_pairs, the candidate pairs (as launch_pairs)
-// and their merge test; then the read-back (as launch_stage_out).
 // The pass of a small one-component box in one launch, behind launch_mask_words (its mask words and
 // the totals' partial sums): labels, totals, table, statistics, pairs, read-back.
 constexpr int kSmallParts = 128;  // blocks of the partial sums of 2^15 nodes
@@ -291,6 +284,8 @@ bool small_pass_fits(const FieldArgs& a);
 hipError_t launch_pass_small(int q, int storage, const void* f, uint32_t* scratch,
                              uint32_t* labels, const double* partials, double* tot,
                              const SmallPass& p, const FieldArgs& a, hipStream_t st);
+// The tail of a test pass in one block: with do_pairs, the candidate pairs (as launch_pairs)
+// and their merge test; then the read-back.
 hipError_t launch_pass_tail(int q, int storage, const BubbleTab& t, const int32_t* group,
                             int film_max, MergePair* pairs, int32_t* ab, MergeResult* res,
                             int cap, int do_pairs, const StageOut& o, const void* f,
@@ -353,7 +348,5 @@ hipError_t launch_frontier_list(int q, const uint16_t* owner, uint32_t* list,
                                 unsigned int* count_d, const FieldArgs& a, hipStream_t st);
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n,
-                           hipStream_t st);
 
 }  // namespace sc

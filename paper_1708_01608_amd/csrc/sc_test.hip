@@ -214,21 +214,6 @@ __global__ void __launch_bounds__(256) k_totals(const S* f, double* partials, Fi
 }
 
 // ---- bubble statistics ------------------------------------------------------------------------
-__global__ void k_gather(const uint32_t* labels, const int64_t* nodes, uint32_t* out, int n,
-                         int64_t N)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int64_t nd = nodes[k];
-    out[k] = (nd >= 0 && nd < N) ? labels[nd] : 0u;
-}
-
-__global__ void k_set_slots(int32_t* slot_of_root, const uint32_t* labs, int nb, int clear)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nb) slot_of_root[labs[b] - 1] = clear ? -1 : b;
-}
-
 // One mask word a thread, its runs at once: 256^3 with 1.45 M gas nodes in 200 bubbles 171 us with a
 // node a thread, whose 200,000 atomics met on 200 lines.
 __global__ void __launch_bounds__(256) k_stats(const uint32_t* __restrict__ labels,
@@ -761,13 +746,6 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n)
         p[k] = v;
 }
 
-__global__ void k_fill_u64(unsigned long long* p, unsigned long long v, int64_t n)
-{
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x)
-        p[k] = v;
-}
-
 // ---- launchers ------------------------------------------------------------------------------
 #define SC_DISPATCH(q, storage, CALL)                                                             \
     do {                                                                                          \
@@ -836,24 +814,6 @@ hipError_t launch_totals(int q, int storage, const void* f, double* partials, do
     return launch_totals_final(partials, nb, out_d, (double)a.N * a.rho_ref_d, st);
 }
 
-hipError_t launch_gather_labels(const uint32_t* labels, const int64_t* nodes_d, uint32_t* out_d,
-                                int n, int64_t N, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather, dim3((n + 255) / 256), dim3(256), 0, st, labels, nodes_d, out_d,
-                       n, N);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_slots(int32_t* slot_of_root, const uint32_t* labs_d, int nb, int clear,
-                            hipStream_t st)
-{
-    if (nb <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_set_slots, dim3((nb + 255) / 256), dim3(256), 0, st, slot_of_root,
-                       labs_d, nb, clear);
-    return hipGetLastError();
-}
-
 hipError_t launch_stats(const uint32_t* labels, uint32_t* scratch, const int32_t* slot_of_root,
                         const int32_t* anchors_d, unsigned long long* count_d,
                         unsigned long long* sums_d, const FieldArgs& a, hipStream_t st)
@@ -916,14 +876,6 @@ __device__ void stage_out_body(const StageOut& o)
         o.dst_ab[2 * k + 1] = o.ab[2 * k + 1];
         o.dst_res[k] = o.res[k];
     }
-}
-
-__global__ void __launch_bounds__(256) k_stage_out(StageOut o) { stage_out_body(o); }
-
-hipError_t launch_stage_out(const StageOut& o, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_stage_out, dim3(1), dim3(256), 0, st, o);
-    return hipGetLastError();
 }
 
 // ---- device bubble table and candidate pairs --------------------------------------------------
@@ -1157,7 +1109,7 @@ __global__ void __launch_bounds__(1024) k_pass_small(uint32_t* scratch,
         }
     }
     __syncthreads();
-    if (t < 4) {  // the partials in block order, as launch_totals_final
+    if (t < 4) {  // the partials in block order (launch_totals_final: by lanes, other roundings)
         double s = 0.0;
         for (int b = 0; b < nparts; ++b) s += part[4 * b + t];
         tot[t] = t == 0 ? base_mass + s : s;
@@ -1357,14 +1309,6 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_i32, grid_for(n), dim3(256), 0, st, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n,
-                           hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_u64, grid_for(n), dim3(256), 0, st, p, v, n);
     return hipGetLastError();
 }
 
