@@ -9,14 +9,14 @@
 // together fit the N entries of the caller's scratch.
 //   1. mask words (from a byte mask, from rho < threshold, or with the FP64 totals of the same
 //      sweep);
-//   2. k_label_local: a block unites the runs of its tile (256 words: 16 x 16 rows of 64 nodes, in
-//      2D 256 rows) in LDS and writes every run's parent;
+//   2. k_label_local: a block unites the runs of its tile (16 x 16 rows of 64 nodes, in 2D 256
+//      rows or 128) in LDS and writes every run's parent;
 //   3. k_label_cross: the links between tiles, between segments and around the box, in global
 //      memory;
 //   4. k_label_flatten: every gas node takes its run's root.
 // Roots link to the smaller index, so the labels are canonical whatever the order of the unions.
 // 256^3 mask with 8.6% gas in 200 balls, microseconds with a union a node (local in 16^3 tiles) and
-// now: mask 25 -> 6, local 118 -> 22, cross 268 -> 31, flatten 36 -> 34; the call 477 -> 115.
+// now: mask 25 -> 6, local 118 -> 21, cross 268 -> 30, flatten 36 -> 36; the call 477 -> 111.
 #include <algorithm>
 
 #include "sc_device.hpp"
